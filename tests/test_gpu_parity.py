@@ -860,6 +860,30 @@ def test_trial_division_flags():
     assert [int(v) for v in got] == [int(primality.trial_division(n, primes=pr)) for n in big]
 
 
+@pytest.mark.parametrize("limbs,count,n_primes", [
+    (1, 9, 1), (1, 130, 257), (2, 8, 256), (7, 17, 600), (31, 129, 10000), (32, 1, 10000),
+    (33, 16, 255), (40, 137, 10000), (65, 24, 5000), (96, 5, 10000)])
+def test_trial_division_edges(limbs, count, n_primes):
+    """Rows around the 8- and 32-limb steps of the limb sums, candidate counts
+    around the groups of 8 and the second pass's 128, prime counts around the
+    first pass's 256: random rows of either parity, rows of zeros and ones
+    bits, multiples of single primes of either pass, and the primes
+    themselves (short values in long rows)."""
+    from paper_1305_3699_amd import trial_division
+    pr = primality.small_primes(10000)
+    rng = random.Random(limbs * 1000 + count)
+    top = 1 << (32 * limbs)
+    picks = [pr[0], pr[min(255, n_primes - 1)], pr[min(256, n_primes - 1)], pr[n_primes - 1], pr[n_primes // 2]]
+    vals = [top - 1, 0] + picks
+    vals += [(rng.randrange(top // p) | 1) * p for p in picks]
+    vals = [v for v in vals if v < top][:count]
+    while len(vals) < count:
+        vals.append(rng.randrange(top) | rng.randrange(2))
+    got = _flags(trial_division(_dev(gen.to_limbs(vals, limbs)), n_primes=n_primes))
+    want = [int(all(n % p or n == p for p in pr[:n_primes])) for n in vals]
+    assert [int(v) for v in got] == want
+
+
 def _mr_case(cands, rounds, limbs, seed):
     from paper_1305_3699_amd import miller_rabin
     rng = random.Random(seed)
