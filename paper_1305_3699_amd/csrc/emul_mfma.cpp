@@ -21,8 +21,8 @@ struct MCtx {
     const MLayout ly;
     int K;
     // [W][4MT][4 bytes][64*KSTEPS]: the A-row byte b of each slot, per K index
-    // (A2s: the key's second extension for scaled B residues)
-    std::vector<int16_t> A1, A2, A2s;
+    // (A2s: the key's second extension for scaled B residues; AX: the exit)
+    std::vector<int16_t> A1, A2, A2s, AX;
     bool sq;    // B residues kept scaled (x R s_i): the key holds the scaled form
 
     MCtx(const MfmaTables &t, bool scaled) : T(t), ly(t.shape), K(t.shape.K), sq(scaled && t.scaled) {
@@ -30,6 +30,7 @@ struct MCtx {
         A1.assign((size_t)ly.W * SW * 4 * KK, 0);
         A2.assign((size_t)ly.W * SW * 4 * KK, 0);
         if (sq) A2s.assign(A2.size(), 0);
+        AX.assign(A2.size(), 0);
         for (int w = 0; w < ly.W; w++)
             for (int s = 0; s < SW; s++)
                 for (int b = 0; b < 4; b++)
@@ -37,6 +38,7 @@ struct MCtx {
                         const size_t at = (((size_t)w * SW + s) * 4 + b) * KK + kap;
                         A1[at] = tile_byte(T.key.data() + ly.a1(), w, s, b, kap);
                         A2[at] = tile_byte(T.base.data() + ly.a2(), w, s, b, kap);
+                        AX[at] = tile_byte(T.base.data() + ly.xt(), w, s, b, kap);
                         if (sq) A2s[at] = tile_byte(T.key.data() + ly.a2s(), w, s, b, kap);
                     }
     }
@@ -323,49 +325,33 @@ bool emul_modexp_mfma(const ModPlan &mp, const MfmaTables &T, const std::vector<
         mm(c, a, unit, dig1, dig2, false);
         // leave the RNS, element by element
         for (int e = 0; e < NM && g0 + e < batch; e++) {
-            std::vector<uint32_t> X(K), acc(L + 1), tmp(L + 1);
-            uint32_t s2 = 0;
-            for (int j = 0; j < K; j++) {
-                const uint32_t v = dig2[(size_t)e * BROW + j] ^ kDigitBias;
-                X[j] = v;
-                s2 += v * T.base[ly.mplo() + j];
+            // limb sums of sum_j xi'_j M'_j, each made positive by the offset
+            // (alpha from limb 0); minus alpha M' modulo 2^(32 (K+1))
+            std::vector<uint64_t> t(K + 1);
+            for (int l = 0; l <= K; l++) {
+                const int64_t S = extension(c.AX, (size_t)l, dig2, e, 64 * ly.KSTEPS(), BROW, K) + (int64_t)kExitOffset;
+                if (S < 0) t_in_range = false;
+                t[l] = (uint64_t)S;
             }
-            const uint32_t alpha = (s2 - a.r[e]) * T.base[ly.bscal()];
-            uint64_t cy = 0;
-            for (int l = 0; l <= L; l++) {
-                Acc sum;
-                sum.lo = cy;
-                for (int j = 0; j < K; j++) acc_mac(sum, X[j], T.base[ly.MpL() + (size_t)j * (K + 1) + l]);
-                uint64_t lo;
-                uint32_t top;
-                acc_value(sum, lo, top);
-                acc[l] = (uint32_t)lo;
-                cy = (lo >> 32) | ((uint64_t)top << 32);
+            const uint32_t alpha = ((uint32_t)t[0] - a.r[e]) * T.base[ly.bscal()];
+            std::vector<uint32_t> acc(K + 1);
+            uint64_t cy = alpha;
+            for (int l = 0; l <= K; l++) {
+                const uint64_t v = t[l] + (uint64_t)alpha * ~T.base[ly.MpF() + l] + cy;
+                acc[l] = (uint32_t)v;
+                cy = v >> 32;
             }
-            uint64_t carry = 0;
-            uint32_t borrow = 0;
-            for (int l = 0; l <= L; l++) {
-                const uint64_t p = (uint64_t)alpha * T.base[ly.MpF() + l] + carry;
-                carry = p >> 32;
-                const uint32_t v = acc[l], pl = (uint32_t)p;
-                const uint32_t d = v - pl, d2 = d - borrow;
-                borrow = (v < pl) | (d < borrow);
-                acc[l] = d2;
-            }
-            int qb = 0;
-            while ((1 << qb) <= K + 1) qb++;
-            for (int b = qb - 1; b >= 0; b--) {
-                uint32_t br = 0;
-                for (int l = 0; l <= L; l++) {
-                    const uint32_t nlo = l < L ? T.key[ly.Nl() + l] : 0u;
-                    const uint32_t nhi = (b && l > 0) ? (T.key[ly.Nl() + l - 1] >> (32 - b)) : 0u;
-                    const uint32_t nl = (nlo << b) | nhi;
-                    const uint32_t v = acc[l];
-                    const uint32_t d = v - nl, d2 = d - br;
-                    br = (v < nl) | (d < br);
-                    tmp[l] = d2;
+            // the value is below (K+2) N: subtract N until it is canonical
+            for (;;) {
+                std::vector<uint32_t> d(K + 1);
+                uint64_t c1 = 1;
+                for (int l = 0; l <= K; l++) {
+                    const uint64_t v = (uint64_t)acc[l] + (uint32_t)~(l < L ? T.key[ly.Nl() + l] : 0u) + c1;
+                    d[l] = (uint32_t)v;
+                    c1 = v >> 32;
                 }
-                if (!br) acc = tmp;
+                if (!c1) break;
+                acc = d;
             }
             std::copy(acc.begin(), acc.begin() + L, out + (g0 + e) * (size_t)L);
         }

@@ -23,6 +23,7 @@
 
 #include "arith.hpp"
 #include "kernels.hpp"
+#include "limbs.hpp"
 #include "mfma_layout.hpp"
 
 namespace rnsrsa {
@@ -40,20 +41,12 @@ struct MShp {
     static constexpr int ECOLS = (int)LY.ecols();
     static constexpr int OSH = mfma_offset_shift(K);   // REDC offset m 2^OSH of steps (iii) and (iv)
     static constexpr bool PAIR_I32 = mfma_pair_fits_i32(K);   // byte partials paired in int32 (K <= 127)
-    // smallest b with 2^b > K+1: an exit value below (K+2)N has quotient < 2^b
-    static constexpr int qbits() {
-        int b = 0;
-        while ((1 << b) <= K + 1) b++;
-        return b;
-    }
-    // Exit: [K][NM] digits and 2 x [K+1][NM] limbs; with the split exit (from
-    // 49 channels on, where it pays for itself) also the carries out of the
-    // limb ranges that the 64 W / NM workers per element sum, [workers][2][NM].
-    // Below that one lane per element sums all limbs, and the main loop keeps
-    // its register allocation (the split exit measured 7% slower at k = 33).
-    static constexpr bool SPLIT_EXIT = K >= 49;
-    static constexpr int EXIT_CORE = (K + 2 * (K + 1)) * NM;
-    static constexpr int EXIT_WORDS = EXIT_CORE + (SPLIT_EXIT ? 128 * W : 0);
+    // Exit: a 64-bit sum per limb slot and a redundant residue per element
+    static constexpr int XSLOTS = 4 * W * MT;
+    static constexpr int EXIT_WORDS = (2 * XSLOTS + 1) * NM;
+    static_assert(XSLOTS > K, "a limb slot for each of the exit's K + 1 limbs");
+    // Entry: input limbs whose table words are in registers at once
+    static constexpr int ENTRY_STEP = MT <= 3 ? 8 : 4;
     static constexpr int BUF_WORDS = 2 * NM * BROW;
     static constexpr int WORK_WORDS = EXIT_WORDS > BUF_WORDS ? EXIT_WORDS : BUF_WORDS;
     // Where the second extension's constant tiles (the same for every key of
@@ -62,7 +55,7 @@ struct MShp {
     // registers would overflow while the tiles still fit LDS; otherwise they
     // are read from global memory (L2) at each step.
     static constexpr int A2_TILE_WORDS = W * MT * KSTEPS * 64 * 4;
-    static constexpr bool A2_FITS_LDS = (EXIT_WORDS > BUF_WORDS ? EXIT_WORDS : BUF_WORDS) + A2_TILE_WORDS <= 36 * 1024;
+    static constexpr bool A2_FITS_LDS = WORK_WORDS + A2_TILE_WORDS <= 36 * 1024;
     static constexpr bool A2_GLOBAL = KSTEPS > 5 || (KSTEPS == 5 && !A2_FITS_LDS);
     static constexpr bool A2_LDS = !A2_GLOBAL && (NT == 1 || KSTEPS >= 5);
     // the per-key first-extension tiles follow the second ones to global
@@ -229,6 +222,31 @@ __device__ __forceinline__ void mfma_extension(const MConstOf<K, W, MT, NT> &C, 
         // operands read from memory: keep at most one k-step of them in
         // flight, or the scheduler hoists all of them and the registers spill
         if (S::A1_GLOBAL) __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// D = tiles * digits, the tiles ([MT][KSTEPS][64] of this wave) read from
+// global memory at each k-step.
+template <int K, int W, int MT, int NT>
+__device__ __forceinline__ void mfma_contract(gcv4i *tiles, uint32_t loff, const uint32_t *buf, int lane,
+                                              mfma_v4i (&D)[MT][NT]) {
+    using S = MShp<K, W, MT, NT>;
+#pragma unroll
+    for (int mt = 0; mt < MT; mt++)
+#pragma unroll
+        for (int nt = 0; nt < NT; nt++) D[mt][nt] = mfma_v4i{0, 0, 0, 0};
+#pragma unroll 2
+    for (int ks = 0; ks < S::KSTEPS; ks++) {
+        mfma_v4i a[MT];
+#pragma unroll
+        for (int mt = 0; mt < MT; mt++) a[mt] = mfma_tile_load(tiles, mt * S::KSTEPS + ks, loff);
+#pragma unroll
+        for (int nt = 0; nt < NT; nt++) {
+            const mfma_v4i bop =
+                *(const mfma_v4i *)(buf + (16 * nt + (lane & 15)) * S::BROW + 16 * ks + 4 * (lane >> 4));
+#pragma unroll
+            for (int mt = 0; mt < MT; mt++) D[mt][nt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[mt], bop, D[mt][nt], 0, 0, 0);
+        }
     }
 }
 
@@ -488,79 +506,106 @@ __device__ __forceinline__ int mjob_tile_elems(const MJob &J, int NM) {
     return J.tile_elems > 0 && J.tile_elems < NM ? J.tile_elems : NM;
 }
 
-// End of the exit on wave 0, lane n (element n of the tile, message msg):
-// acc holds the L+1 limbs of sum_j xi'_j M'_j; subtracts alpha M', takes the
-// canonical representative mod N by conditional subtractions of N 2^b, and
-// stores the L limbs (columns beyond the tile's elements store nothing).
+// Leave the RNS: buf2 holds the digits xi' of the exit product, r its
+// redundant residues.  The limb sums of sum_j xi'_j M'_j are one more
+// contraction of those digits, on the matrix cores with the base's exit tiles
+// (read once, from global memory); then each wave takes every W-th element,
+// one limb per lane (limbs.hpp): minus alpha M' (alpha from limb 0 and r), the
+// quotient by N from the top limbs, canonical limbs stored coalesced.
+//
+// RSA-2048 encryption of 10,007 messages spent about 350 of its 416 us in the
+// entry and an exit of K (L + 1) multiply-adds and ceil(log2(K + 2))
+// conditional subtractions on one lane per element.
 template <int K, int W, int MT, int NT>
-__device__ __forceinline__ void mfma_exit_tail(const gu32 *__restrict__ mb, const gu32 *__restrict__ mk, uint32_t *acc,
-                                               uint32_t *tmp, uint32_t alpha, int L, int n, int msg, const MJob &J,
-                                               gu32 *__restrict__ out) {
+__device__ __forceinline__ void mfma_exit(const MConstOf<K, W, MT, NT> &C, const gu32 *__restrict__ mb,
+                                          const gu32 *__restrict__ mk, uint32_t *__restrict__ lds,
+                                          const uint32_t (&r)[NT], int wave, int lane, const MJob &J, int e0,
+                                          gu32 *__restrict__ out) {
     using S = MShp<K, W, MT, NT>;
-    constexpr int NM = S::NM;
-    {
-        uint64_t carry = 0;
-        uint32_t borrow = 0;
-        for (int l = 0; l <= L; l++) {
-            const uint64_t p = (uint64_t)alpha * mb[S::LY.MpF() + l] + carry;
-            carry = p >> 32;
-            const uint32_t v = acc[l * NM + n], pl = (uint32_t)p;
-            const uint32_t d = v - pl, d2 = d - borrow;
-            borrow = (v < pl) | (d < borrow);
-            acc[l * NM + n] = d2;
-        }
+    constexpr int LC = (K + 1 + 63) / 64;                       // words per lane of a K + 1 limb number
+    const int g = lane >> 4;
+    const uint32_t *buf2 = lds + S::NM * S::BROW;
+    uint64_t *tsum = (uint64_t *)lds;                           // [NM][XSLOTS]
+    uint32_t *rl = lds + 2 * S::NM * S::XSLOTS;                 // [NM]
+    mfma_v4i D[MT][NT];
+    mfma_contract<K, W, MT, NT>((gcv4i *)(mb + S::LY.xt()) + (size_t)wave * MT * S::KSTEPS * 64, C.loff, buf2, lane, D);
+    uint32_t Mp[LC], N[LC];
+#pragma unroll
+    for (int c = 0; c < LC; c++) {
+        const int l = 64 * c + lane;
+        Mp[c] = l <= K ? mb[S::LY.MpF() + l] : 0u;
+        N[c] = l < K ? mk[S::LY.Nl() + l] : 0u;
     }
-    for (int b = S::qbits() - 1; b >= 0; b--) {
-        uint32_t borrow = 0;
-        for (int l = 0; l <= L; l++) {
-            const uint32_t nlo = l < L ? mk[S::LY.Nl() + l] : 0u;
-            const uint32_t nhi = (b && l > 0) ? (mk[S::LY.Nl() + l - 1] >> (32 - b)) : 0u;
-            const uint32_t nl = (nlo << b) | nhi;
-            const uint32_t v = acc[l * NM + n];
-            const uint32_t d = v - nl, d2 = d - borrow;
-            borrow = (v < nl) | (d < borrow);
-            tmp[l * NM + n] = d2;
-        }
-        if (!borrow)
-            for (int l = 0; l <= L; l++) acc[l * NM + n] = tmp[l * NM + n];
+    __syncthreads();                                            // every wave has read buf2
+#pragma unroll
+    for (int mt = 0; mt < MT; mt++)
+#pragma unroll
+        for (int nt = 0; nt < NT; nt++)
+            tsum[(16 * nt + (lane & 15)) * S::XSLOTS + (wave * MT + mt) * 4 + g] =
+                mfma_accumulate<S::PAIR_I32>(D[mt][nt], kExitOffset, C.kf);
+    if (wave == 0 && g == 0)
+#pragma unroll
+        for (int nt = 0; nt < NT; nt++) rl[16 * nt + lane] = r[nt];
+    __syncthreads();
+    const int L = J.L, t = top_limb<LC>(N);
+    const double nd = limbs_top<LC>(N, t);
+    const int left = J.batch - e0, te = mjob_tile_elems(J, S::NM);
+    const int ne = left < te ? left : te;
+    for (int n = wave; n < ne; n += W) {
+        uint64_t T[LC];
+        uint32_t v[LC];
+#pragma unroll
+        for (int c = 0; c < LC; c++) T[c] = 64 * c + lane <= K ? tsum[n * S::XSLOTS + 64 * c + lane] : 0u;
+        const uint32_t alpha =
+            ((uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)T[0]) - rl[n]) * C.Mpinv_r;   // in [0, K)
+#pragma unroll
+        for (int c = 0; c < LC; c++) T[c] += (uint64_t)alpha * (uint32_t)~Mp[c];                 // - alpha M'
+        if (lane == 0) T[0] += alpha;
+        limbs_of_sums<LC>(T, v, lane);
+#pragma unroll
+        for (int c = 0; c < LC; c++) v[c] = 64 * c + lane <= K ? v[c] : 0u;
+        const uint32_t q = limbs_quotient<LC>(v, t, nd);        // the value is below (K + 2) N
+#pragma unroll
+        for (int c = 0; c < LC; c++) T[c] = v[c] + (uint64_t)q * (uint32_t)~N[c];                // - q N
+        if (lane == 0) T[0] += q;
+        limbs_of_sums<LC>(T, v, lane);
+#pragma unroll
+        for (int c = 0; c < LC; c++) v[c] = 64 * c + lane <= K ? v[c] : 0u;
+        limbs_reduce_once<LC>(v, N, lane);
+        gu32 *__restrict__ o = out + (size_t)(e0 + n) * J.out_stride;
+#pragma unroll
+        for (int c = 0; c < LC; c++)
+            if (64 * c + lane < L) o[64 * c + lane] = v[c];
     }
-    if (msg < J.batch && n < mjob_tile_elems(J, NM))
-        for (int l = 0; l < L; l++) out[(size_t)msg * J.out_stride + l] = acc[l * NM + n];
 }
 
-// Workgroup set-up shared by the kernels of the matrix-core engine: the
-// constant digit rows of both exchange buffers (channel K holds the offset
-// digit 1, the channels after it zero) and the per-lane constants of C (tiles
-// in registers, LDS or global memory, per-slot constants, scalars).
-template <int K, int W, int MT, int NT, bool SQ = false>
-__device__ __forceinline__ void mfma_setup(const gu32 *__restrict__ mb, const gu32 *__restrict__ mk,
-                                           uint32_t *__restrict__ lds, int wave, int lane,
-                                           MConstOf<K, W, MT, NT> &C) {
+// The constant digit rows of both exchange buffers: channel K holds the
+// offset digit 1, the channels after it zero.
+template <int K, int W, int MT, int NT>
+__device__ __forceinline__ void mfma_rows(uint32_t *__restrict__ lds) {
     using S = MShp<K, W, MT, NT>;
-    static_assert(!SQ || (S::LY.sq_ok() && !S::A2_GLOBAL && !S::C_LDS), "scaled B residues need per-key tiles in registers or LDS");
-    // second extension's tiles and nu: the base's, or the key's scaled ones
-    const gu32 *__restrict__ a2src = SQ ? mk + S::LY.a2s() : mb + S::LY.a2();
     uint32_t *buf1 = lds;
     uint32_t *buf2 = lds + S::NM * S::BROW;
-    const int g = lane >> 4;
-    // constant digit rows: channel K holds the offset digit 1, the rest zero
     for (int i = threadIdx.x; i < S::NM * (S::BROW - K); i += 64 * W) {
         const int n = i / (S::BROW - K), c = K + i % (S::BROW - K);
         const uint32_t v = c == K ? 1u : 0u;
         buf1[n * S::BROW + c] = v;
         buf2[n * S::BROW + c] = v;
     }
+}
 
+// Workgroup set-up shared by the kernels of the matrix-core engine: the
+// per-lane constants of C (per-slot constants, scalars, tiles in global memory).
+template <int K, int W, int MT, int NT, bool SQ = false>
+__device__ __forceinline__ void mfma_setup(const gu32 *__restrict__ mb, const gu32 *__restrict__ mk,
+                                           uint32_t *__restrict__ lds, int wave, int lane,
+                                           MConstOf<K, W, MT, NT> &C) {
+    using S = MShp<K, W, MT, NT>;
+    const int g = lane >> 4;
     // per-lane constants
 #pragma unroll
     for (int mt = 0; mt < MT; mt++) {
         const size_t sl = (size_t)wave * MT + mt;
-#pragma unroll
-        for (int ks = 0; ks < S::KSTEPS; ks++) {
-            const size_t ti = ((sl * S::KSTEPS + ks) * 64 + lane) * 4;
-            if (!S::A1_GLOBAL) C.A1[mt][ks] = *(gcv4i *)(mk + S::LY.a1() + ti);
-            if (!S::A2_LDS && !S::A2_GLOBAL) C.A2[mt][ks] = *(gcv4i *)(a2src + ti);
-        }
         if (!S::C_LDS) {
             C.mB[mt] = mb[S::LY.slotB() + (sl * 3 + 0) * 64 + lane];
             C.uB[mt] = mb[S::LY.slotB() + (sl * 3 + 1) * 64 + lane];
@@ -588,14 +633,6 @@ __device__ __forceinline__ void mfma_setup(const gu32 *__restrict__ mb, const gu
         C.cl = cl + ((size_t)wave * MT * 4 + g) * 8;
         __syncthreads();
     }
-    if (S::A2_LDS) {
-        // each wave copies its own tiles; it alone reads them, so program
-        // order suffices (no barrier)
-        mfma_v4i *dst = (mfma_v4i *)(lds + S::WORK_WORDS) + (size_t)wave * MT * S::KSTEPS * 64;
-        gcv4i *src = (gcv4i *)a2src + (size_t)wave * MT * S::KSTEPS * 64;
-        for (int i = lane; i < MT * S::KSTEPS * 64; i += 64) dst[i] = src[i];
-        C.a2lds = dst;
-    }
     if (S::A2_GLOBAL) C.a2mem = (gcv4i *)(mb + S::LY.a2()) + (size_t)wave * MT * S::KSTEPS * 64;
     if (S::A1_GLOBAL) C.a1mem = (gcv4i *)(mk + S::LY.a1()) + (size_t)wave * MT * S::KSTEPS * 64;
     C.loff = 16u * lane;
@@ -609,6 +646,34 @@ __device__ __forceinline__ void mfma_setup(const gu32 *__restrict__ mb, const gu
         asm volatile("" : "+s"(C.kf[b]));
     }
 
+}
+
+// The extensions' tiles into registers or LDS (where the shape keeps them),
+// after the entry, whose sums and table words need the registers first.
+template <int K, int W, int MT, int NT, bool SQ = false>
+__device__ __forceinline__ void mfma_load_tiles(const gu32 *__restrict__ mb, const gu32 *__restrict__ mk,
+                                                uint32_t *__restrict__ lds, int wave, int lane,
+                                                MConstOf<K, W, MT, NT> &C) {
+    using S = MShp<K, W, MT, NT>;
+    static_assert(!SQ || (S::LY.sq_ok() && !S::A2_GLOBAL && !S::C_LDS), "scaled B residues need per-key tiles in registers or LDS");
+    // second extension's tiles: the base's, or the key's scaled ones
+    const gu32 *__restrict__ a2src = SQ ? mk + S::LY.a2s() : mb + S::LY.a2();
+#pragma unroll
+    for (int mt = 0; mt < MT; mt++)
+#pragma unroll
+        for (int ks = 0; ks < S::KSTEPS; ks++) {
+            const size_t ti = ((((size_t)wave * MT + mt) * S::KSTEPS + ks) * 64 + lane) * 4;
+            if (!S::A1_GLOBAL) C.A1[mt][ks] = *(gcv4i *)(mk + S::LY.a1() + ti);
+            if (!S::A2_LDS && !S::A2_GLOBAL) C.A2[mt][ks] = *(gcv4i *)(a2src + ti);
+        }
+    if (S::A2_LDS) {
+        // each wave copies its own tiles; it alone reads them, so program
+        // order suffices (no barrier)
+        mfma_v4i *dst = (mfma_v4i *)(lds + S::WORK_WORDS) + (size_t)wave * MT * S::KSTEPS * 64;
+        gcv4i *src = (gcv4i *)a2src + (size_t)wave * MT * S::KSTEPS * 64;
+        for (int i = lane; i < MT * S::KSTEPS * 64; i += 64) dst[i] = src[i];
+        C.a2lds = dst;
+    }
 }
 
 // One tile of exponentiation job J: columns n < 16*NT hold elements e0 + n
@@ -632,39 +697,65 @@ __device__ __forceinline__ void modexp_mfma_tile(const MJob &J, int e0, uint32_t
     const int lane = threadIdx.x & 63;
     const int g = lane >> 4;
 
+    // the tile's inputs, coalesced, [NM][is] in the (still unused) exchange
+    // buffers: in_limbs <= 2 K words per element, below 2 BROW
+    const int is = J.in_limbs | 1;
+    for (int l = lane; l < J.in_limbs; l += 64) {
+        uint32_t v[(S::NM + W - 1) / W];
+#pragma unroll
+        for (int i = 0; i < (S::NM + W - 1) / W; i++) {
+            const int n = wave + i * W, m = e0 + n;
+            v[i] = n < S::NM && m < J.batch ? in[(size_t)m * J.in_stride + l] : 0u;
+        }
+#pragma unroll
+        for (int i = 0; i < (S::NM + W - 1) / W; i++)
+            if (wave + i * W < S::NM) lds[(wave + i * W) * is + l] = v[i];
+    }
+
     MConstOf<K, W, MT, NT> C;
     mfma_setup<K, W, MT, NT, SQ>(mb, mk, lds, wave, lane, C);
+    __syncthreads();
 
-    // entry: residues of Z = sum_h X_h Y_h in the kept representation
+    // entry: residues of Z = sum_h X_h Y_h in the kept representation; the
+    // table's words of ENTRY_STEP limbs are loaded before they are used, so
+    // that a step waits for memory once
     MState<MT, NT> a;
     {
+        constexpr int STEP = S::ENTRY_STEP;
         Acc ab[MT][NT], ap[MT][NT];
         uint32_t zr[NT];
-        int msg[NT];
 #pragma unroll
-        for (int nt = 0; nt < NT; nt++) {
-            msg[nt] = e0 + 16 * nt + (lane & 15);
-            zr[nt] = 0;
-        }
-        const int colB = wave * 4 * MT + g, colP = W * 4 * MT + wave * 4 * MT + g;
-        for (int l = 0; l < J.in_limbs; l++) {
-            const gu32 *__restrict__ row = E + (size_t)l * S::ECOLS;
-            uint32_t v[NT];
+        for (int nt = 0; nt < NT; nt++) zr[nt] = 0;
+        const gu32 *__restrict__ EB = E + wave * 4 * MT + g, *__restrict__ EP = EB + W * 4 * MT;
+        for (int l0 = 0; l0 < J.in_limbs; l0 += STEP) {
+            uint32_t eb[STEP][MT], ep[STEP][MT], er[STEP];
 #pragma unroll
-            for (int nt = 0; nt < NT; nt++)
-                v[nt] = msg[nt] < J.batch ? in[(size_t)msg[nt] * J.in_stride + l] : 0u;
-            const uint32_t er = row[S::ECOLS - 1];
+            for (int z = 0; z < STEP; z++) {
+                // past the last limb: any row, its input word counts as zero
+                const size_t row = (size_t)(l0 + z < J.in_limbs ? l0 + z : 0) * S::ECOLS;
 #pragma unroll
-            for (int mt = 0; mt < MT; mt++) {
-                const uint32_t eb = row[colB + 4 * mt], ep = row[colP + 4 * mt];
-#pragma unroll
-                for (int nt = 0; nt < NT; nt++) {
-                    acc_mac(ab[mt][nt], v[nt], eb);
-                    acc_mac(ap[mt][nt], v[nt], ep);
+                for (int mt = 0; mt < MT; mt++) {
+                    eb[z][mt] = EB[row + 4 * mt];
+                    ep[z][mt] = EP[row + 4 * mt];
                 }
+                er[z] = E[row + S::ECOLS - 1];
             }
 #pragma unroll
-            for (int nt = 0; nt < NT; nt++) zr[nt] += v[nt] * er;
+            for (int z = 0; z < STEP; z++) {
+                uint32_t v[NT];
+#pragma unroll
+                for (int nt = 0; nt < NT; nt++)
+                    v[nt] = l0 + z < J.in_limbs ? lds[(16 * nt + (lane & 15)) * is + l0 + z] : 0u;
+#pragma unroll
+                for (int mt = 0; mt < MT; mt++)
+#pragma unroll
+                    for (int nt = 0; nt < NT; nt++) {
+                        acc_mac(ab[mt][nt], v[nt], eb[z][mt]);
+                        acc_mac(ap[mt][nt], v[nt], ep[z][mt]);
+                    }
+#pragma unroll
+                for (int nt = 0; nt < NT; nt++) zr[nt] += v[nt] * er[z];
+            }
         }
 #pragma unroll
         for (int mt = 0; mt < MT; mt++)
@@ -678,6 +769,9 @@ __device__ __forceinline__ void modexp_mfma_tile(const MJob &J, int e0, uint32_t
 #pragma unroll
         for (int nt = 0; nt < NT; nt++) a.r[nt] = zr[nt];
     }
+    __syncthreads();                                            // every wave has read the inputs
+    mfma_rows<K, W, MT, NT>(lds);
+    mfma_load_tiles<K, W, MT, NT, SQ>(mb, mk, lds, wave, lane, C);
     const int w = J.window;
     const int T = 1 << w;
     const size_t estride = (size_t)W * S::SLOTS * 64;
@@ -857,123 +951,7 @@ __device__ __forceinline__ void modexp_mfma_tile(const MJob &J, int e0, uint32_t
         }
     }
 
-    // leave the RNS
-    if constexpr (!S::SPLIT_EXIT) {
-        // wave 0, lane n < NM handles element n of the workgroup alone
-        __syncthreads();
-        if (wave != 0 || lane >= S::NM) return;
-        const int n = lane;
-        const int msg = e0 + n;
-        uint32_t rr = a.r[0];
-#pragma unroll
-        for (int nt = 1; nt < NT; nt++) rr = (n >> 4) == nt ? a.r[nt] : rr;   // lane n holds element n's r in slot n/16
-        const int L = J.L;
-        constexpr int NM = S::NM;
-        uint32_t *X = lds;                               // [K][NM] xi'_j of the exit product
-        uint32_t *acc = lds + K * NM;                    // [L+1][NM]
-        uint32_t *tmp = acc + (L + 1) * NM;              // [L+1][NM]
-        uint32_t s2 = 0;
-        for (int jj = 0; jj < K; jj++) {
-            const uint32_t v = buf2[n * S::BROW + jj] ^ kDigitBias;       // xi'_j in [0, m'_j)
-            X[jj * NM + n] = v;
-            s2 += v * mb[S::LY.mplo() + jj];
-        }
-        const uint32_t alpha = (s2 - rr) * C.Mpinv_r;                    // in [0, K)
-        {
-            uint64_t carry = 0;
-            for (int l = 0; l <= L; l++) {
-                Acc sum;
-                sum.lo = carry;
-                for (int jj = 0; jj < K; jj++) acc_mac(sum, X[jj * NM + n], mb[S::LY.MpL() + (size_t)jj * (K + 1) + l]);
-                uint64_t lo;
-                uint32_t top;
-                acc_value(sum, lo, top);
-                acc[l * NM + n] = (uint32_t)lo;
-                carry = (lo >> 32) | ((uint64_t)top << 32);
-            }
-        }
-        {
-            uint64_t carry = 0;
-            uint32_t borrow = 0;
-            for (int l = 0; l <= L; l++) {
-                const uint64_t p = (uint64_t)alpha * mb[S::LY.MpF() + l] + carry;
-                carry = p >> 32;
-                const uint32_t v = acc[l * NM + n], pl = (uint32_t)p;
-                const uint32_t d = v - pl, d2 = d - borrow;
-                borrow = (v < pl) | (d < borrow);
-                acc[l * NM + n] = d2;
-            }
-        }
-        for (int b = S::qbits() - 1; b >= 0; b--) {
-            uint32_t borrow = 0;
-            for (int l = 0; l <= L; l++) {
-                const uint32_t nlo = l < L ? mk[S::LY.Nl() + l] : 0u;
-                const uint32_t nhi = (b && l > 0) ? (mk[S::LY.Nl() + l - 1] >> (32 - b)) : 0u;
-                const uint32_t nl = (nlo << b) | nhi;
-                const uint32_t v = acc[l * NM + n];
-                const uint32_t d = v - nl, d2 = d - borrow;
-                borrow = (v < nl) | (d < borrow);
-                tmp[l * NM + n] = d2;
-            }
-            if (!borrow)
-                for (int l = 0; l <= L; l++) acc[l * NM + n] = tmp[l * NM + n];
-        }
-        if (msg < J.batch && n < mjob_tile_elems(J, NM))
-            for (int l = 0; l < L; l++) out[(size_t)msg * J.out_stride + l] = acc[l * NM + n];
-    } else {
-        __syncthreads();
-        const int L = J.L;
-        constexpr int NM = S::NM;
-        uint32_t *X = lds;                           // [K][NM] xi'_j of the exit product
-        uint32_t *acc = lds + K * NM;                // [L+1][NM]
-        uint32_t *tmp = acc + (L + 1) * NM;          // [L+1][NM]
-        // wave 0 (lane n < NM: element n) gathers xi'_j and alpha; then every
-        // wave and lane group sums a contiguous range of the limbs of
-        // sum_j xi'_j M'_j (the range sums are independent); wave 0 adds the
-        // carries between the ranges and finishes
-        uint32_t *cout = lds + S::EXIT_CORE;         // [workers][2][NM]
-        uint32_t alpha = 0;
-        if (wave == 0 && lane < NM) {
-            const int n = lane;
-            uint32_t rr = a.r[0];
-#pragma unroll
-            for (int nt = 1; nt < NT; nt++) rr = (n >> 4) == nt ? a.r[nt] : rr;
-            uint32_t s2 = 0;
-            for (int jj = 0; jj < K; jj++) {
-                const uint32_t v = buf2[n * S::BROW + jj] ^ kDigitBias;
-                X[jj * NM + n] = v;
-                s2 += v * mb[S::LY.mplo() + jj];
-            }
-            alpha = (s2 - rr) * C.Mpinv_r;
-        }
-        __syncthreads();
-        constexpr int NW = W * (64 / NM);            // workers per element
-        const int CW = (L + 1 + NW - 1) / NW;        // limbs per worker
-        {
-            const int n = lane % NM, wid = wave * (64 / NM) + lane / NM;
-            const int l0 = wid * CW < L + 1 ? wid * CW : L + 1;
-            const int l1 = l0 + CW < L + 1 ? l0 + CW : L + 1;
-            uint64_t carry = 0;
-            for (int l = l0; l < l1; l++) {
-                Acc sum;
-                sum.lo = carry;
-                for (int jj = 0; jj < K; jj++)
-                    acc_mac(sum, X[jj * NM + n], mb[S::LY.MpL() + (size_t)jj * (K + 1) + l]);
-                uint64_t lo;
-                uint32_t top;
-                acc_value(sum, lo, top);
-                acc[l * NM + n] = (uint32_t)lo;
-                carry = (lo >> 32) | ((uint64_t)top << 32);
-            }
-            cout[2 * NM * wid + n] = (uint32_t)carry;
-            cout[2 * NM * wid + NM + n] = (uint32_t)(carry >> 32);
-        }
-        __syncthreads();
-        if (wave != 0 || lane >= NM) return;
-        const int n = lane;
-        ripple_carries(acc + n, NM, L + 1, cout + n, NM, NW, CW);
-        mfma_exit_tail<K, W, MT, NT>(mb, mk, acc, tmp, alpha, L, n, e0 + n, J, out);
-    }
+    mfma_exit<K, W, MT, NT>(C, mb, mk, lds, a.r, wave, lane, J, e0, out);
 }
 
 // Exponentiation kernel, matrix-core variant: workgroup t runs tile t of the
@@ -1038,6 +1016,8 @@ __global__ __launch_bounds__(64 * W) void montmul_mfma_kernel(MontMulMfmaLaunch 
     const int g = lane >> 4;
     MConstOf<K, W, MT, NT> C;
     mfma_setup<K, W, MT, NT>(mb, mk, lds, wave, lane, C);
+    mfma_rows<K, W, MT, NT>(lds);
+    mfma_load_tiles<K, W, MT, NT>(mb, mk, lds, wave, lane, C);
     const int te = A.tile_elems > 0 && A.tile_elems < S::NM ? A.tile_elems : S::NM;
     const size_t B = (size_t)A.batch;
     int elem[NT];

@@ -1,0 +1,99 @@
+// Integers held across a wavefront: limb 64 c + lane of a number is word c of
+// that lane, so additions, small multiples and comparisons take a few
+// instructions whatever the length.  Carries between the limbs are resolved
+// for all lanes at once: with masks G (limbs that carry out by themselves) and
+// P (limbs of all ones, which pass a carry on), the 64-bit sum (G << 1) + P
+// on the scalar unit ripples every carry through the P runs.
+#pragma once
+
+#include "arith.hpp"
+
+namespace rnsrsa {
+
+// Carry into each lane from masks g and p (never both set for a lane) and the
+// carry cin into lane 0; cin becomes the carry out of lane 63.
+__device__ __forceinline__ uint64_t limb_carries(uint64_t g, uint64_t p, uint32_t &cin) {
+    const uint64_t y = (g << 1) | cin, s = y + p;
+    cin = (uint32_t)(g >> 63) | (s < p ? 1u : 0u);
+    return s ^ p;
+}
+
+__device__ __forceinline__ uint32_t lane_bit(uint64_t mask, int lane) { return (uint32_t)(mask >> lane) & 1u; }
+
+// Word of the lane below (lane 0: `first`).
+__device__ __forceinline__ uint32_t lane_up(uint32_t v, uint32_t first) {
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)first, (int)v, 0x138 /* wave_shr:1 */, 0xF, 0xF, false);
+}
+
+// Limbs of sum_l t_l 2^(32 l), every t_l below 2^63; the carry out of the top
+// lane is dropped.
+template <int C>
+__device__ __forceinline__ void limbs_of_sums(const uint64_t (&t)[C], uint32_t (&v)[C], int lane) {
+    uint32_t below = 0, cin = 0;
+#pragma unroll
+    for (int c = 0; c < C; c++) {
+        const uint32_t lo = (uint32_t)t[c], hi = (uint32_t)(t[c] >> 32);
+        const uint32_t u = lo + lane_up(hi, below);
+        below = (uint32_t)__builtin_amdgcn_readlane((int)hi, 63);
+        const uint64_t cm = limb_carries(__ballot(u < lo), __ballot(u == 0xFFFFFFFFu), cin);
+        v[c] = u + lane_bit(cm, lane);
+    }
+}
+
+// v <- v - n when v >= n.
+template <int C>
+__device__ __forceinline__ void limbs_reduce_once(uint32_t (&v)[C], const uint32_t (&n)[C], int lane) {
+    uint32_t d[C], cin = 1;                                  // v - n = v + ~n + 1
+#pragma unroll
+    for (int c = 0; c < C; c++) {
+        const uint32_t u = v[c] + ~n[c];
+        const uint64_t cm = limb_carries(__ballot(u < v[c]), __ballot(u == 0xFFFFFFFFu), cin);
+        d[c] = u + lane_bit(cm, lane);
+    }
+    if (cin) {                                               // no borrow
+#pragma unroll
+        for (int c = 0; c < C; c++) v[c] = d[c];
+    }
+}
+
+// Limb l (uniform) of a number.
+template <int C>
+__device__ __forceinline__ uint32_t limb_at(const uint32_t (&v)[C], int l) {
+    uint32_t r = 0;
+#pragma unroll
+    for (int c = 0; c < C; c++)
+        if (l >> 6 == c) r = (uint32_t)__builtin_amdgcn_readlane((int)v[c], l & 63);
+    return r;
+}
+
+// Index of the top nonzero limb (0 when there is none).
+template <int C>
+__device__ __forceinline__ int top_limb(const uint32_t (&v)[C]) {
+    int t = 0;
+#pragma unroll
+    for (int c = 0; c < C; c++) {
+        const uint64_t m = __ballot(v[c] != 0);
+        if (m) t = 64 * c + 63 - __builtin_clzll(m);
+    }
+    return t;
+}
+
+// n's top two limbs as a double, for limbs_quotient.
+template <int C>
+__device__ __forceinline__ double limbs_top(const uint32_t (&n)[C], int t) {
+    return (double)limb_at(n, t) + (t ? (double)limb_at(n, t - 1) * 0x1p-32 : 0.0);
+}
+
+// floor(v / n) or one less, for v / n < 2^11; t = top_limb(n), nd =
+// limbs_top(n, t) >= 1.  The limbs left out of either top change the
+// quotient's value by less than 2^11 (2^-31 + 2^-50), so the estimate lowered by
+// 2^-19 is below it by less than 2^-18.
+template <int C>
+__device__ __forceinline__ uint32_t limbs_quotient(const uint32_t (&v)[C], int t, double nd) {
+    const double x = (double)limb_at(v, t + 1) * 0x1p32 + (double)limb_at(v, t) +
+                     (t ? (double)limb_at(v, t - 1) * 0x1p-32 : 0.0);
+    const double q = x / nd - 0x1p-19;
+    return (uint32_t)__builtin_amdgcn_readfirstlane(q > 0.0 ? (int)q : 0);
+}
+
+}  // namespace rnsrsa

@@ -55,6 +55,10 @@ constexpr bool mfma_prime_fits(uint32_t m, int K, bool in_bprime) {
     return m <= kMaxPrimeP && off + smax < (uint64_t)m * ((1ull << 32) - m) + 2ull * m - 1;
 }
 
+// Added to every limb sum of the exit, whose magnitude is at most
+// mfma_sum_bound(513) < 2^50, so that the sums are positive.
+constexpr uint64_t kExitOffset = 1ull << 50;
+
 struct MLayout {
     int K, W, MT, NT;
     constexpr int CH() const { return 4 * MT - 1; }                 // prime channels per wave
@@ -71,10 +75,10 @@ struct MLayout {
     constexpr size_t a2() const { return 0; }                                  // [W][MT][KSTEPS][64][4] second extension
     constexpr size_t slotB() const { return tiles(); }                         // [W][MT][3][64] m, m^-1 mod 2^32, nu
     constexpr size_t slotP() const { return slotB() + (size_t)W * MT * 3 * 64; }  // [W][MT][4][64] m', m'^-1, H, kappa
-    constexpr size_t mpj() const { return slotP() + (size_t)W * MT * 4 * 64; }  // [K] m'_j
-    constexpr size_t mplo() const { return mpj() + K; }                        // [K] M'_j mod 2^32
-    constexpr size_t MpL() const { return mplo() + K; }                        // [K][K+1] limbs of M'_j
-    constexpr size_t MpF() const { return MpL() + (size_t)K * (K + 1); }        // [K+1] limbs of M'
+    // [W][MT][KSTEPS][64][4] leaving the RNS: slot s = (w MT + mt) 4 + g holds limb s of
+    // the sum over j of xi'_j M'_j (see make_mfma_tables)
+    constexpr size_t xt() const { return slotP() + (size_t)W * MT * 4 * 64; }
+    constexpr size_t MpF() const { return xt() + tiles(); }                    // [K+1] limbs of M'
     constexpr size_t bscal() const { return MpF() + K + 1; }                   // [4] M'^-1, M^-1 mod 2^32
     // [W][MT][3][64] conversions of the standalone product between plain
     // residues and the kept representation: R^2 mod m (into B), R^2 M^-1 mod m'

@@ -99,6 +99,59 @@ void fill_tiles(const MfmaShape &sh, uint32_t *dst, F value) {
                 }
 }
 
+// Exit tiles: the matrix whose row 4 s + b, applied to the digits of xi'
+// (minus kDigitBias) and the offset digit, gives byte partial b of limb s,
+// modulo 2^(32 (K+1)).  Column (j, a) holds the balanced base-256 digits of
+// M'_j moved up by a bytes; the offset column those of
+// kDigitBias sum_j M'_j - kExitOffset sum_s 2^(32 s).
+void fill_exit_tiles(const MfmaShape &sh, const BaseSet &bs, uint32_t *dst) {
+    const int K = sh.K, NB = 4 * (K + 1), KS = sh.KSTEPS();
+    auto balanced_digits = [&](const Limbs &x, int8_t *d) {
+        int c = 0;
+        for (int r = 0; r < NB; r++) {
+            const size_t l = (size_t)r / 4;
+            int v = (int)((l < x.size() ? x[l] : 0u) >> (8 * (r % 4)) & 0xFFu) + c;
+            c = v > 127 ? 1 : 0;
+            d[r] = (int8_t)(v - 256 * c);
+        }
+    };
+    std::vector<int8_t> D((size_t)(K + 1) * NB);
+    Limbs sum{0};
+    for (int j = 0; j < K; j++) {
+        Limbs Mj{1};
+        for (int t = 0; t < K; t++)
+            if (t != j) Mj = bn_mul_word(Mj, bs.Bp[t]);
+        sum = bn_add(sum, Mj);
+        balanced_digits(Mj, D.data() + (size_t)j * NB);
+    }
+    Limbs off((size_t)K + 1, 0u);
+    for (int l = 1; l <= K; l++) off[l] = (uint32_t)(kExitOffset >> 32);   // limb 0 of the offset is 0
+    Limbs o = bn_mul_word(sum, kDigitBias);
+    o.resize((size_t)K + 1, 0u);
+    uint32_t borrow = 0;
+    for (int l = 0; l <= K; l++) {                                         // o - off mod 2^(32 (K+1))
+        const uint64_t d = (uint64_t)o[l] - off[l] - borrow;
+        o[l] = (uint32_t)d;
+        borrow = (uint32_t)(d >> 63);
+    }
+    balanced_digits(o, D.data() + (size_t)K * NB);
+    for (int st = 0; st < sh.W * sh.MT; st++)
+        for (int ks = 0; ks < KS; ks++)
+            for (int l = 0; l < 64; l++) {
+                uint32_t words[4] = {0, 0, 0, 0};
+                const int r = 16 * st + l % 16;                            // output byte 4 s + b
+                for (int j = 0; j < 16; j++) {
+                    const int kappa = 64 * ks + 16 * (l / 16) + j;
+                    const int ch = kappa / 4, a = kappa % 4;
+                    int8_t v = 0;
+                    if (r < NB && (ch < K || (ch == K && a == 0)) && r >= a) v = D[(size_t)ch * NB + r - a];
+                    words[j / 4] |= (uint32_t)(uint8_t)v << (8 * (j % 4));
+                }
+                uint32_t *p = dst + (((size_t)st * KS + ks) * 64 + l) * 4;
+                for (int q = 0; q < 4; q++) p[q] = words[q];
+            }
+}
+
 // Per-lane slot table [W][MT][64] of f(channel) (channel -1 or >= K: junk).
 template <class F>
 void fill_slots(const MfmaShape &sh, uint32_t *dst, size_t field_stride, F f) {
@@ -216,13 +269,6 @@ MfmaTables make_mfma_tables(const ModPlan &mp, const MfmaShape &sh, bool with_ba
     const std::vector<int64_t> V2 = ext_values(bs.Bp, bs.B, [&](int t) { return pow2_64_mod(bs.B[t]); }, plus);
     fill_tiles(sh, out.base.data() + ly.a2(),
                [&](int t, int j, int a) -> int64_t { return V2[(size_t)(t + 1) * KK + (size_t)j * 4 + a]; });
-    auto Mpj_lo = [&](int j) {
-        uint32_t w = 1;
-        for (int t = 0; t < K; t++)
-            if (t != j) w *= bs.Bp[t];
-        return w;
-    };
-
     // per-slot constants; junk slots use a valid modulus and zero constants
     const uint32_t mB0 = bs.B[K - 1], mP0 = bs.Bp[K - 1];
     const size_t fs = (size_t)3 * 64;      // [W][MT][3][64]
@@ -249,17 +295,7 @@ MfmaTables make_mfma_tables(const ModPlan &mp, const MfmaShape &sh, bool with_ba
             if (j != t) others.push_back(bs.Bp[j]);
         return mulmod32(prod_mod32(bs.B, m), invmod32(prod_mod32(others, m), m), m);   // H = M (M'_t)^-1
     });
-    // leaving the RNS: m'_j, M'_j mod 2^32, limbs of M'_j and of M'
-    for (int j = 0; j < K; j++) {
-        out.base[ly.mpj() + j] = bs.Bp[j];
-        out.base[ly.mplo() + j] = Mpj_lo(j);
-        std::vector<uint32_t> others;
-        for (int t = 0; t < K; t++)
-            if (t != j) others.push_back(bs.Bp[t]);
-        Limbs Mj{1};
-        for (uint32_t x : others) Mj = bn_mul_word(Mj, x);
-        for (int l = 0; l <= K && l < (int)Mj.size(); l++) out.base[ly.MpL() + (size_t)j * (K + 1) + l] = Mj[l];
-    }
+    fill_exit_tiles(sh, bs, out.base.data() + ly.xt());
     for (int l = 0; l <= K && l < (int)bs.Mp.size(); l++) out.base[ly.MpF() + l] = bs.Mp[l];
     out.base[ly.bscal() + 0] = inv2_32(bn_low(bs.Mp));
     out.base[ly.bscal() + 1] = inv2_32(bn_low(bs.M));
