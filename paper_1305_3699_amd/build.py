@@ -48,20 +48,14 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=" + ARCH,
           "-mllvm", "-amdgpu-mfma-vgpr-form",
           "-Wno-unused-command-line-argument", "-I", INC, "-I", CSRC]
 # Matrix-kernel bases compiled with the iterative ILP instruction scheduler:
-# measured 3-19% faster per launch than the default scheduler on these
-# (RSA-2048 CRT 3.76 -> 3.88 M/s at w = 5, RSA-16384 plain decryption
-# +19%); k = 49 measured 3% slower and its 32-element tile does not compile
-# with it, and the small test bases keep the default.
-ILP_SCHED_K = {17, 33, 65, 66, 97, 129, 257, 513}
+# measured 3-19% faster per launch than the default scheduler on these (k = 33:
+# 16,384 RSA-2048 CRT decryptions 2.53 ms, 2.75 ms with the default; RSA-16384
+# plain decryption +19%); k = 49 measured 3% slower and its 32-element tile does
+# not compile with it, nor does k = 17's, and the small test bases keep the
+# default.  The split kernel keeps it too (8,192 decryptions 1.55 ms, 1.84 ms with
+# the ILP one).
+ILP_SCHED_K = {33, 65, 66, 97, 129, 257, 513}
 ILP_SCHED = ["-mllvm", "-amdgpu-sched-strategy=iterative-ilp"]
-# Shapes measured faster with another scheduler: the 32-element tile at
-# k = 33, held to 168 VGPRs, with the memory-clause scheduler (RSA-2048 CRT
-# halves, 16,384 ciphertexts: 3.27 vs 3.66 ms with the iterative ILP one,
-# 3.39 ms with the default; the other shapes measured slower with it or
-# within noise) and the AMDGPU register-pressure trackers (51 instead of 55
-# spilled registers, 1-2% shorter launches in four alternating runs).
-SCHED_BY_SHAPE = {(33, 3, 3, 2): ["-mllvm", "-amdgpu-sched-strategy=max-memory-clause",
-                                  "-mllvm", "-amdgpu-use-amdgpu-trackers=1"]}
 HOST_SOURCES = ["capi.cpp", "noalloc.cpp", "mr_gpu.cpp", "batch.cpp", "jobs.cpp", "server.cpp", "keygen.cpp", "plan.cpp", "plan_mfma.cpp", "emul.cpp",
                 "emul_mfma.cpp", "kernels_dispatch.cpp", "verify.cpp", "probe.cpp", "range.cpp"]
 
@@ -75,6 +69,13 @@ def mfma_shapes() -> list:
     txt = open(os.path.join(CSRC, "kernel_configs_mfma.inc")).read()
     return [tuple(int(v) for v in m) for m in
             re.findall(r"RNSRSA_MSHAPE\((\d+),\s*(\d+),\s*(\d+),\s*(\d+)\)", txt)]
+
+
+def split_shapes() -> dict:
+    """Waves per tile of the split kernels by (k, mt)."""
+    txt = open(os.path.join(CSRC, "kernel_configs_split.inc")).read()
+    return {(int(k), int(mt)): int(wv) for k, mt, wv in
+            re.findall(r"RNSRSA_MSPLIT\((\d+),\s*(\d+),\s*(\d+)\)", txt)}
 
 
 def _shape_source(k: int, w: int) -> str:
@@ -124,16 +125,21 @@ def build(jobs: int | None = None, verbose: bool = False, sanitize: bool = False
             with open(src, "w") as f:
                 f.write(text)
         units.append((src, os.path.join(build_dir, "shape_%d_%d.o" % (k, w)), []))
+    split = split_shapes()
     for k, w, mt, nt in mfma_shapes():
         # the exponentiation kernel and the standalone product in separate
         # units: only the former takes the scheduler choice
-        sched = SCHED_BY_SHAPE.get((k, w, mt, nt), ILP_SCHED if k in ILP_SCHED_K else [])
+        sched = ILP_SCHED if k in ILP_SCHED_K else []
         tus = (("mshape", sched,
                 "template hipError_t launch_modexp_mfma_t<%d, %d, %d, %d>(const ModexpMfmaLaunch &, hipStream_t);\n"
                 "template int mfma_blocks_per_cu_t<%d, %d, %d, %d>();\n" % (k, w, mt, nt, k, w, mt, nt)),
                ("mmul", [],
                 "template hipError_t launch_montmul_mfma_t<%d, %d, %d, %d>(const MontMulMfmaLaunch &, hipStream_t);\n"
                 % (k, w, mt, nt)))
+        if (k, mt) in split and nt == 1 and w == 1:
+            tus += (("msplit", [],
+                     "template hipError_t launch_modexp_split_t<%d, %d, %d>(const ModexpMfmaLaunch &, hipStream_t);\n"
+                     % (k, mt, split[k, mt])),)
         for prefix, flags, body in tus:
             stem = os.path.join(build_dir, "%s_%d_%d_%d_%d" % (prefix, k, w, mt, nt))
             text = '#include "kernels_mfma.hpp"\nnamespace rnsrsa {\n' + body + "}\n"
@@ -144,8 +150,8 @@ def build(jobs: int | None = None, verbose: bool = False, sanitize: bool = False
     for name in HOST_SOURCES:
         units.append((os.path.join(CSRC, name), os.path.join(build_dir, name.replace(".cpp", ".o")), []))
     # longest compiles first
-    units.sort(key=lambda u: -int(re.search(r"(?:shape|mmul)_(\d+)", u[0]).group(1))
-               if re.search(r"(?:shape|mmul)_\d", u[0]) else 0)
+    units.sort(key=lambda u: -int(re.search(r"(?:shape|mmul|msplit)_(\d+)", u[0]).group(1))
+               if re.search(r"(?:shape|mmul|msplit)_\d", u[0]) else 0)
     jobs = jobs or min(16, os.cpu_count() or 4)
 
     def compile_unit(src, obj, flags):

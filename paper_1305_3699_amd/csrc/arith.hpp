@@ -36,6 +36,32 @@ RNS_HD uint32_t redc(uint32_t xl, uint32_t xh, uint32_t m, uint32_t minv) {
     return t + (borrow ? m : 0u);
 }
 
+// A representative of x 2^-32 mod m below 2^32 for any x below 2^64; nminv =
+// -m^-1 mod 2^32.  x + u m (u = xl nminv) is a multiple of 2^32 below 2^65; its
+// carry out of 64 bits stands for 2^32, replaced by 2^32 - m.  One
+// multiplication less than redc's two and no comparison: the multiply-add's own
+// carry decides.
+RNS_HD uint32_t redc_any(uint64_t x, uint32_t m, uint32_t nminv) {
+    const uint32_t u = (uint32_t)x * nminv;
+#if defined(__HIP_DEVICE_COMPILE__)
+    uint64_t s, carry;
+    uint32_t corr;
+    asm("v_mad_u64_u32 %0, %1, %2, %3, %4" : "=&v"(s), "=s"(carry) : "v"(u), "v"(m), "v"(x));
+    // two wait states between a vector write of a scalar register pair and its
+    // use as a mask
+    asm("s_nop 1\n\tv_cndmask_b32 %0, 0, %1, %2" : "=v"(corr) : "v"(m), "s"(carry));
+    return (uint32_t)(s >> 32) - corr;
+#else
+    const uint64_t p = (uint64_t)u * m, s = p + x;
+    return (uint32_t)(s >> 32) - (s < p ? m : 0u);
+#endif
+}
+
+// The same for x below 2^64 - 2^32 m: no carry.
+RNS_HD uint32_t redc_small(uint64_t x, uint32_t m, uint32_t nminv) {
+    return (uint32_t)(((uint64_t)((uint32_t)x * nminv) * m + x) >> 32);
+}
+
 // a * b * 2^-32 mod m for a, b < m.
 RNS_HD uint32_t mulredc(uint32_t a, uint32_t b, uint32_t m, uint32_t minv) {
     const uint64_t p = (uint64_t)a * b;

@@ -260,6 +260,9 @@ MfmaShape auto_tile(const MfmaShape &sh, size_t tiles, int dev, bool small_jobs)
     if (sh.NT != 2) return sh;
     MfmaShape alt;
     if (!mfma_shape_for(sh.K, alt, 16) || alt.NT != 1 || alt.W != sh.W || alt.MT != sh.MT) return sh;
+    // Single-wave shapes: a wave's registers then hold the first extension's
+    // tiles too (16,384 RSA-2048 decryptions 2.53 ms, 2.71 ms with 32 elements)
+    if (sh.W == 1) return alt;
     // jobs of a few elements each: the 16-element tile needs hardly more
     // workgroups, and each does half the work
     if (small_jobs) return alt;
@@ -273,10 +276,20 @@ MfmaShape auto_tile(const MfmaShape &sh, size_t tiles, int dev, bool small_jobs)
     return tiles < (size_t)(simds / 4) * per_cu ? alt : sh;
 }
 
+// A launch with no more tiles than SIMDs keeps the split kernel's workgroups all
+// resident: 8,192 RSA-2048 decryptions (1,024 tiles) take 1.55 ms split and 1.83
+// ms on single waves, a lone one 1.00 and 1.69 ms.  One tile more starts a
+// second round of workgroups: 8,200 to 16,384 take 2.29 to 2.59 ms on single waves,
+// 3.27 ms split.
+bool split_tiles(const MfmaShape &sh, size_t tiles, int dev) {
+    return sh.split_waves() && tiles <= (size_t)device_simds(dev);
+}
+
 int spread_tile_elems(const MfmaShape &sh, size_t tiles, int dev) {
     const int simds = device_simds(dev);
+    const int waves = sh.split_waves() ? sh.split_waves() : sh.W;
     int e = sh.NM();
-    while (simds && e > kMinTileElems && tiles * (size_t)sh.W < (size_t)simds) {
+    while (simds && e > kMinTileElems && tiles * (size_t)waves < (size_t)simds) {
         e /= 2;
         tiles *= 2;
     }
@@ -341,10 +354,13 @@ int run_modexp(const rns_ctx *c0, const rns_ctx *c1, const uint32_t *E0, const u
             J.exp_stride = exp_stride;
             J.window = c0->window;
             J.tile0 = j * per_job;
+            J.group0 = j * sh.groups(per_job);
             J.tile_elems = te;
         }
         a.njobs = njobs;
         a.tiles = per_job * njobs;
+        a.groups = sh.groups(per_job) * njobs;
+        a.split = split_tiles(sh, (size_t)a.tiles, c0->device);
         a.max_window = c0->window;
         a.scaled = c0->mscaled && (njobs < 2 || c1->mscaled);
         Scratch table;

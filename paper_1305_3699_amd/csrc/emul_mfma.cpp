@@ -24,8 +24,9 @@ struct MCtx {
     // (A2s: the key's second extension for scaled B residues; AX: the exit)
     std::vector<int16_t> A1, A2, A2s, AX;
     bool sq;    // B residues kept scaled (x R s_i): the key holds the scaled form
+    bool wide;  // with the wide second extension (kWideShift)
 
-    MCtx(const MfmaTables &t, bool scaled) : T(t), ly(t.shape), K(t.shape.K), sq(scaled && t.scaled) {
+    MCtx(const MfmaTables &t, bool scaled) : T(t), ly(t.shape), K(t.shape.K), sq(scaled && t.scaled), wide(sq && t.shape.wide()) {
         const int SW = 4 * ly.MT, KK = 64 * ly.KSTEPS();
         A1.assign((size_t)ly.W * SW * 4 * KK, 0);
         A2.assign((size_t)ly.W * SW * 4 * KK, 0);
@@ -42,11 +43,13 @@ struct MCtx {
                         if (sq) A2s[at] = tile_byte(T.key.data() + ly.a2s(), w, s, b, kap);
                     }
     }
-    // byte b of slot s's constant at K index kap, read through the hardware
+    // byte b of slot s's constant at digit kap % 4 of channel kap / 4, read through the hardware
     // operand layout: A row 4g+b of tile mt lives in lane (row + 16 lg), K
     // index 16 lg + j of the k-step in byte j of that lane's 16 bytes
     int16_t tile_byte(const uint32_t *tiles, int w, int s, int b, int kap) const {
-        const int mt = s / 4, g = s % 4, ks = kap / 64, k = kap % 64, lg = k / 16, j = k % 16;
+        if (ly.W == 1 && kap / 4 > K) return 0;
+        const int phys = 4 * ly.word_of(kap / 4) + kap % 4;
+        const int mt = s / 4, g = s % 4, ks = phys / 64, k = phys % 64, lg = k / 16, j = k % 16;
         const int lane = 16 * lg + 4 * g + b;
         const uint32_t word = tiles[((((size_t)w * ly.MT + mt) * ly.KSTEPS() + ks) * 64 + lane) * 4 + j / 4];
         return (int16_t)(int8_t)(word >> (8 * (j % 4)));
@@ -134,7 +137,8 @@ void mm(const MCtx &c, MSt &x, const MSt &y, std::vector<uint32_t> &dig1, std::v
             const uint32_t ci = c.kslot(ly.slotC(), 1, 0, w, s);
             for (int e = 0; e < NM; e++) {
                 // sigma_i x y c_i: one REDC of the operands when they are scaled
-                const uint32_t t = mulredc(x.b[idx(w, s, e)], y.b[idx(w, s, e)], m, u);
+                const uint32_t xb = x.b[idx(w, s, e)], yb = y.b[idx(w, s, e)];
+                const uint32_t t = c.wide ? redc_any((uint64_t)xb * yb, m, 0u - u) : mulredc(xb, yb, m, u);
                 const uint32_t xi = c.sq ? t : mulredc(t, ci, m, u);
                 if (c.real(w, s)) dig1[(size_t)e * BROW + c.channel(w, s)] = pack_digits(xi);
             }
@@ -154,24 +158,42 @@ void mm(const MCtx &c, MSt &x, const MSt &y, std::vector<uint32_t> &dig1, std::v
                 // x' y' + S + m 2^sh in one REDC
                 const uint32_t r = reduce_offset((uint64_t)x.p[idx(w, s, e)] * y.p[idx(w, s, e)], S, m, u, sh);
                 x.p[idx(w, s, e)] = r;
-                if (c.real(w, s)) dig2[(size_t)e * BROW + c.channel(w, s)] = pack_digits(mulredc(r, H, m, u));
+                // the wide form's digits are the kept residues; the exit takes xi' in any case
+                if (c.real(w, s))
+                    dig2[(size_t)e * BROW + c.channel(w, s)] = pack_digits(c.wide && full ? r : mulredc(r, H, m, u));
             }
         }
     for (int e = 0; e < NM; e++) x.r[e] = rr[e];
     if (!full) return;
     const std::vector<int16_t> &A2 = c.sq ? c.A2s : c.A2;
     for (int w = 0; w < ly.W; w++) {
-        std::vector<uint32_t> alpha(NM);
+        std::vector<uint32_t> alpha(NM), alpha_h(NM);
         for (int e = 0; e < NM; e++) {
             const int64_t S = extension(A2, (size_t)w * SW + SW - 1, dig2, e, KK, BROW, c.K);
             alpha[e] = ((uint32_t)S - rr[e]) * Mpinv_r;
+            if (c.wide) {
+                int64_t P[4];
+                partials(A2, (size_t)w * SW + SW - 2, dig2, e, KK, BROW, P);
+                const int32_t h = ((int32_t)P[0] + (int32_t)c.T.key[ly.kscal() + 1] - (int32_t)(alpha[e] >> 18)) >> 14;
+                alpha_h[e] = ((uint32_t)h << (32 - kWideShift)) + (alpha[e] >> kWideShift);
+                alpha[e] &= (1u << kWideShift) - 1;
+            }
         }
         for (int s = 0; s < SW; s++) {
             const uint32_t m = c.slot(ly.slotB(), 3, 0, w, s), u = c.slot(ly.slotB(), 3, 1, w, s);
-            const uint32_t nu = c.sq ? c.kslot(ly.sqB(), 3, 0, w, s) : c.slot(ly.slotB(), 3, 2, w, s);
+            const uint32_t nu = c.sq ? c.kslot(ly.sqB(), 4, 0, w, s) : c.slot(ly.slotB(), 3, 2, w, s);
             for (int e = 0; e < NM; e++) {
                 const int64_t S = extension(A2, (size_t)w * SW + s, dig2, e, KK, BROW, c.K);
-                x.b[idx(w, s, e)] = reduce_offset((uint64_t)alpha[e] * nu, S, m, u, sh);
+                if (!c.wide) {
+                    x.b[idx(w, s, e)] = reduce_offset((uint64_t)alpha[e] * nu, S, m, u, sh);
+                    continue;
+                }
+                const uint32_t nu2 = c.kslot(ly.sqB(), 4, 3, w, s);
+                const __int128 T = (__int128)((uint64_t)alpha[e] * nu) + (uint64_t)alpha_h[e] * nu2 + S;
+                if (!c.real(w, s)) continue;
+                const __int128 top = s < 4 ? (__int128)1 << 64 : ((__int128)1 << 64) - ((__int128)m << 32);
+                if (T < 0 || T >= top) t_in_range = false;
+                x.b[idx(w, s, e)] = s < 4 ? redc_any((uint64_t)T, m, 0u - u) : redc_small((uint64_t)T, m, 0u - u);
             }
         }
     }
@@ -230,11 +252,11 @@ bool emul_modexp_mfma(const ModPlan &mp, const MfmaTables &T, const std::vector<
                     }
                     a.b[idx(wv, s, e)] = acc_redc(sb, m, u);
                     a.p[idx(wv, s, e)] = acc_redc(sp, mpp, up);
-                    unit.b[idx(wv, s, e)] = c.sq ? c.kslot(ly.sqB(), 3, 1, wv, s) : 0u - m;
+                    unit.b[idx(wv, s, e)] = c.sq ? c.kslot(ly.sqB(), 4, 1, wv, s) : 0u - m;
                     unit.p[idx(wv, s, e)] = kap;
                     unit_in.b[idx(wv, s, e)] = c.sq ? c.kslot(ly.slotC(), 1, 0, wv, s) : 0u - m;
                     unit_in.p[idx(wv, s, e)] = kap;
-                    one.b[idx(wv, s, e)] = c.sq ? c.kslot(ly.sqB(), 3, 2, wv, s) : c.kslot(ly.one(), 2, 0, wv, s);
+                    one.b[idx(wv, s, e)] = c.sq ? c.kslot(ly.sqB(), 4, 2, wv, s) : c.kslot(ly.one(), 2, 0, wv, s);
                     one.p[idx(wv, s, e)] = c.kslot(ly.one(), 2, 1, wv, s);
                 }
             }

@@ -204,12 +204,15 @@ void finish_group(JobGroup &g) {
     size_t full = 0;
     for (const PlannedJob &J : g.jobs) full += (size_t)mfma_tiles(g.shape, (size_t)J.j.batch);
     const int te = spread_tile_elems(g.shape, full, g.device);
-    g.tiles = 0;
+    g.tiles = g.groups = 0;
     g.max_window = 1;
     for (PlannedJob &J : g.jobs) {
         J.j.tile0 = g.tiles;
+        J.j.group0 = g.groups;
         J.j.tile_elems = te;
-        g.tiles += mfma_job_tiles(g.shape, (size_t)J.j.batch, te);
+        const int t = mfma_job_tiles(g.shape, (size_t)J.j.batch, te);
+        g.tiles += t;
+        g.groups += g.shape.groups(t);
         g.max_window = std::max(g.max_window, J.j.window);
     }
 }
@@ -219,6 +222,8 @@ hipError_t launch_group(const JobGroup &g, const MJob *d_jobs, uint32_t *table, 
     a.jobs = d_jobs;
     a.njobs = (int)g.jobs.size();
     a.tiles = g.tiles;
+    a.groups = g.groups;
+    a.split = split_tiles(g.shape, (size_t)g.tiles, g.device);
     a.max_window = g.max_window;
     a.table = table;
     a.scaled = g.scaled ? 1 : 0;

@@ -46,7 +46,7 @@ struct JobGroup {
     bool auto_tile = true;  // no context asked for a tile and none was tuned
     int device = 0;
     std::vector<PlannedJob> jobs;
-    int tiles = 0;
+    int tiles = 0, groups = 0;
     int max_window = 1;
     bool scaled = false;    // every job's key holds the scaled form (the kernel keeps B residues scaled)
     size_t table_words() const { return modexp_mfma_table_words(shape, max_window, (size_t)tiles); }

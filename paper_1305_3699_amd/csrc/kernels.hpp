@@ -81,6 +81,7 @@ struct MJob {
     uint32_t *out;
     int batch, in_limbs, in_stride, L, out_stride, exp_limbs, exp_stride, window;
     int tile0;
+    int group0;          // first workgroup (MLayout::groups; split launches: tile0)
     int tile_elems;
 };
 
@@ -90,7 +91,9 @@ struct ModexpMfmaLaunch {
     MJob inl[2];
     const MJob *jobs;
     int njobs;
-    int tiles;           // total tiles of all jobs = workgroups launched
+    int tiles;           // total tiles of all jobs
+    int groups;          // total workgroups of all jobs (MLayout::groups)
+    bool split;          // run the split kernel, one workgroup per tile
     int max_window;      // window table slots hold 2^max_window entries
     uint32_t *table;     // scratch: modexp_mfma_table_words(shape, max_window, tiles) words
     int scaled;          // every job's key keeps scaled B residues (MfmaTables::scaled)

@@ -47,7 +47,7 @@ size_t modexp_mfma_table_words(const MLayout &s, int max_window, size_t workgrou
     return workgroups * ((size_t)1 << max_window) * (size_t)s.W * s.SLOTS() * 64;
 }
 
-int mfma_tiles(const MLayout &s, size_t elements) { return (int)((elements + s.NM() - 1) / s.NM()); }
+int mfma_tiles(const MLayout &s, size_t elements) { return mfma_job_tiles(s, elements, 0); }
 
 int mfma_job_tiles(const MLayout &s, size_t elements, int tile_elems) {
     const size_t e = tile_elems > 0 && tile_elems < s.NM() ? (size_t)tile_elems : (size_t)s.NM();

@@ -21,6 +21,8 @@
 // with s_i^2 = sigma_i c_i 2^-32, sigma_i = +-1 (see mfma_publish_xi).
 #pragma once
 
+#include <type_traits>
+
 #include "arith.hpp"
 #include "kernels.hpp"
 #include "limbs.hpp"
@@ -45,9 +47,22 @@ struct MShp {
     static constexpr int XSLOTS = 4 * W * MT;
     static constexpr int EXIT_WORDS = (2 * XSLOTS + 1) * NM;
     static_assert(XSLOTS > K, "a limb slot for each of the exit's K + 1 limbs");
-    // Entry: input limbs whose table words are in registers at once
-    static constexpr int ENTRY_STEP = MT <= 3 ? 8 : 4;
+    // The exchange buffers (the entry stages its inputs there); a single wave
+    // exchanges nothing
+    static constexpr bool WAVE = W == 1;
     static constexpr int BUF_WORDS = 2 * NM * BROW;
+    // Single-wave shapes that also run split over waves (SplitEngine), 16
+    // elements per workgroup; the words of its exchange, operand buffers and
+    // the inputs or limb sums
+    static constexpr int SPLIT = LY.split_waves();
+    static constexpr int SPLIT_WORDS(int wv) { return 2 * (MT + 1) * 64 + wv * (2 * MT / wv + 1) * 64 + WAVE_IO_WORDS; }
+    // Single-wave shapes: waves of a workgroup, the LDS words each needs (16
+    // elements' inputs, then a product's second operand, then 16 elements'
+    // limb sums), and the words of the constants they share
+    static constexpr int WAVE_GROUP = kWaveGroup;
+    static constexpr int WAVE_IO_WORDS = 16 * (2 * K + 1) > (2 * XSLOTS + 1) * 16 ? 16 * (2 * K + 1) : (2 * XSLOTS + 1) * 16;
+    static constexpr int WAVE_WORDS = ((WAVE_IO_WORDS > SLOTS * 64 ? WAVE_IO_WORDS : SLOTS * 64) + 3) & ~3;
+    static constexpr int WAVE_TILE_WORDS = 2 * MT * KSTEPS * 64 * 4 + MT * 32;
     static constexpr int WORK_WORDS = EXIT_WORDS > BUF_WORDS ? EXIT_WORDS : BUF_WORDS;
     // Where the second extension's constant tiles (the same for every key of
     // the base pair) live: registers for 32-element tiles with few k-steps;
@@ -56,8 +71,8 @@ struct MShp {
     // are read from global memory (L2) at each step.
     static constexpr int A2_TILE_WORDS = W * MT * KSTEPS * 64 * 4;
     static constexpr bool A2_FITS_LDS = WORK_WORDS + A2_TILE_WORDS <= 36 * 1024;
-    static constexpr bool A2_GLOBAL = KSTEPS > 5 || (KSTEPS == 5 && !A2_FITS_LDS);
-    static constexpr bool A2_LDS = !A2_GLOBAL && (NT == 1 || KSTEPS >= 5);
+    static constexpr bool A2_GLOBAL = !WAVE && (KSTEPS > 5 || (KSTEPS == 5 && !A2_FITS_LDS));
+    static constexpr bool A2_LDS = !WAVE && !A2_GLOBAL && (NT == 1 || KSTEPS >= 5);
     // the per-key first-extension tiles follow the second ones to global
     // memory for those shapes (their workgroups of 9-12 waves leave 168
     // registers per lane)
@@ -68,21 +83,18 @@ struct MShp {
     // them in LDS, [W][MT][4 lane groups][8 words], read where they are used.
     static constexpr bool C_LDS = KSTEPS > 9;
     static constexpr int C_WORDS = C_LDS ? W * MT * 4 * 8 : 0;
-    static constexpr int LDS_WORDS = WORK_WORDS + A2_WORDS + C_WORDS;
+    static constexpr int LDS_WORDS = WAVE ? WAVE_TILE_WORDS + WAVE_GROUP * WAVE_WORDS : WORK_WORDS + A2_WORDS + C_WORDS;
     // Each wave's second operand of the next window multiplication is
     // prefetched from the window table into LDS while the squarings before it
     // run: [SLOTS][64] words per wave, wherever that still fits the 160 KiB
     // a workgroup may hold (every shape but the 513-channel one).
     static constexpr int PF_WORDS = W * SLOTS * 64;
-    static constexpr bool PREFETCH = (size_t)(LDS_WORDS + PF_WORDS) * 4 <= 160 * 1024;
+    static constexpr bool PREFETCH = !WAVE && (size_t)(LDS_WORDS + PF_WORDS) * 4 <= 160 * 1024;
     // Resident waves per SIMD the register allocation must allow (1: no
-    // constraint).  The 32-element tile at k = 33 keeps both extensions'
-    // tiles in registers (25 KB of LDS per workgroup) and would take 205
-    // VGPRs, i.e. 2 waves per SIMD; held to 168 VGPRs (3 waves, 4 workgroups
-    // and 128 elements per CU) it spills about 70 registers to scratch and
-    // still runs the RSA-2048 CRT launch 6% faster than the 16-element tile
-    // (4 waves per SIMD, 128 VGPRs, spilled in the hot loop: 2.5x slower).
-    static constexpr int WAVES_PER_EU = (K == 33 && NT == 2) ? 3 : 1;
+    // constraint).  A wave alone on its SIMD issues a multiply-add every 8.8
+    // cycles, two together one every 4.3, so single-wave shapes hold to two.
+    static constexpr int WAVES_PER_EU = WAVE ? 2 : 1;
+    static constexpr int THREADS = 64 * (WAVE ? WAVE_GROUP : W);
 };
 
 template <int MT, int NT>
@@ -359,7 +371,7 @@ __device__ __forceinline__ void mfma_mm(const MConstOf<K, W, MT, NT> &C, MState<
 }
 
 template <int MT, int NT>
-__device__ __forceinline__ void mstate_store(gu32 *__restrict__ p, const MState<MT, NT> &a) {
+__device__ __forceinline__ void mstate_store(gu32 *__restrict__ p, const MState<MT, NT> &a, bool r = true) {
 #pragma unroll
     for (int mt = 0; mt < MT; mt++)
 #pragma unroll
@@ -367,12 +379,13 @@ __device__ __forceinline__ void mstate_store(gu32 *__restrict__ p, const MState<
             p[(mt * NT + nt) * 64] = a.b[mt][nt];
             p[(MT * NT + mt * NT + nt) * 64] = a.p[mt][nt];
         }
+    if (r)
 #pragma unroll
-    for (int nt = 0; nt < NT; nt++) p[(2 * MT * NT + nt) * 64] = a.r[nt];
+        for (int nt = 0; nt < NT; nt++) p[(2 * MT * NT + nt) * 64] = a.r[nt];
 }
 
 template <int MT, int NT>
-__device__ __forceinline__ void mstate_load(const gu32 *__restrict__ p, MState<MT, NT> &a) {
+__device__ __forceinline__ void mstate_load(const gu32 *__restrict__ p, MState<MT, NT> &a, bool r = true) {
 #pragma unroll
     for (int mt = 0; mt < MT; mt++)
 #pragma unroll
@@ -380,8 +393,31 @@ __device__ __forceinline__ void mstate_load(const gu32 *__restrict__ p, MState<M
             a.b[mt][nt] = p[(mt * NT + nt) * 64];
             a.p[mt][nt] = p[(MT * NT + mt * NT + nt) * 64];
         }
+    if (r)
 #pragma unroll
-    for (int nt = 0; nt < NT; nt++) a.r[nt] = p[(2 * MT * NT + nt) * 64];
+        for (int nt = 0; nt < NT; nt++) a.r[nt] = p[(2 * MT * NT + nt) * 64];
+}
+
+// Table digits of the elements of one lane's slots.
+template <int NT>
+struct MDigits {
+    uint32_t d[NT];
+};
+
+// Each lane slot loads the entry of its own element's digit.
+template <int MT, int NT>
+__device__ __forceinline__ void mstate_load_elems(const gu32 *__restrict__ tw, size_t estride, const MDigits<NT> &d,
+                                                  MState<MT, NT> &y, bool r = true) {
+#pragma unroll
+    for (int nt = 0; nt < NT; nt++) {
+        const gu32 *__restrict__ pe = tw + (size_t)d.d[nt] * estride;
+#pragma unroll
+        for (int mt = 0; mt < MT; mt++) {
+            y.b[mt][nt] = pe[(mt * NT + nt) * 64];
+            y.p[mt][nt] = pe[(MT * NT + mt * NT + nt) * 64];
+        }
+        if (r) y.r[nt] = pe[(2 * MT * NT + nt) * 64];
+    }
 }
 
 // The same in LDS (p = this wave's buffer + lane): each wave reads and
@@ -429,7 +465,7 @@ __device__ __forceinline__ void mstate_unit(const MConstOf<K, W, MT, NT> &C, con
         const size_t sl = (size_t)wave * MT + mt;
         const uint32_t kap = mb[S::LY.slotP() + (sl * 4 + 3) * 64 + lane];
         uint32_t ub = 0u - C.slotB(mt).m;
-        if (SQ) ub = entry ? mk[S::LY.slotC() + sl * 64 + lane] : mk[S::LY.sqB() + (sl * 3 + 1) * 64 + lane];
+        if (SQ) ub = entry ? mk[S::LY.slotC() + sl * 64 + lane] : mk[S::LY.sqB() + (sl * 4 + 1) * 64 + lane];
 #pragma unroll
         for (int nt = 0; nt < NT; nt++) {
             y.b[mt][nt] = ub;
@@ -453,6 +489,13 @@ __device__ __forceinline__ uint32_t mexp_limb(const gu32 *__restrict__ e, int l)
 // (s_waitcnt vmcnt(0): on this target the immediate holds vmcnt in bits 3:0
 // and 15:14, expcnt in 6:4, lgkmcnt in 11:8; the others stay at their maximum).
 __device__ __forceinline__ void vmem_drain() { __builtin_amdgcn_s_waitcnt(0x0F70); }
+
+// Orders the LDS accesses of one wave's lanes: those before it are done (they
+// complete in order) when another lane's after it read or write.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
 
 // One row of the operand prefetch: lane l's word src[l] lands in LDS at
 // dst[l] without passing through registers (global_load_lds_dword; M0 holds
@@ -506,29 +549,17 @@ __device__ __forceinline__ int mjob_tile_elems(const MJob &J, int NM) {
     return J.tile_elems > 0 && J.tile_elems < NM ? J.tile_elems : NM;
 }
 
-// Leave the RNS: buf2 holds the digits xi' of the exit product, r its
-// redundant residues.  The limb sums of sum_j xi'_j M'_j are one more
-// contraction of those digits, on the matrix cores with the base's exit tiles
-// (read once, from global memory); then each wave takes every W-th element,
-// one limb per lane (limbs.hpp): minus alpha M' (alpha from limb 0 and r), the
-// quotient by N from the top limbs, canonical limbs stored coalesced.
-//
-// RSA-2048 encryption of 10,007 messages spent about 350 of its 416 us in the
-// entry and an exit of K (L + 1) multiply-adds and ceil(log2(K + 2))
-// conditional subtractions on one lane per element.
+// The end of the exit: each wave takes every `waves`-th element, one limb per lane
+// (limbs.hpp).  tsum: [NM][XSLOTS] limb sums of sum_j xi'_j M'_j, each plus
+// kExitOffset; rl: [NM] redundant residues; ne: elements to store, the first
+// being element e0 of the job.
 template <int K, int W, int MT, int NT>
-__device__ __forceinline__ void mfma_exit(const MConstOf<K, W, MT, NT> &C, const gu32 *__restrict__ mb,
-                                          const gu32 *__restrict__ mk, uint32_t *__restrict__ lds,
-                                          const uint32_t (&r)[NT], int wave, int lane, const MJob &J, int e0,
-                                          gu32 *__restrict__ out) {
+__device__ __forceinline__ void mfma_exit_limbs(const gu32 *__restrict__ mb, const gu32 *__restrict__ mk,
+                                                const uint64_t *tsum, const uint32_t *rl, uint32_t Mpinv_r, int wave,
+                                                int waves, int lane, const MJob &J, int e0, int ne) {
     using S = MShp<K, W, MT, NT>;
     constexpr int LC = (K + 1 + 63) / 64;                       // words per lane of a K + 1 limb number
-    const int g = lane >> 4;
-    const uint32_t *buf2 = lds + S::NM * S::BROW;
-    uint64_t *tsum = (uint64_t *)lds;                           // [NM][XSLOTS]
-    uint32_t *rl = lds + 2 * S::NM * S::XSLOTS;                 // [NM]
-    mfma_v4i D[MT][NT];
-    mfma_contract<K, W, MT, NT>((gcv4i *)(mb + S::LY.xt()) + (size_t)wave * MT * S::KSTEPS * 64, C.loff, buf2, lane, D);
+    gu32 *__restrict__ out = (gu32 *)J.out;
     uint32_t Mp[LC], N[LC];
 #pragma unroll
     for (int c = 0; c < LC; c++) {
@@ -536,28 +567,15 @@ __device__ __forceinline__ void mfma_exit(const MConstOf<K, W, MT, NT> &C, const
         Mp[c] = l <= K ? mb[S::LY.MpF() + l] : 0u;
         N[c] = l < K ? mk[S::LY.Nl() + l] : 0u;
     }
-    __syncthreads();                                            // every wave has read buf2
-#pragma unroll
-    for (int mt = 0; mt < MT; mt++)
-#pragma unroll
-        for (int nt = 0; nt < NT; nt++)
-            tsum[(16 * nt + (lane & 15)) * S::XSLOTS + (wave * MT + mt) * 4 + g] =
-                mfma_accumulate<S::PAIR_I32>(D[mt][nt], kExitOffset, C.kf);
-    if (wave == 0 && g == 0)
-#pragma unroll
-        for (int nt = 0; nt < NT; nt++) rl[16 * nt + lane] = r[nt];
-    __syncthreads();
     const int L = J.L, t = top_limb<LC>(N);
     const double nd = limbs_top<LC>(N, t);
-    const int left = J.batch - e0, te = mjob_tile_elems(J, S::NM);
-    const int ne = left < te ? left : te;
-    for (int n = wave; n < ne; n += W) {
+    for (int n = wave; n < ne; n += waves) {
         uint64_t T[LC];
         uint32_t v[LC];
 #pragma unroll
         for (int c = 0; c < LC; c++) T[c] = 64 * c + lane <= K ? tsum[n * S::XSLOTS + 64 * c + lane] : 0u;
         const uint32_t alpha =
-            ((uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)T[0]) - rl[n]) * C.Mpinv_r;   // in [0, K)
+            ((uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)T[0]) - rl[n]) * Mpinv_r;   // in [0, K)
 #pragma unroll
         for (int c = 0; c < LC; c++) T[c] += (uint64_t)alpha * (uint32_t)~Mp[c];                 // - alpha M'
         if (lane == 0) T[0] += alpha;
@@ -577,6 +595,42 @@ __device__ __forceinline__ void mfma_exit(const MConstOf<K, W, MT, NT> &C, const
         for (int c = 0; c < LC; c++)
             if (64 * c + lane < L) o[64 * c + lane] = v[c];
     }
+}
+
+// Leave the RNS: buf2 holds the digits xi' of the exit product, r its
+// redundant residues.  The limb sums of sum_j xi'_j M'_j are one more
+// contraction of those digits, on the matrix cores with the base's exit tiles
+// (read once, from global memory); then each wave takes every W-th element,
+// one limb per lane (limbs.hpp): minus alpha M' (alpha from limb 0 and r), the
+// quotient by N from the top limbs, canonical limbs stored coalesced.
+//
+// RSA-2048 encryption of 10,007 messages spent about 350 of its 416 us in the
+// entry and an exit of K (L + 1) multiply-adds and ceil(log2(K + 2))
+// conditional subtractions on one lane per element.
+template <int K, int W, int MT, int NT>
+__device__ __forceinline__ void mfma_exit(const MConstOf<K, W, MT, NT> &C, const gu32 *__restrict__ mb,
+                                          const gu32 *__restrict__ mk, uint32_t *__restrict__ lds,
+                                          const uint32_t (&r)[NT], int wave, int lane, const MJob &J, int e0) {
+    using S = MShp<K, W, MT, NT>;
+    const int g = lane >> 4;
+    const uint32_t *buf2 = lds + S::NM * S::BROW;
+    uint64_t *tsum = (uint64_t *)lds;                           // [NM][XSLOTS]
+    uint32_t *rl = lds + 2 * S::NM * S::XSLOTS;                 // [NM]
+    mfma_v4i D[MT][NT];
+    mfma_contract<K, W, MT, NT>((gcv4i *)(mb + S::LY.xt()) + (size_t)wave * MT * S::KSTEPS * 64, C.loff, buf2, lane, D);
+    __syncthreads();                                            // every wave has read buf2
+#pragma unroll
+    for (int mt = 0; mt < MT; mt++)
+#pragma unroll
+        for (int nt = 0; nt < NT; nt++)
+            tsum[(16 * nt + (lane & 15)) * S::XSLOTS + (wave * MT + mt) * 4 + g] =
+                mfma_accumulate<S::PAIR_I32>(D[mt][nt], kExitOffset, C.kf);
+    if (wave == 0 && g == 0)
+#pragma unroll
+        for (int nt = 0; nt < NT; nt++) rl[16 * nt + lane] = r[nt];
+    __syncthreads();
+    const int left = J.batch - e0, te = mjob_tile_elems(J, S::NM);
+    mfma_exit_limbs<K, W, MT, NT>(mb, mk, tsum, rl, C.Mpinv_r, wave, W, lane, J, e0, left < te ? left : te);
 }
 
 // The constant digit rows of both exchange buffers: channel K holds the
@@ -611,7 +665,7 @@ __device__ __forceinline__ void mfma_setup(const gu32 *__restrict__ mb, const gu
             C.uB[mt] = mb[S::LY.slotB() + (sl * 3 + 1) * 64 + lane];
             C.mP[mt] = mb[S::LY.slotP() + (sl * 4 + 0) * 64 + lane];
             C.uP[mt] = mb[S::LY.slotP() + (sl * 4 + 1) * 64 + lane];
-            C.nuB[mt] = SQ ? mk[S::LY.sqB() + (sl * 3 + 0) * 64 + lane] : mb[S::LY.slotB() + (sl * 3 + 2) * 64 + lane];
+            C.nuB[mt] = SQ ? mk[S::LY.sqB() + (sl * 4 + 0) * 64 + lane] : mb[S::LY.slotB() + (sl * 3 + 2) * 64 + lane];
             C.HP[mt] = mb[S::LY.slotP() + (sl * 4 + 2) * 64 + lane];
             if (!SQ) C.cB[mt] = mk[S::LY.slotC() + sl * 64 + lane];
         }
@@ -676,6 +730,126 @@ __device__ __forceinline__ void mfma_load_tiles(const gu32 *__restrict__ mb, con
     }
 }
 
+// The tile's input rows into LDS, coalesced: [NM][in_limbs | 1] words in the
+// (still unused) exchange buffers (in_limbs <= 2 K, so a row is below 2 BROW).
+template <int W, int NM>
+__device__ __forceinline__ void mfma_stage_inputs(const MJob &J, int e0, uint32_t *__restrict__ lds, int wave, int lane) {
+    constexpr int R = (NM + W - 1) / W;
+    const gu32 *__restrict__ in = (const gu32 *)J.in;
+    const int is = J.in_limbs | 1;
+    for (int l = lane; l < J.in_limbs; l += 64) {
+        uint32_t v[R];
+#pragma unroll
+        for (int i = 0; i < R; i++) {
+            const int n = wave + i * W, m = e0 + n;
+            v[i] = n < NM && m < J.batch ? in[(size_t)m * J.in_stride + l] : 0u;
+        }
+#pragma unroll
+        for (int i = 0; i < R; i++)
+            if (wave + i * W < NM) lds[(wave + i * W) * is + l] = v[i];
+    }
+}
+
+// Entry: residues of Z = sum_h X_h Y_h in the kept representation, from the
+// staged inputs, for MT tiles from column col on.  The table's words of STEP
+// limbs are loaded before they are used, so that a step waits for memory once.
+template <int ECOLS, int MT, int NT>
+__device__ __forceinline__ void mfma_entry_half(const MJob &J, const uint32_t *__restrict__ lds, int col, int lane,
+                                                const uint32_t (&m)[MT], const uint32_t (&u)[MT],
+                                                uint32_t (&x)[MT][NT]) {
+    constexpr int STEP = MT <= 3 ? 8 : 4;
+    const gu32 *__restrict__ E = (const gu32 *)J.E + col;
+    const int is = J.in_limbs | 1;
+    Acc acc[MT][NT];
+    for (int l0 = 0; l0 < J.in_limbs; l0 += STEP) {
+        uint32_t e[STEP][MT];
+#pragma unroll
+        for (int z = 0; z < STEP; z++) {
+            // past the last limb: any row, its input word counts as zero
+            const size_t row = (size_t)(l0 + z < J.in_limbs ? l0 + z : 0) * ECOLS;
+#pragma unroll
+            for (int mt = 0; mt < MT; mt++) e[z][mt] = E[row + 4 * mt];
+        }
+#pragma unroll
+        for (int z = 0; z < STEP; z++)
+#pragma unroll
+            for (int nt = 0; nt < NT; nt++) {
+                const uint32_t v = l0 + z < J.in_limbs ? lds[(16 * nt + (lane & 15)) * is + l0 + z] : 0u;
+#pragma unroll
+                for (int mt = 0; mt < MT; mt++) acc_mac(acc[mt][nt], v, e[z][mt]);
+            }
+    }
+#pragma unroll
+    for (int mt = 0; mt < MT; mt++)
+#pragma unroll
+        for (int nt = 0; nt < NT; nt++) x[mt][nt] = acc_redc(acc[mt][nt], m[mt], u[mt]);
+}
+
+// tile0: the first of the wave's MT tiles; SLOTB: B slots of the shape.
+template <int ECOLS, int SLOTB, int MT, int NT>
+__device__ __forceinline__ void mfma_entry(const MJob &J, const uint32_t *__restrict__ lds, int tile0, int lane,
+                                           const uint32_t (&mB)[MT], const uint32_t (&uB)[MT],
+                                           const uint32_t (&mP)[MT], const uint32_t (&uP)[MT], MState<MT, NT> &a) {
+    const int colB = 4 * tile0 + (lane >> 4);
+    mfma_entry_half<ECOLS, MT, NT>(J, lds, colB, lane, mB, uB, a.b);
+    mfma_entry_half<ECOLS, MT, NT>(J, lds, colB + SLOTB, lane, mP, uP, a.p);
+    // the redundant column is nonzero in the first row of each chunk only
+    const gu32 *__restrict__ E = (const gu32 *)J.E + ECOLS - 1;
+    const int is = J.in_limbs | 1;
+#pragma unroll
+    for (int nt = 0; nt < NT; nt++) a.r[nt] = 0;
+    for (int l = 0; l < J.in_limbs; l += J.L) {
+        const uint32_t e = E[(size_t)l * ECOLS];
+#pragma unroll
+        for (int nt = 0; nt < NT; nt++) a.r[nt] += lds[(16 * nt + (lane & 15)) * is + l] * e;
+    }
+}
+
+// The entry of one wave's tile, 16 elements at a time (wl: 16 rows).
+template <int K, int MT, int NT, class C>
+__device__ __forceinline__ void wave_entry(const MJob &J, int e0, uint32_t *__restrict__ wl, int lane, const C &c,
+                                           MState<MT, NT> &a) {
+    uint32_t mB[MT], uB[MT], mP[MT], uP[MT];
+#pragma unroll
+    for (int mt = 0; mt < MT; mt++) {
+        const MSlotB sb = c.slotB(mt);
+        const MSlotP sp = c.slotP(mt);
+        mB[mt] = sb.m, uB[mt] = sb.u, mP[mt] = sp.m, uP[mt] = sp.u;
+    }
+#pragma unroll
+    for (int nt = 0; nt < NT; nt++) {
+        MState<MT, 1> h;
+        wave_sync();
+        mfma_stage_inputs<1, 16>(J, e0 + 16 * nt, wl, 0, lane);
+        wave_sync();
+        mfma_entry<MShp<K, 1, MT, NT>::ECOLS, 4 * MT, MT, 1>(J, wl, 0, lane, mB, uB, mP, uP, h);
+#pragma unroll
+        for (int mt = 0; mt < MT; mt++) {
+            a.b[mt][nt] = h.b[mt][0];
+            a.p[mt][nt] = h.p[mt][0];
+        }
+        a.r[nt] = h.r[0];
+    }
+}
+
+// M mod N in the kept representation (M tiles from tile0 on) into a table entry.
+template <int K, int W, int MT, bool SQ, int M, int NT>
+__device__ __forceinline__ void mstate_one(const gu32 *__restrict__ mk, int tile0, int lane, MState<M, NT> &one) {
+    constexpr MLayout LY{K, W, MT, NT};
+#pragma unroll
+    for (int t = 0; t < M; t++) {
+        const size_t sl = (size_t)tile0 + t;
+#pragma unroll
+        for (int nt = 0; nt < NT; nt++) {
+            one.b[t][nt] = SQ ? mk[LY.sqB() + (sl * 4 + 2) * 64 + lane] : mk[LY.one() + (sl * 2 + 0) * 64 + lane];
+            one.p[t][nt] = mk[LY.one() + (sl * 2 + 1) * 64 + lane];
+        }
+    }
+    const uint32_t onr = mk[LY.one() + (size_t)W * MT * 2 * 64];
+#pragma unroll
+    for (int nt = 0; nt < NT; nt++) one.r[nt] = onr;
+}
+
 // One tile of exponentiation job J: columns n < 16*NT hold elements e0 + n
 // of the job (those with n < mjob_tile_elems(J) are stored), with window
 // table slot `slot` of the launch;
@@ -689,85 +863,28 @@ __device__ __forceinline__ void modexp_mfma_tile(const MJob &J, int e0, uint32_t
     uint32_t *buf2 = lds + S::NM * S::BROW;
     const gu32 *__restrict__ mb = (const gu32 *)J.mb;
     const gu32 *__restrict__ mk = (const gu32 *)J.mk;
-    const gu32 *__restrict__ E = (const gu32 *)J.E;
     const gu32 *__restrict__ ex = (const gu32 *)J.exp;
-    const gu32 *__restrict__ in = (const gu32 *)J.in;
     gu32 *__restrict__ out = (gu32 *)J.out;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lane = threadIdx.x & 63;
-    const int g = lane >> 4;
 
-    // the tile's inputs, coalesced, [NM][is] in the (still unused) exchange
-    // buffers: in_limbs <= 2 K words per element, below 2 BROW
-    const int is = J.in_limbs | 1;
-    for (int l = lane; l < J.in_limbs; l += 64) {
-        uint32_t v[(S::NM + W - 1) / W];
-#pragma unroll
-        for (int i = 0; i < (S::NM + W - 1) / W; i++) {
-            const int n = wave + i * W, m = e0 + n;
-            v[i] = n < S::NM && m < J.batch ? in[(size_t)m * J.in_stride + l] : 0u;
-        }
-#pragma unroll
-        for (int i = 0; i < (S::NM + W - 1) / W; i++)
-            if (wave + i * W < S::NM) lds[(wave + i * W) * is + l] = v[i];
-    }
-
+    mfma_stage_inputs<W, S::NM>(J, e0, lds, wave, lane);
     MConstOf<K, W, MT, NT> C;
     mfma_setup<K, W, MT, NT, SQ>(mb, mk, lds, wave, lane, C);
     __syncthreads();
 
-    // entry: residues of Z = sum_h X_h Y_h in the kept representation; the
-    // table's words of ENTRY_STEP limbs are loaded before they are used, so
-    // that a step waits for memory once
     MState<MT, NT> a;
-    {
-        constexpr int STEP = S::ENTRY_STEP;
-        Acc ab[MT][NT], ap[MT][NT];
-        uint32_t zr[NT];
+    if constexpr (S::C_LDS) {
+        uint32_t mB[MT], uB[MT], mP[MT], uP[MT];
 #pragma unroll
-        for (int nt = 0; nt < NT; nt++) zr[nt] = 0;
-        const gu32 *__restrict__ EB = E + wave * 4 * MT + g, *__restrict__ EP = EB + W * 4 * MT;
-        for (int l0 = 0; l0 < J.in_limbs; l0 += STEP) {
-            uint32_t eb[STEP][MT], ep[STEP][MT], er[STEP];
-#pragma unroll
-            for (int z = 0; z < STEP; z++) {
-                // past the last limb: any row, its input word counts as zero
-                const size_t row = (size_t)(l0 + z < J.in_limbs ? l0 + z : 0) * S::ECOLS;
-#pragma unroll
-                for (int mt = 0; mt < MT; mt++) {
-                    eb[z][mt] = EB[row + 4 * mt];
-                    ep[z][mt] = EP[row + 4 * mt];
-                }
-                er[z] = E[row + S::ECOLS - 1];
-            }
-#pragma unroll
-            for (int z = 0; z < STEP; z++) {
-                uint32_t v[NT];
-#pragma unroll
-                for (int nt = 0; nt < NT; nt++)
-                    v[nt] = l0 + z < J.in_limbs ? lds[(16 * nt + (lane & 15)) * is + l0 + z] : 0u;
-#pragma unroll
-                for (int mt = 0; mt < MT; mt++)
-#pragma unroll
-                    for (int nt = 0; nt < NT; nt++) {
-                        acc_mac(ab[mt][nt], v[nt], eb[z][mt]);
-                        acc_mac(ap[mt][nt], v[nt], ep[z][mt]);
-                    }
-#pragma unroll
-                for (int nt = 0; nt < NT; nt++) zr[nt] += v[nt] * er[z];
-            }
+        for (int mt = 0; mt < MT; mt++) {
+            const MSlotB sb = C.slotB(mt);
+            const MSlotP sp = C.slotP(mt);
+            mB[mt] = sb.m, uB[mt] = sb.u, mP[mt] = sp.m, uP[mt] = sp.u;
         }
-#pragma unroll
-        for (int mt = 0; mt < MT; mt++)
-#pragma unroll
-            for (int nt = 0; nt < NT; nt++) {
-                const MSlotB sb = C.slotB(mt);
-                const MSlotP sp = C.slotP(mt);
-                a.b[mt][nt] = acc_redc(ab[mt][nt], sb.m, sb.u);
-                a.p[mt][nt] = acc_redc(ap[mt][nt], sp.m, sp.u);
-            }
-#pragma unroll
-        for (int nt = 0; nt < NT; nt++) a.r[nt] = zr[nt];
+        mfma_entry<S::ECOLS, S::XSLOTS, MT, NT>(J, lds, wave * MT, lane, mB, uB, mP, uP, a);
+    } else {
+        mfma_entry<S::ECOLS, S::XSLOTS, MT, NT>(J, lds, wave * MT, lane, C.mB, C.uB, C.mP, C.uP, a);
     }
     __syncthreads();                                            // every wave has read the inputs
     mfma_rows<K, W, MT, NT>(lds);
@@ -778,18 +895,7 @@ __device__ __forceinline__ void modexp_mfma_tile(const MJob &J, int e0, uint32_t
     gu32 *__restrict__ tw = (gu32 *)table + ((slot << max_window) * W + wave) * (size_t)(S::SLOTS * 64) + lane;
     {
         MState<MT, NT> one;
-#pragma unroll
-        for (int mt = 0; mt < MT; mt++) {
-            const size_t sl = (size_t)wave * MT + mt;
-#pragma unroll
-            for (int nt = 0; nt < NT; nt++) {
-                one.b[mt][nt] = SQ ? mk[S::LY.sqB() + (sl * 3 + 2) * 64 + lane] : mk[S::LY.one() + (sl * 2 + 0) * 64 + lane];
-                one.p[mt][nt] = mk[S::LY.one() + (sl * 2 + 1) * 64 + lane];
-            }
-        }
-        const uint32_t onr = mk[S::LY.one() + (size_t)W * MT * 2 * 64];
-#pragma unroll
-        for (int nt = 0; nt < NT; nt++) one.r[nt] = onr;
+        mstate_one<K, W, MT, SQ>(mk, wave * MT, lane, one);
         mstate_store<MT, NT>(tw, one);   // T[0] = M mod N
     }
 
@@ -816,6 +922,16 @@ __device__ __forceinline__ void modexp_mfma_tile(const MJob &J, int e0, uint32_t
     int bitpos = -1, sq = 0;
     uint32_t dm = 0;
     int ysrc = Y_UNIT, yidx = 0;
+    // per-element exponents: window i of the elements of this lane's slots
+    auto dig_of = [&](int i) {
+        MDigits<NT> d;
+#pragma unroll
+        for (int nt = 0; nt < NT; nt++) {
+            const int m = e0 + 16 * nt + (lane & 15);
+            d.d[nt] = mexp_digit(ex + (size_t)(m < J.batch ? m : 0) * J.exp_stride, J.exp_limbs, nd, w, i);
+        }
+        return d;
+    };
     for (;;) {
         if (ysrc == Y_SQUARE) {
             mfma_mm<K, W, MT, NT, SQ>(C, a, a, buf1, buf2, wave, lane, true);
@@ -831,20 +947,7 @@ __device__ __forceinline__ void modexp_mfma_tile(const MJob &J, int e0, uint32_t
                 if (ysrc == Y_PREF_DMA) vmem_drain();   // the entry copied at the window's start has landed
                 mstate_load_lds<MT, NT>(yb + lane, y);
             } else {
-                // per-element exponents: each lane slot loads the entry of its own element
-#pragma unroll
-                for (int nt = 0; nt < NT; nt++) {
-                    const int m = e0 + 16 * nt + (lane & 15);
-                    const gu32 *__restrict__ ep = ex + (size_t)(m < J.batch ? m : 0) * J.exp_stride;
-                    const uint32_t d = mexp_digit(ep, J.exp_limbs, nd, w, yidx);
-                    const gu32 *__restrict__ pe = tw + (size_t)d * estride;
-#pragma unroll
-                    for (int mt = 0; mt < MT; mt++) {
-                        y.b[mt][nt] = pe[(mt * NT + nt) * 64];
-                        y.p[mt][nt] = pe[(MT * NT + mt * NT + nt) * 64];
-                    }
-                    y.r[nt] = pe[(2 * MT * NT + nt) * 64];
-                }
+                mstate_load_elems<MT, NT>(tw, estride, dig_of(yidx), y);
                 vmem_drain();
             }
             mfma_mm<K, W, MT, NT, SQ>(C, a, y, buf1, buf2, wave, lane, phase != EXIT);
@@ -951,7 +1054,39 @@ __device__ __forceinline__ void modexp_mfma_tile(const MJob &J, int e0, uint32_t
         }
     }
 
-    mfma_exit<K, W, MT, NT>(C, mb, mk, lds, a.r, wave, lane, J, e0, out);
+    mfma_exit<K, W, MT, NT>(C, mb, mk, lds, a.r, wave, lane, J, e0);
+}
+
+}  // namespace rnsrsa
+
+#include "kernels_wave.hpp"
+
+namespace rnsrsa {
+
+// The job of a tile of the launch, its fields in scalar registers: read through
+// a pointer to either the launch's arguments or its job table they would count
+// as different per lane, and so would every address and branch made from them.
+template <int MJob::*FIRST>
+__device__ __forceinline__ MJob mjob_of(const ModexpMfmaLaunch &A, int group) {
+    MJob J;
+    if (A.jobs) {
+        int lo = 0, hi = A.njobs - 1;          // last job that starts at or before the workgroup
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (A.jobs[mid].*FIRST <= group) lo = mid; else hi = mid - 1;
+        }
+        J = A.jobs[lo];
+    } else {
+        J = (A.njobs > 1 && group >= A.inl[1].*FIRST) ? A.inl[1] : A.inl[0];
+    }
+    constexpr int NW = sizeof(MJob) / sizeof(int);
+    static_assert(sizeof(MJob) % sizeof(int) == 0, "whole words");
+    int w[NW];
+    __builtin_memcpy(w, &J, sizeof(J));
+#pragma unroll
+    for (int i = 0; i < NW; i++) w[i] = __builtin_amdgcn_readfirstlane(w[i]);
+    __builtin_memcpy(&J, w, sizeof(J));
+    return J;
 }
 
 // Exponentiation kernel, matrix-core variant: workgroup t runs tile t of the
@@ -961,39 +1096,67 @@ __device__ __forceinline__ void modexp_mfma_tile(const MJob &J, int e0, uint32_t
 // the per-lane addresses of the tile body live across it; the hardware
 // dispatcher refills the CUs as workgroups finish instead.)
 template <int K, int W, int MT, int NT, bool SQ>
-__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(MShp<K, W, MT, NT>::WAVES_PER_EU)))
+__global__ __launch_bounds__((MShp<K, W, MT, NT>::THREADS)) __attribute__((amdgpu_waves_per_eu(MShp<K, W, MT, NT>::WAVES_PER_EU)))
 void modexp_mfma_kernel(ModexpMfmaLaunch A) {
     using S = MShp<K, W, MT, NT>;
     __shared__ __attribute__((aligned(16))) uint32_t lds[S::LDS_WORDS];
     __shared__ __attribute__((aligned(16))) uint32_t ylds[S::PREFETCH ? S::PF_WORDS : 1];
-    const int tile = blockIdx.x;
-    MJob J;
-    if (A.jobs) {
-        int lo = 0, hi = A.njobs - 1;          // last job with tile0 <= tile
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (A.jobs[mid].tile0 <= tile) lo = mid; else hi = mid - 1;
-        }
-        J = A.jobs[lo];
+    const MJob J = mjob_of<&MJob::group0>(A, (int)blockIdx.x);
+    int tile = (int)blockIdx.x - J.group0;                       // of the job
+    if constexpr (W == 1) {
+        const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+        tile = tile * S::WAVE_GROUP + wave;
+        modexp_wave_tile<K, MT, NT, SQ>(J, tile * mjob_tile_elems(J, S::NM), lds,
+                                        lds + S::WAVE_TILE_WORDS + wave * S::WAVE_WORDS, A.table,
+                                        (size_t)(J.tile0 + tile), A.max_window);
     } else {
-        J = (A.njobs > 1 && tile >= A.inl[1].tile0) ? A.inl[1] : A.inl[0];
+        modexp_mfma_tile<K, W, MT, NT, SQ>(J, tile * mjob_tile_elems(J, S::NM), lds, A.table, blockIdx.x,
+                                           A.max_window, ylds);
     }
-    modexp_mfma_tile<K, W, MT, NT, SQ>(J, (tile - J.tile0) * mjob_tile_elems(J, S::NM), lds, A.table, blockIdx.x,
-                                       A.max_window, ylds);
 }
+
+// The split kernel of a single-wave shape: workgroup t runs tile t (see
+// SplitEngine).  Held to 3 waves per SIMD: 8,192 RSA-2048 decryptions, 1,024
+// workgroups that are then all resident, take 1.55 ms instead of 2.27 ms, a lone
+// one 1.00 ms instead of 0.99 ms.
+template <int K, int MT, int WV, bool SQ>
+__global__ __launch_bounds__(64 * WV) __attribute__((amdgpu_waves_per_eu(3))) void modexp_split_kernel(ModexpMfmaLaunch A) {
+    using S = MShp<K, 1, MT, 1>;
+    __shared__ __attribute__((aligned(16))) uint32_t lds[S::SPLIT_WORDS(WV)];
+    const MJob J = mjob_of<&MJob::tile0>(A, (int)blockIdx.x);
+    const int e0 = ((int)blockIdx.x - J.tile0) * mjob_tile_elems(J, 16);
+    modexp_split_tile<K, MT, WV, SQ>(J, e0, lds, A.table, blockIdx.x, A.max_window);
+}
+
+template <int K, int MT, int WV>
+hipError_t launch_modexp_split_t(const ModexpMfmaLaunch &a, hipStream_t s) {
+    if (a.scaled)
+        hipLaunchKernelGGL((modexp_split_kernel<K, MT, WV, true>), dim3((unsigned)a.tiles), dim3(64 * WV), 0, s, a);
+    else
+        hipLaunchKernelGGL((modexp_split_kernel<K, MT, WV, false>), dim3((unsigned)a.tiles), dim3(64 * WV), 0, s, a);
+    return hipGetLastError();
+}
+// compiled in a unit of its own, with the default instruction scheduler
+#define RNSRSA_MSPLIT(k, mt, wv) \
+    extern template hipError_t launch_modexp_split_t<k, mt, wv>(const ModexpMfmaLaunch &, hipStream_t);
+#include "kernel_configs_split.inc"
+#undef RNSRSA_MSPLIT
 
 template <int K, int W, int MT, int NT>
 hipError_t launch_modexp_mfma_t(const ModexpMfmaLaunch &a, hipStream_t s) {
     using S = MShp<K, W, MT, NT>;
     if (a.tiles <= 0) return hipSuccess;
+    if constexpr (S::SPLIT > 0) {
+        if (a.split) return launch_modexp_split_t<K, MT, S::SPLIT>(a, s);
+    }
     if constexpr (S::LY.sq_ok() && !S::A2_GLOBAL && !S::C_LDS) {
         if (a.scaled) {
-            hipLaunchKernelGGL((modexp_mfma_kernel<K, W, MT, NT, true>), dim3((unsigned)a.tiles), dim3(64 * W), 0, s,
+            hipLaunchKernelGGL((modexp_mfma_kernel<K, W, MT, NT, true>), dim3((unsigned)a.groups), dim3(S::THREADS), 0, s,
                                a);
             return hipGetLastError();
         }
     }
-    hipLaunchKernelGGL((modexp_mfma_kernel<K, W, MT, NT, false>), dim3((unsigned)a.tiles), dim3(64 * W), 0, s, a);
+    hipLaunchKernelGGL((modexp_mfma_kernel<K, W, MT, NT, false>), dim3((unsigned)a.groups), dim3(S::THREADS), 0, s, a);
     return hipGetLastError();
 }
 
@@ -1003,7 +1166,7 @@ hipError_t launch_modexp_mfma_t(const ModexpMfmaLaunch &a, hipStream_t s) {
 // kept representation and back with the base table's conversion factors).
 // Workgroup t serves elements [t*E, (t+1)*E), E = A.tile_elems (0: 16*NT).
 template <int K, int W, int MT, int NT>
-__global__ __launch_bounds__(64 * W) void montmul_mfma_kernel(MontMulMfmaLaunch A) {
+__global__ __launch_bounds__((MShp<K, W, MT, NT>::THREADS)) void montmul_mfma_kernel(MontMulMfmaLaunch A) {
     using S = MShp<K, W, MT, NT>;
     __shared__ __attribute__((aligned(16))) uint32_t lds[S::LDS_WORDS];
     const gu32 *__restrict__ mb = (const gu32 *)A.mb;
@@ -1011,13 +1174,22 @@ __global__ __launch_bounds__(64 * W) void montmul_mfma_kernel(MontMulMfmaLaunch 
     const gu32 *__restrict__ x = (const gu32 *)A.x;
     const gu32 *__restrict__ y = (const gu32 *)A.y;
     gu32 *__restrict__ out = (gu32 *)A.out;
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    // single-wave shapes: a tile is one wave's, every wave holds all channels
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int wave = S::WAVE ? 0 : wv;
+    const int tile = S::WAVE ? (int)blockIdx.x * S::WAVE_GROUP + wv : (int)blockIdx.x;
     const int lane = threadIdx.x & 63;
     const int g = lane >> 4;
-    MConstOf<K, W, MT, NT> C;
-    mfma_setup<K, W, MT, NT>(mb, mk, lds, wave, lane, C);
-    mfma_rows<K, W, MT, NT>(lds);
-    mfma_load_tiles<K, W, MT, NT>(mb, mk, lds, wave, lane, C);
+    std::conditional_t<S::WAVE, WaveEngine<K, MT, NT, false>, MConstOf<K, W, MT, NT>> C;
+    if constexpr (S::WAVE) {
+        C.setup(mb, mk, lds, lane);
+        __syncthreads();
+        C.load_tiles();
+    } else {
+        mfma_setup<K, W, MT, NT>(mb, mk, lds, wave, lane, C);
+        mfma_rows<K, W, MT, NT>(lds);
+        mfma_load_tiles<K, W, MT, NT>(mb, mk, lds, wave, lane, C);
+    }
     const int te = A.tile_elems > 0 && A.tile_elems < S::NM ? A.tile_elems : S::NM;
     const size_t B = (size_t)A.batch;
     int elem[NT];
@@ -1025,7 +1197,7 @@ __global__ __launch_bounds__(64 * W) void montmul_mfma_kernel(MontMulMfmaLaunch 
 #pragma unroll
     for (int nt = 0; nt < NT; nt++) {
         const int n = 16 * nt + (lane & 15);
-        elem[nt] = (int)blockIdx.x * te + n;
+        elem[nt] = tile * te + n;
         ok[nt] = n < te && elem[nt] < A.batch;
     }
     MState<MT, NT> a, b;
@@ -1053,9 +1225,13 @@ __global__ __launch_bounds__(64 * W) void montmul_mfma_kernel(MontMulMfmaLaunch 
         a.r[nt] = ok[nt] ? x[(size_t)2 * K * B + elem[nt]] : 0u;
         b.r[nt] = ok[nt] ? y[(size_t)2 * K * B + elem[nt]] : 0u;
     }
-    uint32_t *buf1 = lds;
-    uint32_t *buf2 = lds + S::NM * S::BROW;
-    mfma_mm<K, W, MT, NT>(C, a, b, buf1, buf2, wave, lane, true);
+    if constexpr (S::WAVE) {
+        C.x = a;
+        C.template product<true>(MRegOperand<MT, NT>{b});
+        a = C.x;
+    } else {
+        mfma_mm<K, W, MT, NT>(C, a, b, lds, lds + S::NM * S::BROW, wave, lane, true);
+    }
 #pragma unroll
     for (int mt = 0; mt < MT; mt++) {
         const size_t sl = (size_t)wave * MT + mt;
@@ -1080,18 +1256,20 @@ __global__ __launch_bounds__(64 * W) void montmul_mfma_kernel(MontMulMfmaLaunch 
 
 template <int K, int W, int MT, int NT>
 hipError_t launch_montmul_mfma_t(const MontMulMfmaLaunch &a, hipStream_t s) {
+    using S = MShp<K, W, MT, NT>;
     if (a.tiles <= 0) return hipSuccess;
-    hipLaunchKernelGGL((montmul_mfma_kernel<K, W, MT, NT>), dim3((unsigned)a.tiles), dim3(64 * W), 0, s, a);
+    hipLaunchKernelGGL((montmul_mfma_kernel<K, W, MT, NT>), dim3((unsigned)S::LY.groups(a.tiles)), dim3(S::THREADS), 0, s, a);
     return hipGetLastError();
 }
 
-// Resident workgroups per CU of the kernel for this shape (occupancy).
+// Resident tiles per CU of the kernel for this shape (occupancy).
 template <int K, int W, int MT, int NT>
 int mfma_blocks_per_cu_t() {
     int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, modexp_mfma_kernel<K, W, MT, NT, false>, 64 * W, 0) != hipSuccess)
+    using S = MShp<K, W, MT, NT>;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, modexp_mfma_kernel<K, W, MT, NT, false>, S::THREADS, 0) != hipSuccess)
         return 0;
-    return n;
+    return n * (S::WAVE ? S::WAVE_GROUP : 1);
 }
 
 }  // namespace rnsrsa

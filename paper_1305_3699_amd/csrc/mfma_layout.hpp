@@ -59,11 +59,49 @@ constexpr bool mfma_prime_fits(uint32_t m, int K, bool in_bprime) {
 // mfma_sum_bound(513) < 2^50, so that the sums are positive.
 constexpr uint64_t kExitOffset = 1ull << 50;
 
+// Waves of a workgroup of a single-wave shape (they share the constant tiles).
+constexpr int kWaveGroup = 4;
+
+// Wide second extension of the scaled form in single-wave shapes.  The digits
+// of B' are the kept residues zeta_t = x R M^-1 mod m'_t themselves, with
+// weights W_t = M'_t g_t, g_t = (M'_t)^-1 (R M^-1)^-1 mod m'_t, so that
+// sum_t zeta_t W_t = r + alpha M' with alpha < sum_t g_t, below 2^40 instead of
+// K.  alpha mod 2^32 comes from the redundant row as before, the bits above
+// from an estimate row: the top digits times round(kEstScale g_t / m'_t), which
+// is alpha / 2^18 within 2^13 (kEstScale = 2^6 per 2^24).  Step (iv) adds
+// alpha mod 2^kWideShift times nu and the bits above, plus kWideOffset, times
+// nu2 = 2^kWideShift nu mod m (at least m / 2 by the choice of the root's sign,
+// so that the offset, cancelled in the offset column, exceeds |S|).
+constexpr int kEstScale = 64;
+constexpr int kWideShift = 18;
+constexpr int kWideOffset = 1 << 16;
+
 struct MLayout {
     int K, W, MT, NT;
+    // A tile is the 16 NT elements of a workgroup or, in a single-wave shape, of
+    // one of its waves; the workgroups of a job of `tiles` tiles.
+    constexpr int groups(int tiles) const { return W == 1 ? (tiles + kWaveGroup - 1) / kWaveGroup : tiles; }
+    // Waves of a tile in the split kernel of a single-wave shape (0: it has none).
+    constexpr int split_waves() const { return W == 1 && NT == 1 && MT == 9 ? 3 : 0; }
     constexpr int CH() const { return 4 * MT - 1; }                 // prime channels per wave
     constexpr int KSTEPS() const { return (4 * K + 1 + 63) / 64; }  // 64-deep steps: 4 digits/channel + offset
     constexpr int KCH() const { return KSTEPS() * 16; }             // channels covered by the steps
+    // Order of the digit words in the contractions' K index: word 16 ks + 4 g + j
+    // is word j of lane group g's operand of k-step ks.  Channel ch (K: the
+    // offset digit) is word ch, except in a single-wave shape, where lane
+    // group g holds the digits of slots 4 mt + g and passes those of tiles
+    // 4 ks .. 4 ks + 3 on as they are (the offset follows the last tile).
+    constexpr int word_of(int ch) const {
+        if (W != 1) return ch;
+        const int s = ch < K ? ch : 4 * MT, t = s / 4;
+        return 16 * (t / 4) + 4 * (s % 4) + t % 4;
+    }
+    // Channel of a word: K for the offset, above K for words without one.
+    constexpr int channel_of(int word) const {
+        if (W != 1) return word;
+        const int s = 4 * (4 * (word / 16) + word % 4) + word / 4 % 4;
+        return s < K ? s : s == 4 * MT ? K : K + 1;
+    }
     // LDS words per element row of digits: KCH + 8 (a row stride of 56 words
     // at k = 33) measured 2% faster than KCH + 4, and KCH + 12 .. KCH + 36
     // slower, on the 16-lane digit reads and writes of the exchange
@@ -90,7 +128,7 @@ struct MLayout {
     constexpr size_t slotC() const { return tiles(); }                         // [W][MT][64] c_i
     constexpr size_t one() const { return slotC() + (size_t)W * MT * 64; }     // [W][MT][2][64] + [1]: M mod N
     constexpr size_t Nl() const { return one() + (size_t)W * MT * 2 * 64 + 1; }  // [K] limbs of N
-    constexpr size_t kscal() const { return Nl() + K; }                        // [4] N mod 2^32
+    constexpr size_t kscal() const { return Nl() + K; }                        // [4] N mod 2^32, the wide form's estimate constant
     // Whether a key of this shape may keep its B residues scaled (x R s_i
     // instead of x R, with s_i^2 = sigma_i c_i R^-1 mod m_i, sigma_i = +-1):
     // a product's quotient digit is then one REDC of the two operands.  The
@@ -98,12 +136,15 @@ struct MLayout {
     // per key, so only shapes whose tiles sit in registers or LDS (at most
     // 5 k-steps) take it.
     constexpr bool sq_ok() const { return KSTEPS() <= 5; }
+    // Whether the scaled form's second extension is the wide one; its estimate
+    // row is slot 4 MT - 2, before the redundant one.
+    constexpr bool wide() const { return W == 1 && K <= 4 * MT - 2; }
     // scaled form (sq_ok shapes): [W][MT][KSTEPS][64][4] second extension
-    // with output row t times s_t, then [W][MT][3][64] nu s, R s (the unit),
-    // (M mod N) R s (one)
+    // with output row t times s_t, then [W][MT][4][64] nu s, R s (the unit),
+    // (M mod N) R s (one), nu2 s (wide form)
     constexpr size_t a2s() const { return kscal() + 4; }
     constexpr size_t sqB() const { return a2s() + (sq_ok() ? tiles() : 0); }
-    constexpr size_t key_size() const { return sqB() + (sq_ok() ? (size_t)W * MT * 3 * 64 : 0); }
+    constexpr size_t key_size() const { return sqB() + (sq_ok() ? (size_t)W * MT * 4 * 64 : 0); }
     // entry table: per input limb [W*4*MT B slots | W*4*MT B' slots | redundant]
     constexpr size_t ecols() const { return (size_t)2 * W * 4 * MT + 1; }
 };

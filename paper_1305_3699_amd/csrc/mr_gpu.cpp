@@ -311,7 +311,7 @@ __global__ __launch_bounds__(kMrThreads) void mr_tables_kernel(MrTablesArgs A) {
         uint32_t words[4] = {0, 0, 0, 0};
         for (int j = 0; j < 16; j++) {
             const int kappa = 64 * ks + 16 * (l / 16) + j;
-            const int ch = kappa / 4, a = kappa % 4;
+            const int ch = sh.channel_of(kappa / 4), a = kappa % 4;
             int64_t V = 0;
             if (t < K && ch <= K && (ch < K || a == 0)) {
                 if (t < 0) {

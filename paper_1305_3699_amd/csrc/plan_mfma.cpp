@@ -1,6 +1,9 @@
 // Host-side tables of the matrix-core exponentiation kernel (plan_mfma.hpp).
 #include "plan_mfma.hpp"
 
+#include <cmath>
+#include <functional>
+
 
 namespace rnsrsa {
 
@@ -78,7 +81,8 @@ bool sqrt_mod(uint32_t a, uint32_t p, uint32_t *root) {
 // One matrix of A tiles [W][MT][KSTEPS][64 lanes][16 bytes] from a value
 // function V(slot channel t (-1: redundant), input channel i (K: offset slot), digit a).
 template <class F>
-void fill_tiles(const MfmaShape &sh, uint32_t *dst, F value) {
+void fill_tiles(const MfmaShape &sh, uint32_t *dst, F value, int extra = -2) {   // extra: a row that is no channel
+
     const int KS = sh.KSTEPS();
     for (int w = 0; w < sh.W; w++)
         for (int mt = 0; mt < sh.MT; mt++)
@@ -89,9 +93,9 @@ void fill_tiles(const MfmaShape &sh, uint32_t *dst, F value) {
                     const int t = mfma_slot_channel(sh, w, mt, g);
                     for (int j = 0; j < 16; j++) {
                         const int kappa = 64 * ks + 16 * (l / 16) + j;
-                        const int ch = kappa / 4, a = kappa % 4;
+                        const int ch = sh.channel_of(kappa / 4), a = kappa % 4;
                         int64_t V = 0;
-                        if (t < sh.K && ch <= sh.K && (ch < sh.K || a == 0)) V = value(t, ch, a);
+                        if ((t < sh.K || t == extra) && ch <= sh.K && (ch < sh.K || a == 0)) V = value(t, ch, a);
                         words[j / 4] |= (uint32_t)(uint8_t)digit(V, b) << (8 * (j % 4));
                     }
                     uint32_t *p = dst + ((((size_t)w * sh.MT + mt) * KS + ks) * 64 + l) * 4;
@@ -142,7 +146,7 @@ void fill_exit_tiles(const MfmaShape &sh, const BaseSet &bs, uint32_t *dst) {
                 const int r = 16 * st + l % 16;                            // output byte 4 s + b
                 for (int j = 0; j < 16; j++) {
                     const int kappa = 64 * ks + 16 * (l / 16) + j;
-                    const int ch = kappa / 4, a = kappa % 4;
+                    const int ch = sh.channel_of(kappa / 4), a = kappa % 4;
                     int8_t v = 0;
                     if (r < NB && (ch < K || (ch == K && a == 0)) && r >= a) v = D[(size_t)ch * NB + r - a];
                     words[j / 4] |= (uint32_t)(uint8_t)v << (8 * (j % 4));
@@ -150,6 +154,37 @@ void fill_exit_tiles(const MfmaShape &sh, const BaseSet &bs, uint32_t *dst) {
                 uint32_t *p = dst + (((size_t)st * KS + ks) * 64 + l) * 4;
                 for (int q = 0; q < 4; q++) p[q] = words[q];
             }
+}
+
+// The estimate row's weight of input t (see kEstScale).
+int64_t est_weight(uint32_t g, uint32_t m) { return (int64_t)(((uint64_t)g * kEstScale + m / 2) / m); }
+
+// Whether the wide form is exact for this modulus: values stay below c N, c =
+// 2K + 1 (q^ <= 2 K M: digits of B may exceed their prime by a little, so the
+// offset for sigma_i = -1 is 2 m_i M_i); the estimate of alpha is within half
+// of 2^32; step (iv)'s sum is positive and, but in the first tile (whose
+// reduction takes any sum below 2^64), small enough to leave a result below
+// 2^32 without a correction.
+bool wide_fits(const ModPlan &mp, const MLayout &ly, const std::vector<uint32_t> &nu2, long double gsum) {
+    const BaseSet &bs = *mp.base;
+    const int K = bs.K;
+    const Limbs c = bn_from_u64((uint64_t)2 * K + 1);
+    if (bn_cmp(bn_mul(bn_mul(c, c), mp.N), bs.M) > 0 || bn_cmp(bn_mul(c, mp.N), bs.Mp) >= 0) return false;
+    // estimate: weights rounded by 1/2 (times digits up to 128), the three
+    // lower digits left out (half a unit of 2^24 each), in units of 2^18
+    if ((long double)K * (0.5L * 128 + 0.51L * kEstScale) + 4 >= (long double)(1 << 13)) return false;
+    const long double amax = 4294967296.0L * gsum + 2;
+    if (amax >= 1099511627776.0L) return false;                        // 2^40
+    const uint64_t ah = (uint64_t)(amax / (1 << kWideShift)) + 1 + kWideOffset;
+    const uint64_t smax = mfma_sum_bound(K) + 0x80808080ull;
+    for (int i = 0; i < K; i++) {
+        if ((uint64_t)kWideOffset * nu2[i] <= smax) return false;
+        if (i < 4) continue;
+        const uint64_t m = bs.B[i];
+        const uint64_t hi = (1ull << kWideShift) + ah + (smax >> 32) + 2;   // bound of the sum over 2^32
+        if (m + hi >= 1ull << 32) return false;
+    }
+    return ly.MT >= 1;
 }
 
 // Per-lane slot table [W][MT][64] of f(channel) (channel -1 or >= K: junk).
@@ -200,6 +235,31 @@ MfmaTables make_mfma_tables(const ModPlan &mp, const MfmaShape &sh, bool with_ba
         else if (sqrt_mod(m - a, m, &sB[i])) sgn[i] = -1;
         else out.scaled = false;
     }
+    // The wide form (see kWideShift): weights g_t, and the root's sign that
+    // makes nu2 at least m / 2.
+    bool wide = out.scaled && ly.wide();
+    std::vector<uint32_t> g(K), nu2(K);
+    long double gsum = 0;                                              // sum of g_t / m'_t, so alpha < 2^32 gsum
+    if (wide) {
+        for (int t = 0; t < K; t++) {
+            const uint32_t m = bs.Bp[t];
+            std::vector<uint32_t> others;
+            for (int j = 0; j < K; j++)
+                if (j != t) others.push_back(bs.Bp[j]);
+            const uint32_t lam = mulmod32(pow2_32_mod(m), invmod32(prod_mod32(bs.B, m), m), m);   // R M^-1
+            g[t] = mulmod32(invmod32(prod_mod32(others, m), m), invmod32(lam, m), m);
+            gsum += (long double)g[t] / m;
+        }
+        for (int i = 0; i < K; i++) {
+            const uint32_t m = bs.B[i], mpm = prod_mod32(bs.Bp, m);
+            nu2[i] = mulmod32(mulmod32(mulmod32(m - mpm, pow2_64_mod(m), m), sB[i], m), 1u << kWideShift, m);
+            if (nu2[i] < m / 2) {
+                sB[i] = m - sB[i];
+                nu2[i] = m - nu2[i];
+            }
+        }
+        out.scaled = wide = wide_fits(mp, ly, nu2, gsum);
+    }
     if (!out.scaled) {
         std::fill(sgn.begin(), sgn.end(), 1);
         std::fill(sB.begin(), sB.end(), 1u);
@@ -224,16 +284,20 @@ MfmaTables make_mfma_tables(const ModPlan &mp, const MfmaShape &sh, bool with_ba
     // constants are sig_i C_i and the offset column adds
     // kDigitBias sum_i sig_i C_i + sum_{sig_i = -1} m_i C_i.
     const size_t KK = (size_t)(K + 1) * 4;
+    // A wide second extension takes weight wgt_i M_i in place of M_i, and its
+    // offset column also cancels add(t) (see kWideOffset).  off_sig: multiples of
+    // m_i M_i added for sig_i = -1.
     auto ext_values = [&](const std::vector<uint32_t> &in, const std::vector<uint32_t> &outm, auto scale,
-                          const std::vector<int> &sig) {
+                          const std::vector<int> &sig, uint32_t off_sig = 1, const std::vector<uint32_t> *wgt = nullptr,
+                          std::function<uint32_t(int)> sub = nullptr) {
         std::vector<int64_t> V((size_t)(K + 1) * KK, 0);
         uint32_t prod_lo = 1;
         for (uint32_t m : in) prod_lo *= m;
         uint32_t off_lo = 0;
         for (int i = 0; i < K; i++) {
-            const uint32_t mi_lo = prod_lo * inv2_32(in[i]);
+            const uint32_t mi_lo = prod_lo * inv2_32(in[i]) * (wgt ? (*wgt)[i] : 1u);
             const uint32_t ci_lo = sig[i] < 0 ? 0u - mi_lo : mi_lo;
-            off_lo += kDigitBias * ci_lo + (sig[i] < 0 ? in[i] * mi_lo : 0u);
+            off_lo += kDigitBias * ci_lo + (sig[i] < 0 ? off_sig * in[i] * mi_lo : 0u);
             for (int a = 0; a < 4; a++) V[(size_t)i * 4 + a] = balanced32(ci_lo << (8 * a));
         }
         V[(size_t)K * 4] = balanced32(off_lo);
@@ -243,14 +307,17 @@ MfmaTables make_mfma_tables(const ModPlan &mp, const MfmaShape &sh, bool with_ba
             uint64_t off = 0;
             int64_t *row = V.data() + (size_t)(t + 1) * KK;
             for (int i = 0; i < K; i++) {
-                const uint32_t mi = mulmod32(P, invmod32(in[i] % m, m), m);
+                uint32_t mi = mulmod32(P, invmod32(in[i] % m, m), m);
+                if (wgt) mi = mulmod32(mi, (*wgt)[i] % m, m);
                 const uint32_t ci = sig[i] < 0 && mi ? m - mi : mi;
                 off = (off + mulmod32(kDigitBias % m, ci, m)) % m;
-                if (sig[i] < 0) off = (off + mulmod32(in[i] % m, mi, m)) % m;
+                if (sig[i] < 0) off = (off + mulmod32(mulmod32(off_sig, in[i] % m, m), mi, m)) % m;
                 for (int a = 0; a < 4; a++)
                     row[(size_t)i * 4 + a] = balanced(mulmod32(mulmod32(ci, pow2_mod(8 * a, m), m), f, m), m);
             }
-            row[(size_t)K * 4] = balanced(mulmod32((uint32_t)off, f, m), m);
+            uint32_t o = mulmod32((uint32_t)off, f, m);
+            if (sub) o = (uint32_t)(((uint64_t)o + m - sub(t) % m) % m);
+            row[(size_t)K * 4] = balanced(o, m);
         }
         return V;
     };
@@ -261,7 +328,7 @@ MfmaTables make_mfma_tables(const ModPlan &mp, const MfmaShape &sh, bool with_ba
         uint32_t minv = invmod32(prod_mod32(bs.B, m), m);
         G[t] = mulmod32(mulmod32(bn_mod_word(N, m), pow2_64_mod(m), m), mulmod32(minv, minv, m), m);
     }
-    const std::vector<int64_t> V1 = ext_values(bs.B, bs.Bp, [&](int t) { return G[t]; }, sgn);
+    const std::vector<int64_t> V1 = ext_values(bs.B, bs.Bp, [&](int t) { return G[t]; }, sgn, wide ? 2u : 1u);
     fill_tiles(sh, out.key.data() + ly.a1(),
                [&](int t, int i, int a) -> int64_t { return V1[(size_t)(t + 1) * KK + (size_t)i * 4 + a]; });
     auto okc = [&](int t) { return t >= 0 && t < K; };
@@ -332,12 +399,27 @@ MfmaTables make_mfma_tables(const ModPlan &mp, const MfmaShape &sh, bool with_ba
     for (int l = 0; l < K && l < (int)N.size(); l++) out.key[ly.Nl() + l] = N[l];
     out.key[ly.kscal() + 0] = bn_low(N);
     if (out.scaled) {
-        // second extension with row t scaled by s_t (R^2 s_t mod m_t)
+        // second extension with row t scaled by s_t (R^2 s_t mod m_t); the
+        // wide form's with weights and its estimate row
         const std::vector<int64_t> V2s = ext_values(
-            bs.Bp, bs.B, [&](int t) { return mulmod32(pow2_64_mod(bs.B[t]), sB[t], bs.B[t]); }, plus);
+            bs.Bp, bs.B, [&](int t) { return mulmod32(pow2_64_mod(bs.B[t]), sB[t], bs.B[t]); }, plus, 1,
+            wide ? &g : nullptr,
+            wide ? std::function<uint32_t(int)>([&](int t) { return mulmod32(kWideOffset, nu2[t], bs.B[t]); }) : nullptr);
+        const int est = 4 * sh.MT - 2;
         fill_tiles(sh, out.key.data() + ly.a2s(),
-                   [&](int t, int j, int a) -> int64_t { return V2s[(size_t)(t + 1) * KK + (size_t)j * 4 + a]; });
-        const size_t fq = (size_t)3 * 64;      // [W][MT][3][64]
+                   [&](int t, int j, int a) -> int64_t {
+                       if (wide && t == est) return j < K && a == 3 ? est_weight(g[j], bs.Bp[j]) : 0;
+                       return V2s[(size_t)(t + 1) * KK + (size_t)j * 4 + a];
+                   },
+                   wide ? est : -2);
+        if (wide) {
+            // the digits' bias, half a unit of the estimate's rounding, the offset
+            const long double bias = (long double)kDigitBias / (1 << 24) * kEstScale * gsum;
+            out.key[ly.kscal() + 1] = (uint32_t)(int32_t)llroundl(bias) + (1u << 13) +
+                                      ((uint32_t)kWideOffset >> (32 - kWideShift) << 14);
+        }
+        const size_t fq = (size_t)4 * 64;      // [W][MT][4][64]
+        fill_slots(sh, out.key.data() + ly.sqB() + 3 * 64, fq, [&](int t) -> uint32_t { return wide && okc(t) ? nu2[t] : 0; });
         fill_slots(sh, out.key.data() + ly.sqB() + 0 * 64, fq, [&](int t) -> uint32_t {
             if (!okc(t)) return 0;
             const uint32_t m = bs.B[t], mpm = prod_mod32(bs.Bp, m);

@@ -245,6 +245,40 @@ def test_scaled_and_unscaled_b_residues(bits):
         assert np.array_equal(_host(o), want)
 
 
+@pytest.mark.parametrize("bits,counts,opts", [
+    (1024, [16384], {}), (1024, [16385], {}), (1024, [16403, 1, 65], {}), (1024, [16320, 33, 16], {"group": 32}),
+    (1024, [5, 17, 47], {}), (1024, [16385, 3], {"unscaled": True}), (1024, [4001], {"unscaled": True}),
+    (512, [16387, 1, 64], {}), (512, [17, 2], {"group": 32})])
+def test_single_wave_and_split_launches(bits, counts, opts):
+    """One wave per tile against three (the launch rule's line is one tile of
+    16 elements per SIMD, 16,384 elements on 256 compute units), jobs that end
+    inside a workgroup's four tiles, both tiles and both residue forms:
+    per-element exponents in the first job, shared ones in the others; every
+    output equals the channel engine's, sampled rows the oracle's."""
+    from paper_1305_3699_amd import ENGINE_CHANNEL, modexp_jobs
+    rng = random.Random(bits + sum(counts))
+    L = bits // 32
+    jobs, refs, mods = [], [], []
+    for i, n in enumerate(counts):
+        N = rng.getrandbits(bits) | (1 << (bits - 1)) | 1
+        bases = np.frombuffer(rng.randbytes(4 * n * L), dtype=np.uint32).reshape(n, L).copy()
+        bases[:, -1] &= 0x7FFFFFFF
+        bases[-1] = gen.to_limbs([[N - 1, 0, 1][i % 3]], L)[0]
+        e = (np.frombuffer(rng.randbytes(8 * n), dtype=np.uint32).reshape(n, 2).copy() if i == 0
+             else gen.to_limbs(rng.getrandbits(70), 3)[0])
+        if i == 0:
+            e[:, 1] &= 0xFF
+        jobs.append((_ctx(N, L, **opts), _dev(bases), _dev(e)))
+        refs.append(_run_modexp(_ctx(N, L, engine=ENGINE_CHANNEL), bases, e))
+        mods.append((N, bases, e))
+    outs = [_host(o) for o in modexp_jobs(jobs)] if len(jobs) > 1 else [_host(jobs[0][0].modexp(*jobs[0][1:]))]
+    for got, ref, (N, bases, e) in zip(outs, refs, mods):
+        assert np.array_equal(got, ref)
+        idx = sorted({0, len(bases) - 1, len(bases) // 2})
+        assert np.array_equal(got[idx], oracle.modexp_batch(bases[idx], e[idx] if e.ndim == 2 else e,
+                                                            gen.to_limbs(N, L)[0]))
+
+
 @pytest.mark.parametrize("bits,k", [(64, 3), (128, 5)])
 def test_scaled_b_residues_primes_1_mod_4(bits, k):
     """The kernel's scaled form on an explicit base whose B primes are all
