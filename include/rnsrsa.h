@@ -77,9 +77,11 @@ enum rns_prime_range {
  *               meets the bounds below).  Built sizes: 2, 3, 5, 9, 17, 33, 49,
  *               65, 66, 97, 129, 257 (moduli up to 8192 bits) and 513 (up to
  *               16384 bits; matrix-core engine only).
- *   window      exponent window width w in 1..6 (0 = 5).  The exponent loop
- *               precomputes 2^w table entries and does w squarings plus one
- *               multiplication per w-bit digit.
+ *   window      exponent window width w in 1..6 (0 = 5; the matrix-core
+ *               engine then takes a smaller width where the exponent's length
+ *               makes that the fewest products).  The exponent loop precomputes
+ *               2^w table entries and does w squarings plus one multiplication
+ *               per w-bit digit.
  *   waves       wavefronts per workgroup, which split the channels of 64
  *               messages (0 = default for k; needs an explicit k).
  *   prime_range rns_prime_range; prime_seed seeds the deterministic draw.

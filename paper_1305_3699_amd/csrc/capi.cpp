@@ -38,7 +38,7 @@ int hip_fail(hipError_t e, const char *what) {
     return fail(RNS_EDEVICE, std::string(what) + ": " + hipGetErrorString(e));
 }
 
-int window_or_default(const rns_opts *o) { return (o && o->window) ? o->window : 5; }
+constexpr int kDefaultWindow = 5;
 
 PlanOptions plan_options(const rns_opts *o) {
     PlanOptions p;
@@ -185,11 +185,13 @@ int choose_engine(const BaseSet &bs, int requested, int group, int *engine) {
     return RNS_OK;
 }
 
+// window 0: the kernel chooses, up to kDefaultWindow.
 int ctx_from_plan(ModPlan &&mp, int window, int engine_req, int group, rns_ctx **out, bool allow_scaled = true) {
     std::unique_ptr<rns_ctx> c(new (std::nothrow) rns_ctx);
     if (!c) return fail(RNS_ENOMEM, "out of host memory");
     c->plan = std::move(mp);
-    c->window = window;
+    c->window = window ? window : kDefaultWindow;
+    c->window_max = window == 0;
     int rc = choose_engine(*c->plan.base, engine_req, group, &c->engine);
     if (rc) return rc;
     hipError_t e = hipGetDevice(&c->device);
@@ -353,6 +355,7 @@ int run_modexp(const rns_ctx *c0, const rns_ctx *c1, const uint32_t *E0, const u
             J.exp_limbs = exp_limbs;
             J.exp_stride = exp_stride;
             J.window = c0->window;
+            J.window_max = c0->window_max;
             J.tile0 = j * per_job;
             J.group0 = j * sh.groups(per_job);
             J.tile_elems = te;
@@ -446,7 +449,7 @@ int make_context(const Limbs &N, int L, rns_ctx **out) {
     std::string err;
     int rc = make_modplan(N, L, PlanOptions{}, mp, err);
     if (rc) return fail(rc, err);
-    return ctx_from_plan(std::move(mp), 5, 0, 0, out);
+    return ctx_from_plan(std::move(mp), 0, 0, 0, out);
 }
 
 }  // namespace api
@@ -468,7 +471,7 @@ int rns_setup(const uint32_t *mod, size_t mod_limbs, const rns_opts *opts, rns_c
         std::string err;
         rc = make_modplan(limbs_of(mod, mod_limbs), (int)mod_limbs, plan_options(opts), mp, err);
         if (rc) return fail(rc, err);
-        rc = ctx_from_plan(std::move(mp), window_or_default(opts), opts ? opts->engine : 0, opts ? opts->group : 0,
+        rc = ctx_from_plan(std::move(mp), opts ? opts->window : 0, opts ? opts->engine : 0, opts ? opts->group : 0,
                            out, !(opts && opts->unscaled));
         if (rc) return rc;
     } catch (const std::bad_alloc &) {
@@ -584,6 +587,7 @@ int rns_modexp_jobs(const rns_job *jobs, size_t njobs, void *hip_stream) {
             J.j.exp_limbs = (int)j.exp_limbs;
             J.j.exp_stride = (int)j.exp_stride;
             J.j.window = c->window;
+            J.j.window_max = c->window_max;
             J.cost = 32 * j.exp_limbs;   // the exponents stay on the device: their length orders the tiles
             g.jobs.push_back(J);
         }
@@ -665,7 +669,7 @@ int rsa_key_load(const uint32_t *n, size_t n_limbs, const uint32_t *e, size_t e_
         key->n_limbs = n_limbs;
         key->e_limbs = e_limbs;
         key->half = half_limbs;
-        const int window = window_or_default(opts);
+        const int window = opts ? opts->window : 0;
         const int engine = opts ? opts->engine : 0;
         const int group = opts ? opts->group : 0;
         const bool scaled = !(opts && opts->unscaled);
@@ -846,7 +850,7 @@ int rns_plan_create(const uint32_t *mod, size_t mod_limbs, const rns_opts *opts,
         std::string err;
         rc = make_modplan(limbs_of(mod, mod_limbs), (int)mod_limbs, plan_options(opts), p->plan, err);
         if (rc) return fail(rc, err);
-        p->window = window_or_default(opts);
+        p->window = opts && opts->window ? opts->window : kDefaultWindow;
         const int group = opts ? opts->group : 0;
         if ((rc = choose_engine(*p->plan.base, opts ? opts->engine : 0, group, &p->engine))) return rc;
         if (p->engine == RNS_ENGINE_MATRIX) {

@@ -51,6 +51,7 @@ WindowCosts window_costs(const std::vector<uint32_t> &e);
 struct rns_ctx {
     rnsrsa::ModPlan plan;
     int window = 5;
+    bool window_max = false;      // no width was asked for: window is the widest the kernel may choose
     int device = 0;
     int engine = RNS_ENGINE_CHANNEL;
     uint32_t *d_base = nullptr;  // shared, owned by the process-wide cache

@@ -83,6 +83,7 @@ struct MJob {
     int tile0;
     int group0;          // first workgroup (MLayout::groups; split launches: tile0)
     int tile_elems;
+    int window_max;      // window is the widest allowed, not the width (mexp_width)
 };
 
 // A launch of the matrix-core kernel: njobs jobs of one shape, from the

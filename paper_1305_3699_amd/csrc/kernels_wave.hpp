@@ -470,7 +470,7 @@ __device__ __forceinline__ void wave_exponent(const MJob &J, int e0, E &w, int t
         mstate_one<K, 1, MT, SQ>(mk, tile0, lane, one);
         mstate_store<M, NT>(tw, one, has_r);                     // T[0] = M mod N
     }
-    const int wd = J.window;
+    const int wd = mexp_width(ex, J);
     const bool shared_exp = J.exp_stride == 0;
     const int nd = (32 * J.exp_limbs + wd - 1) / wd;
     auto dig_of = [&](int i) {
@@ -518,7 +518,7 @@ __device__ __forceinline__ void wave_exponent(const MJob &J, int e0, E &w, int t
                 bitpos = mexp_top_bit(ex, J.exp_limbs);
                 int low = 0;
                 const uint32_t t = bitpos < 0 ? 0u : mexp_window(ex, J.exp_limbs, bitpos, wd, &low);
-                mstate_load<M, NT>(tw + (size_t)t * estride, a, has_r);   // e = 0: the result is 1
+                if (t != 1 || wd > 1) mstate_load<M, NT>(tw + (size_t)t * estride, a, has_r);   // e = 0: the result is 1
                 bitpos = low - 1;
             } else {
                 mstate_load_elems<M, NT>(tw, estride, dig_of(0), a, has_r);

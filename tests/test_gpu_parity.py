@@ -279,6 +279,31 @@ def test_single_wave_and_split_launches(bits, counts, opts):
                                                             gen.to_limbs(N, L)[0]))
 
 
+@pytest.mark.parametrize("bits", [96, 1024, 2048])
+@pytest.mark.parametrize("limbs", [1, 2, 3])
+def test_window_width_by_exponent(bits, limbs):
+    """The kernel's choice of the window width (no width asked for): exponents
+    with few, many and alternating bits around the lengths where the width
+    changes, with leading zero limbs, shared and per element, on kernels of
+    one, three and six waves; every output equals Python's pow."""
+    rng = random.Random(bits + limbs)
+    N = rng.getrandbits(bits) | (1 << (bits - 1)) | 1
+    ctx = _ctx(N, bits // 32)
+    assert ctx.info["window"] == 5
+    vals = [rng.getrandbits(bits - 1) for _ in range(18)] + [0, 1]
+    bases = gen.to_limbs(vals, bits // 32)
+    exps = {0, 1, 2, 3, 5, 65537, (1 << 32 * limbs) - 1, 1 << (32 * limbs - 1)}
+    exps |= {rng.getrandbits(n) | 1 << (n - 1) for n in (4, 9, 31, 32, 33, 63, 64, 65, 90) if n <= 32 * limbs}
+    exps |= {int("10" * 16 * limbs, 2), (1 << 32 * limbs) // 3 | 1}
+    exps = sorted(e for e in exps if e < 1 << 32 * limbs)
+    for e in exps:
+        got = _run_modexp(ctx, bases, gen.to_limbs(e, limbs)[0])
+        assert np.array_equal(got, gen.to_limbs([pow(v, e, N) for v in vals], bits // 32)), e
+    each = [exps[i % len(exps)] for i in range(len(vals))]
+    got = _run_modexp(ctx, bases, gen.to_limbs(each, limbs))
+    assert np.array_equal(got, gen.to_limbs([pow(v, e, N) for v, e in zip(vals, each)], bits // 32))
+
+
 @pytest.mark.parametrize("bits,k", [(64, 3), (128, 5)])
 def test_scaled_b_residues_primes_1_mod_4(bits, k):
     """The kernel's scaled form on an explicit base whose B primes are all
