@@ -57,7 +57,7 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=" + ARCH,
 ILP_SCHED_K = {33, 65, 66, 97, 129, 257, 513}
 ILP_SCHED = ["-mllvm", "-amdgpu-sched-strategy=iterative-ilp"]
 HOST_SOURCES = ["capi.cpp", "noalloc.cpp", "mr_gpu.cpp", "batch.cpp", "jobs.cpp", "server.cpp", "keygen.cpp", "plan.cpp", "plan_mfma.cpp", "emul.cpp",
-                "emul_mfma.cpp", "kernels_dispatch.cpp", "verify.cpp", "probe.cpp", "range.cpp"]
+                "emul_mfma.cpp", "kernels_dispatch.cpp", "verify.cpp", "probe.cpp", "range.cpp", "garner.cpp"]
 
 
 def shapes() -> list:

@@ -420,12 +420,12 @@ int crt_halves(const rsa_key *key, const uint32_t *c, uint32_t *mpq, size_t batc
                       c, (int)key->n_limbs, key->d_dp, key->d_dq, L, 0, mpq, mpq + L, 2 * L, batch, s, table, spread);
 }
 
-// Garner recombination over the p-modulus tables.
 GarnerLaunch garner_launch_of(const rsa_key *key, const uint32_t *mpq, uint32_t *m, size_t batch) {
     GarnerLaunch g{};
     g.bc = key->p->d_base;
     g.mc = key->p->d_mod;
     g.E = key->d_gentry;
+    g.lk = key->d_glimbs;
     g.qlimbs = key->d_qlimbs;
     g.in = mpq;
     g.out = m;
@@ -438,7 +438,8 @@ GarnerLaunch garner_launch_of(const rsa_key *key, const uint32_t *mpq, uint32_t 
 
 int crt_combine(const rsa_key *key, const uint32_t *mpq, uint32_t *m, size_t batch, hipStream_t s) {
     const BaseSet &bs = *key->p->plan.base;
-    hipError_t e = launch_garner(bs.K, bs.W, garner_launch_of(key, mpq, m, batch), s);
+    const GarnerLaunch g = garner_launch_of(key, mpq, m, batch);
+    hipError_t e = g.lk ? launch_garner_limbs(g, s) : launch_garner(bs.K, bs.W, g, s);
     if (e != hipSuccess) return hip_fail(e, "garner launch");
     return RNS_OK;
 }
@@ -727,10 +728,23 @@ int rsa_key_load(const uint32_t *n, size_t n_limbs, const uint32_t *e, size_t e_
             std::vector<uint32_t> Ep = make_entry_table(pp, Yp, L), Eq = make_entry_table(qp, Yq, L);
             Ep.resize((size_t)n_limbs * Layout{bs->K, bs->KP}.ecols());
             Eq.resize((size_t)n_limbs * Layout{bs->K, bs->KP}.ecols());
-            // Garner: Z = m_p A + m_q (p - A), A = qinv M mod p
-            Limbs A = bn_mod(bn_mul(limbs_of(qinv, half_limbs), pp.Mmod), P);
-            Limbs Bv = bn_is_zero(A) ? Limbs{} : bn_sub(P, A);
-            std::vector<uint32_t> Eg = make_entry_table(pp, {A, Bv}, L);
+            // Garner in limbs: a Montgomery product by qinv 2^(32 L) mod p, which needs
+            // an odd p (at half the sizes of every shape with a Garner kernel).  Else
+            // in the RNS: Z = m_p A + m_q (p - A), A = qinv M mod p.
+            std::vector<uint32_t> Eg, lk;
+            if ((P[0] & 1) && L <= kGarnerLimbs && channel_kernel(bs->K, bs->W)) {
+                const Limbs A = bn_mod(bn_shl(limbs_of(qinv, half_limbs), 32u * L), P);
+                const Limbs D = bn_sub(P, A);
+                for (const Limbs *v : std::initializer_list<const Limbs *>{&P, &Q, &A, &D})
+                    for (int l = 0; l < L; l++) lk.push_back(l < (int)v->size() ? (*v)[l] : 0u);
+                uint32_t inv = P[0];                             // P[0]^-1 mod 2^3, doubled four times
+                for (int i = 0; i < 4; i++) inv *= 2u - P[0] * inv;
+                lk.push_back(0u - inv);
+            } else {
+                const Limbs A = bn_mod(bn_mul(limbs_of(qinv, half_limbs), pp.Mmod), P);
+                const Limbs Bv = bn_is_zero(A) ? Limbs{} : bn_sub(P, A);
+                Eg = make_entry_table(pp, {A, Bv}, L);
+            }
             std::vector<uint32_t> Epm, Eqm;
             MfmaShape msh;
             const bool mfma = mfma_shape_for(bs->K, msh, group);
@@ -748,7 +762,8 @@ int rsa_key_load(const uint32_t *n, size_t n_limbs, const uint32_t *e, size_t e_
                 if ((rc = upload(Epm, &key->d_mcentry_p))) return rc;
                 if ((rc = upload(Eqm, &key->d_mcentry_q))) return rc;
             }
-            if ((rc = upload(Eg, &key->d_gentry))) return rc;
+            if (!Eg.empty() && (rc = upload(Eg, &key->d_gentry))) return rc;
+            if (!lk.empty() && (rc = upload(lk, &key->d_glimbs))) return rc;
             key->h_dp.assign(dp, dp + half_limbs);
             key->h_dq.assign(dq, dq + half_limbs);
             key->wc_dp = window_costs(key->h_dp);

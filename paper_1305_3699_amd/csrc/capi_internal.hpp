@@ -91,13 +91,14 @@ struct rsa_key {
     uint32_t *d_dp = nullptr, *d_dq = nullptr;
     uint32_t *d_centry_p = nullptr, *d_centry_q = nullptr;  // entry tables for n_limbs-limb inputs
     uint32_t *d_mcentry_p = nullptr, *d_mcentry_q = nullptr;  // the same for the matrix-core engine
-    uint32_t *d_gentry = nullptr;                           // Garner entry table (p-modulus)
+    uint32_t *d_glimbs = nullptr;                           // Garner constants in limbs (GarnerLaunch::lk), odd p
+    uint32_t *d_gentry = nullptr;                           // Garner entry table (p-modulus), even p
     uint32_t *d_qlimbs = nullptr;
     ~rsa_key() {
         delete n;
         delete p;
         delete q;
-        for (uint32_t *x : {d_n, d_e, d_d, d_dp, d_dq, d_centry_p, d_centry_q, d_mcentry_p, d_mcentry_q, d_gentry,
+        for (uint32_t *x : {d_n, d_e, d_d, d_dp, d_dq, d_centry_p, d_centry_q, d_mcentry_p, d_mcentry_q, d_gentry, d_glimbs,
                             d_qlimbs})
             if (x) hipFree(x);
         if (d_status) hipFree(d_status);

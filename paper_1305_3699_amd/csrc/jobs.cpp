@@ -231,17 +231,19 @@ hipError_t launch_group(const JobGroup &g, const MJob *d_jobs, uint32_t *table, 
 }
 
 std::vector<GarnerGroup> garner_groups(const JobPlan &p) {
-    std::map<std::pair<int, int>, GarnerGroup> m;
+    std::map<std::tuple<int, int, bool>, GarnerGroup> m;
     for (const GarnerJob &gj : p.garners) {
         if (gj.count == 0) continue;
         const BaseSet &bs = *gj.key->p->plan.base;
-        GarnerGroup &g = m[std::make_pair(bs.K, bs.W)];
+        const bool limbs = gj.key->d_glimbs != nullptr;
+        GarnerGroup &g = m[std::make_tuple(bs.K, bs.W, limbs)];
         g.K = bs.K;
         g.W = bs.W;
+        g.limbs = limbs;
         GJob J{};
         J.g = garner_launch_of(gj.key, gj.mpq, gj.out, gj.count);
         J.tile0 = g.tiles;
-        g.tiles += (int)((gj.count + 63) / 64);
+        g.tiles += limbs ? garner_limbs_tiles(gj.count) : (int)((gj.count + 63) / 64);
         g.jobs.push_back(J);
     }
     std::vector<GarnerGroup> out;
@@ -250,6 +252,7 @@ std::vector<GarnerGroup> garner_groups(const JobPlan &p) {
 }
 
 hipError_t launch_garner_group(const GarnerGroup &g, const GJob *d_jobs, hipStream_t s) {
+    if (g.limbs) return launch_garner_limbs_jobs(g.K - 1, d_jobs, (int)g.jobs.size(), g.tiles, s);   // L < K
     return launch_garner_jobs(g.K, g.W, d_jobs, (int)g.jobs.size(), g.tiles, s);
 }
 

@@ -111,6 +111,7 @@ int launch_plain_and_garner(const JobPlan &p, hipStream_t s, bool plain, bool ga
 // workgroups serve every key's step of that shape at once.
 struct GarnerGroup {
     int K = 0, W = 0;
+    bool limbs = false;   // recombined in limbs
     std::vector<GJob> jobs;
     int tiles = 0;
 };

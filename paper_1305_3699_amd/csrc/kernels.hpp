@@ -38,13 +38,14 @@ struct ModexpLaunch {
     int njobs;
 };
 
-// Garner recombination m = m_q + q * ((m_p - m_q) qinv mod p) over the
-// p-modulus tables: in = [m_p | m_q] (2*L limbs per element).
+// Garner recombination m = m_q + q * ((m_p - m_q) qinv mod p): in = [m_p | m_q]
+// (2*L limbs per element).  In limbs (lk set) or over the p-modulus tables.
 struct GarnerLaunch {
     const uint32_t *bc;
     const uint32_t *mc;    // p-modulus table
     const uint32_t *E;     // entry table mapping (m_p, m_q) to (m_p - m_q) qinv M
     const uint32_t *qlimbs;  // L limbs of q
+    const uint32_t *lk;      // limbs of p, q, B = qinv 2^(32 L) mod p and p - B, then -p^-1 mod 2^32
     const uint32_t *in;
     uint32_t *out;
     int L;          // half limbs
@@ -54,8 +55,8 @@ struct GarnerLaunch {
 };
 
 // One Garner step of a grouped launch (several keys of one base shape):
-// the fields of GarnerLaunch plus the job's first workgroup (64 elements
-// each) in the launch.  Jobs are ordered by tile0.
+// the fields of GarnerLaunch plus the job's first workgroup in the launch (64 elements
+// each, 4 in limbs).  Jobs are ordered by tile0.
 struct GJob {
     GarnerLaunch g;
     int tile0;
@@ -124,6 +125,11 @@ hipError_t launch_modexp_mfma(const MLayout &shape, const ModexpMfmaLaunch &a, h
 hipError_t launch_montmul_mfma(const MLayout &shape, const MontMulMfmaLaunch &a, hipStream_t s);
 hipError_t launch_modexp(int K, int W, const ModexpLaunch &a, hipStream_t s);
 hipError_t launch_garner(int K, int W, const GarnerLaunch &a, hipStream_t s);
+// The same in limbs (odd p, up to kGarnerLimbs half limbs; garner.cpp).
+constexpr int kGarnerLimbs = 256;
+int garner_limbs_tiles(size_t elements);
+hipError_t launch_garner_limbs(const GarnerLaunch &a, hipStream_t s);
+hipError_t launch_garner_limbs_jobs(int max_limbs, const GJob *jobs, int njobs, int tiles, hipStream_t s);
 // Grouped Garner steps: `tiles` workgroups over njobs jobs (device table).
 hipError_t launch_garner_jobs(int K, int W, const GJob *jobs, int njobs, int tiles, hipStream_t s);
 hipError_t launch_montmul(int K, int W, const MontMulLaunch &a, hipStream_t s);

@@ -25,10 +25,10 @@ __device__ __forceinline__ uint32_t lane_up(uint32_t v, uint32_t first) {
     return (uint32_t)__builtin_amdgcn_update_dpp((int)first, (int)v, 0x138 /* wave_shr:1 */, 0xF, 0xF, false);
 }
 
-// Limbs of sum_l t_l 2^(32 l), every t_l below 2^63; the carry out of the top
-// lane is dropped.
+// Limbs of sum_l t_l 2^(32 l), every t_l below 2^63; returns the carry out of the
+// top lane.
 template <int C>
-__device__ __forceinline__ void limbs_of_sums(const uint64_t (&t)[C], uint32_t (&v)[C], int lane) {
+__device__ __forceinline__ uint32_t limbs_of_sums(const uint64_t (&t)[C], uint32_t (&v)[C], int lane) {
     uint32_t below = 0, cin = 0;
 #pragma unroll
     for (int c = 0; c < C; c++) {
@@ -38,11 +38,12 @@ __device__ __forceinline__ void limbs_of_sums(const uint64_t (&t)[C], uint32_t (
         const uint64_t cm = limb_carries(__ballot(u < lo), __ballot(u == 0xFFFFFFFFu), cin);
         v[c] = u + lane_bit(cm, lane);
     }
+    return below + cin;
 }
 
-// v <- v - n when v >= n.
+// v <- v - n when v >= n; over: a carry out of v's top lane that counts to v.
 template <int C>
-__device__ __forceinline__ void limbs_reduce_once(uint32_t (&v)[C], const uint32_t (&n)[C], int lane) {
+__device__ __forceinline__ void limbs_reduce_once(uint32_t (&v)[C], const uint32_t (&n)[C], int lane, uint32_t over = 0) {
     uint32_t d[C], cin = 1;                                  // v - n = v + ~n + 1
 #pragma unroll
     for (int c = 0; c < C; c++) {
@@ -50,7 +51,7 @@ __device__ __forceinline__ void limbs_reduce_once(uint32_t (&v)[C], const uint32
         const uint64_t cm = limb_carries(__ballot(u < v[c]), __ballot(u == 0xFFFFFFFFu), cin);
         d[c] = u + lane_bit(cm, lane);
     }
-    if (cin) {                                               // no borrow
+    if (cin | over) {                                        // no borrow
 #pragma unroll
         for (int c = 0; c < C; c++) v[c] = d[c];
     }

@@ -304,6 +304,47 @@ def test_window_width_by_exponent(bits, limbs):
     assert np.array_equal(got, gen.to_limbs([pow(v, e, N) for v, e in zip(vals, each)], bits // 32))
 
 
+@pytest.mark.parametrize("half,pbits,count", [
+    (1, 5, 9), (1, 32, 4), (2, 33, 3), (31, 31 * 32, 5), (32, 1000, 17), (33, 33 * 32, 1), (63, 63 * 32 - 1, 6),
+    (64, 64 * 32, 7), (65, 65 * 32, 2), (128, 128 * 32, 5), (129, 129 * 32, 3), (256, 256 * 32, 4)])
+def test_garner_in_limbs(half, pbits, count):
+    """rsa_crt_combine around the 64-limb words of a lane, with p above and
+    below q, for residues in and out of their ranges (rows of ones, zeros,
+    m_p below m_q) and against Python's integers; a grouped launch recombines
+    two keys with different half sizes like two single calls; p = 2 takes the
+    RNS form."""
+    from paper_1305_3699_amd import OP_DECRYPT, RsaBatch, RsaKey
+    rng = random.Random(half * 7 + pbits)
+    for top in ("p", "q"):
+        big = rng.getrandbits(32 * half) | 1 << (32 * half - 1) | 1
+        small = rng.getrandbits(pbits) | 1 << (pbits - 1) | 1
+        p, q = (big, small) if top == "p" else (small, big)
+        qinv = rng.randrange(p)
+        rk = RsaKey(p * q, 3, None, p, q, 3, 3, qinv)
+        w, R = 32 * half, 1 << (32 * half)
+        rows = [(R - 1, R - 1), (0, R - 1), (R - 1, 0), (0, 0), (p - 1, 0), (0, q - 1)]
+        rows = (rows + [(rng.randrange(R), rng.randrange(R)) for _ in range(count)])[-max(count, 3):]
+        out = _host(rk.crt_combine(_dev(gen.to_limbs([a | b << w for a, b in rows], 2 * half))))
+        want = [(b + (a - b) * qinv % p * q) % (1 << (32 * rk.L)) for a, b in rows]
+        assert np.array_equal(out, gen.to_limbs(want, rk.L)), top
+    other = RsaKey(p * 3, 3, None, p, 3, 3, 1, 1)
+    even = RsaKey(2 * q, 3, None, 2, q, 1, 3, 1)
+    mpq = [(0, q - 1), (1, 5), (1, 0)]
+    got = _host(even.crt_combine(_dev(gen.to_limbs([a | b << 32 * even._half for a, b in mpq], 2 * even._half))))
+    assert np.array_equal(got, gen.to_limbs([b + (a - b) % 2 * q for a, b in mpq], even.L))
+    ops, want = [], []
+    for k, n in ((rk, 5), (other, 1), (even, 2)):
+        c = _dev(gen.to_limbs([rng.randrange(k.n) for _ in range(n)], k.L))
+        ops.append((k, OP_DECRYPT, c, torch.zeros_like(c)))
+        want.append(_host(k.decrypt(c)))
+    b = RsaBatch(ops)
+    b.run()
+    torch.cuda.synchronize()
+    for o, w in zip(ops, want):
+        assert np.array_equal(_host(o[3]), w)
+    b.close()
+
+
 @pytest.mark.parametrize("bits,k", [(64, 3), (128, 5)])
 def test_scaled_b_residues_primes_1_mod_4(bits, k):
     """The kernel's scaled form on an explicit base whose B primes are all
