@@ -18,29 +18,6 @@ namespace {
 
 constexpr int kGarnerWaves = 4;
 
-// Word of the lane above (lane 63: `last`).
-__device__ __forceinline__ uint32_t lane_down(uint32_t v, uint32_t last) {
-    return (uint32_t)__builtin_amdgcn_update_dpp((int)last, (int)v, 0x130 /* wave_shl:1 */, 0xF, 0xF, false);
-}
-
-template <int C>
-__device__ __forceinline__ uint32_t low_limb(const uint64_t (&u)[C]) {
-    return (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u[0]);
-}
-
-// One step's shift: t <- (v's low words + 2^32 (u's high words + v's, + t's))
-// / 2^32, v's limb 0 dropped.  t stays below 3 2^32.
-template <int C, bool TWO>
-__device__ __forceinline__ void shift_step(const uint64_t (&u)[C], const uint64_t (&v)[C], uint64_t (&t)[C]) {
-#pragma unroll
-    for (int c = 0; c < C; c++) {
-        uint32_t last = 0;
-        if (c + 1 < C) last = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v[c + 1 < C ? c + 1 : 0]);
-        const uint32_t dn = lane_down((uint32_t)v[c], last);
-        t[c] = (uint64_t)dn + (uint32_t)(u[c] >> 32) + (TWO ? (uint32_t)(v[c] >> 32) : 0u) + (uint32_t)(t[c] >> 32);
-    }
-}
-
 template <int C>
 __device__ __forceinline__ void garner_element(const GarnerLaunch &G, int e, int lane) {
     const int L = G.L;
@@ -57,7 +34,6 @@ __device__ __forceinline__ void garner_element(const GarnerLaunch &G, int e, int
         q[c] = in ? lk[L + l] : 0u;
         B[c] = in ? lk[2 * L + l] : 0u;
     }
-    const uint32_t ninv = lk[4 * L];
     // a <- m_p - m_q mod 2^(32 L); no borrow leaves the carry 1 (the lanes from L
     // on hold ones and pass it)
     uint32_t nb = 1;
@@ -67,38 +43,18 @@ __device__ __forceinline__ void garner_element(const GarnerLaunch &G, int e, int
         const uint64_t cm = limb_carries(__ballot(u < a[c]), __ballot(u == 0xFFFFFFFFu), nb);
         a[c] = u + lane_bit(cm, lane);
     }
-    uint64_t t[C], u[C], v[C];
-#pragma unroll
-    for (int c = 0; c < C; c++) t[c] = 0;
-    // h = a B / 2^(32 L) mod p, below 2 p
-#pragma unroll
-    for (int k = 0; k < C; k++)
-        for (int i = 0; i < 64 && 64 * k + i < L; i++) {
-            const uint32_t x = (uint32_t)__builtin_amdgcn_readlane((int)a[k], i);
-#pragma unroll
-            for (int c = 0; c < C; c++) u[c] = (uint64_t)x * B[c] + (uint32_t)t[c];
-            const uint32_t m = low_limb(u) * ninv;
-#pragma unroll
-            for (int c = 0; c < C; c++) v[c] = (uint64_t)m * p[c] + (uint32_t)u[c];
-            shift_step<C, true>(u, v, t);
-        }
     uint32_t h[C];
-    uint32_t over = limbs_of_sums(t, h, lane);
-    limbs_reduce_once(h, p, lane, over);
+    limbs_montmul(a, B, p, lk[4 * L], L, lane, h);
     if (!nb) {                                               // minus 2^(32 L) qinv = B
-        uint32_t cin = 0;
+        uint32_t d[C];
 #pragma unroll
-        for (int c = 0; c < C; c++) {
-            const int l = 64 * c + lane;
-            const uint32_t d = l < L ? lk[3 * L + l] : 0u;   // p - B
-            const uint32_t s = h[c] + d;
-            const uint64_t cm = limb_carries(__ballot(s < d), __ballot(s == 0xFFFFFFFFu), cin);
-            h[c] = s + lane_bit(cm, lane);
-        }
-        limbs_reduce_once(h, p, lane, cin);
+        for (int c = 0; c < C; c++) d[c] = 64 * c + lane < L ? lk[3 * L + 64 * c + lane] : 0u;   // p - B
+        const uint32_t over = limbs_add(h, d, lane);
+        limbs_reduce_once(h, p, lane, over);
     }
     // m = m_q + h q, its low limbs one per step
     uint32_t lo[C];
+    uint64_t t[C], u[C];
 #pragma unroll
     for (int c = 0; c < C; c++) {
         t[c] = mq[c];

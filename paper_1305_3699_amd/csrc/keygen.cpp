@@ -419,6 +419,16 @@ bool bn_modinv_odd(const Limbs &a, const Limbs &p, Limbs &out) {
     return true;
 }
 
+// 2 <= a <= N - 2, for odd N: a is none of 0, 1 and N - 1 and below N.
+bool valid_base(const uint32_t *a, const uint32_t *N, int L) {
+    int l = L - 1;
+    while (l > 0 && a[l] == N[l]) l--;
+    if (l == 0 ? a[0] + (uint64_t)1 >= N[0] : a[l] >= N[l]) return false;   // above it only limb 0 differs
+    for (l = L - 1; l > 0; l--)
+        if (a[l]) return true;
+    return a[0] >= 2;
+}
+
 bool rows_equal(const uint32_t *a, const Limbs &b, int L) {
     for (int l = 0; l < L; l++)
         if (a[l] != (l < (int)b.size() ? b[l] : 0u)) return false;
@@ -483,31 +493,32 @@ int rsa_miller_rabin(const uint32_t *cand, size_t count, int limbs, const uint32
     const int L = limbs;
     const size_t row = (size_t)rounds * L;
     try {
-        std::vector<Candidate> cs(count);
         for (size_t i = 0; i < count; i++) {
-            Limbs N = bn_from_ptr(cand + i * L, (size_t)L);
-            bn_trim(N);
-            if (bn_low(N) % 2 == 0 || bn_cmp(N, Limbs{3}) <= 0) return fail(RNS_EINVAL, "candidates must be odd and > 3");
-            Candidate &c = cs[i];
-            c.nm1 = bn_sub(N, Limbs{1});
-            for (int r = 0; r < rounds; r++) {
-                Limbs a = bn_from_ptr(bases + i * row + (size_t)r * L, (size_t)L);
-                bn_trim(a);
-                if (bn_cmp(a, Limbs{2}) < 0 || bn_cmp(a, bn_sub(N, Limbs{2})) > 0)
-                    return fail(RNS_EINVAL, "bases must lie in [2, N - 2]");
-            }
-            c.d = c.nm1;
-            while (bn_low(c.d) % 2 == 0) {
-                c.d = bn_shr1(c.d);
-                c.s++;
-            }
-            c.d.resize((size_t)L, 0u);
+            const uint32_t *N = cand + i * L;
+            int n = L;
+            while (n > 0 && N[n - 1] == 0) n--;
+            if (n == 0 || !(N[0] & 1u) || (n == 1 && N[0] <= 3)) return fail(RNS_EINVAL, "candidates must be odd and > 3");
+            for (int r = 0; r < rounds; r++)
+                if (!valid_base(bases + i * row + (size_t)r * L, N, L)) return fail(RNS_EINVAL, "bases must lie in [2, N - 2]");
         }
         // every candidate's tables built on the device when its base runs on
         // the matrix engine (the default bases do)
         {
             const int grc = miller_rabin_gpu(cand, count, L, bases, rounds, verdict, s);
             if (grc != RNS_EUNSUPPORTED) return grc ? grc : ok();
+        }
+        std::vector<Candidate> cs(count);
+        for (size_t i = 0; i < count; i++) {
+            Limbs N = bn_from_ptr(cand + i * L, (size_t)L);
+            bn_trim(N);
+            Candidate &c = cs[i];
+            c.nm1 = bn_sub(N, Limbs{1});
+            c.d = c.nm1;
+            while (bn_low(c.d) % 2 == 0) {
+                c.d = bn_shr1(c.d);
+                c.s++;
+            }
+            c.d.resize((size_t)L, 0u);
         }
         // otherwise one context per candidate, built on a pool of host
         // threads (each on the caller's device); errors are reported on this

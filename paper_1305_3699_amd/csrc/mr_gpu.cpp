@@ -3,11 +3,11 @@
 // Sec. 4.3: key material stays on the GPU).  All candidates of one size share
 // one base pair.  A table kernel derives each candidate's matrix-engine
 // tables from N alone: N's residues, the first extension's constant tiles,
-// c_i = -N^-1 M_i^-1, M mod N and M^2 mod N (a one-thread long division by
-// N), the entry table, and d, s with N - 1 = 2^s d.  The exponentiations
-// a^d and the squarings run as grouped matrix-core launches on those tables,
-// and a check kernel takes each decision (1, N - 1) on the device; the host
-// only plans the launches and reads the verdicts once.
+// c_i = -N^-1 M_i^-1, M mod N and M^2 mod N (Montgomery products in limbs), the
+// entry table, and d, s with N - 1 = 2^s d.  The exponentiations a^d run as one
+// grouped matrix-core launch on those tables, and one kernel then decides each
+// base: the squarings up to N - 1, in limbs, and the comparisons.  The host only
+// plans the launches and reads the verdicts once.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -19,6 +19,7 @@
 
 #include "capi_internal.hpp"
 #include "jobs.hpp"
+#include "limbs.hpp"
 #include "mr_gpu.hpp"
 
 namespace rnsrsa {
@@ -37,7 +38,8 @@ struct MrLayout {
     constexpr size_t kap() const { return 10 * (size_t)K; }                // [K] R^2 M^-1 mod m'_t
     constexpr size_t p1() const { return 11 * (size_t)K; }                 // [K][K+1][4] (M_i mod m'_t) 2^8a R mod m'_t
     constexpr size_t vred() const { return p1() + (size_t)K * (K + 1) * 4; }  // [K+1][4] redundant row, raw words
-    constexpr size_t size() const { return vred() + (size_t)(K + 1) * 4; }
+    constexpr size_t mlimbs() const { return vred() + (size_t)(K + 1) * 4; }  // [K] limbs of M
+    constexpr size_t size() const { return mlimbs() + (size_t)K; }
 };
 
 std::vector<uint32_t> make_mr_consts(const BaseSet &bs) {
@@ -85,6 +87,9 @@ std::vector<uint32_t> make_mr_consts(const BaseSet &bs) {
         for (int a = 0; a < 4; a++) v[ly.vred() + (size_t)i * 4 + a] = mi_lo << (8 * a);
     }
     v[ly.vred() + (size_t)K * 4] = kDigitBias * sum_lo;
+    Limbs M{1};
+    for (uint32_t m : bs.B) M = bn_mul(M, Limbs{m});
+    std::copy(M.begin(), M.end(), v.begin() + ly.mlimbs());     // below 2^(32 K)
     return v;
 }
 
@@ -94,6 +99,7 @@ struct MrTablesArgs {
     uint32_t *keys;         // count x key_size: the matrix engine's per-modulus tables
     uint32_t *entry;        // count x (L x ecols): entry tables for L-limb inputs
     uint32_t *dexp;         // count x L: d
+    uint32_t *r2;           // count x L: 2^(64 L) mod N
     uint8_t *flag;          // count: 0 N coprime to every channel, 1 a channel prime divides N, 2 N is one
     MLayout sh;
     int L;
@@ -142,55 +148,90 @@ __device__ __forceinline__ uint32_t digit_dev(int64_t V, int b) {
     return (uint32_t)(uint8_t)(int8_t)((int)((w >> (8 * b)) & 0xFFu) - 128);
 }
 
-// t (n + 1 limbs, below Nn 2^32) <- t mod Nn; Nn normalised (top bit of limb
-// n - 1 set).  The quotient digit from the top two limbs over Nn's top limb
-// overshoots by at most 2 (Knuth, Vol. 2, 4.3.1), corrected by adding Nn back.
-__device__ void reduce_one(uint32_t *t, const uint32_t *Nn, int n) {
-    const uint64_t num = ((uint64_t)t[n] << 32) | t[n - 1];
-    uint64_t q = num / Nn[n - 1];
-    if (q > 0xFFFFFFFFull) q = 0xFFFFFFFFull;
-    uint64_t mul = 0;
-    uint32_t borrow = 0;
-    for (int l = 0; l <= n; l++) {
-        const uint64_t p = (l < n ? q * Nn[l] : 0) + mul;
-        mul = p >> 32;
-        const uint32_t pl = (uint32_t)p, v = t[l];
-        const uint32_t d = v - pl, d2 = d - borrow;
-        borrow = (v < pl) | (d < borrow);
-        t[l] = d2;
-    }
-    while (borrow) {                                            // negative: add Nn back
-        uint32_t c = 0;
-        for (int l = 0; l <= n; l++) {
-            const uint64_t s = (uint64_t)t[l] + (l < n ? Nn[l] : 0) + c;
-            t[l] = (uint32_t)s;
-            c = (uint32_t)(s >> 32);
+// Limb c 64 + lane of x, n limbs.
+template <int C>
+__device__ __forceinline__ void limbs_load(const uint32_t *x, int n, int lane, uint32_t (&v)[C]) {
+#pragma unroll
+    for (int c = 0; c < C; c++) v[c] = 64 * c + lane < n ? x[64 * c + lane] : 0u;
+}
+template <int C>
+__device__ __forceinline__ void limbs_store(uint32_t *x, int n, int lane, const uint32_t (&v)[C]) {
+#pragma unroll
+    for (int c = 0; c < C; c++)
+        if (64 * c + lane < n) x[64 * c + lane] = v[c];
+}
+
+// R^2 mod N, M mod N and M^2 mod N with R = 2^(32 L), on one wave.  R 2^32 by
+// doublings from N's top bit, R 2^(32 j) to j = L by Montgomery products along L's
+// bits; M by its chunks of L limbs, each times R.
+template <int C>
+__device__ __forceinline__ void mr_limb_constants(const uint32_t *Nl, const uint32_t *__restrict__ ml, int K, int L,
+                                                  int lane, uint32_t *r2g, uint32_t *Mm, uint32_t *Yv) {
+    uint32_t n[C], x[C], r2[C], t[C], acc[C];
+    limbs_load(Nl, L, lane, n);
+    const uint32_t ninv = neg_inverse32(limb_at(n, 0));
+    const int tl = top_limb(n), top = 32 * tl + 31 - __builtin_clz(limb_at(n, tl));   // 2^top <= N
+#pragma unroll
+    for (int c = 0; c < C; c++) x[c] = 64 * c + lane == tl ? 1u << (top & 31) : 0u;
+    for (int i = top; i < 32 * L + 32; i++) {
+        uint32_t below = 0;
+#pragma unroll
+        for (int c = 0; c < C; c++) {
+            const uint32_t up = lane_up(x[c], below);
+            below = (uint32_t)__builtin_amdgcn_readlane((int)x[c], 63);
+            x[c] = x[c] << 1 | up >> 31;
         }
-        borrow = c ? 0u : 1u;                                   // a carry out of the top limb ends the deficit
+        limbs_reduce_once(x, n, lane, below >> 31);
     }
+#pragma unroll
+    for (int c = 0; c < C; c++) r2[c] = x[c];
+    for (int b = 30 - __builtin_clz(L); b >= 0; b--) {
+        limbs_montmul(r2, r2, n, ninv, L, lane, t);
+#pragma unroll
+        for (int c = 0; c < C; c++) r2[c] = t[c];
+        if (L >> b & 1) {
+            limbs_montmul(t, x, n, ninv, L, lane, r2);
+        }
+    }
+    limbs_store(r2g, L, lane, r2);
+#pragma unroll
+    for (int c = 0; c < C; c++) acc[c] = 0;
+    for (int h = (K - 1) / L; h >= 0; h--) {                    // acc <- (acc 2^(32 L) + chunk) R
+        uint32_t ch[C];
+        limbs_load(ml + (size_t)h * L, K - h * L < L ? K - h * L : L, lane, ch);
+        limbs_montmul(acc, r2, n, ninv, L, lane, t);
+        limbs_montmul(ch, r2, n, ninv, L, lane, acc);
+        const uint32_t over = limbs_add(acc, t, lane);
+        limbs_reduce_once(acc, n, lane, over);
+    }
+#pragma unroll
+    for (int c = 0; c < C; c++) t[c] = c == 0 && lane == 0 ? 1u : 0u;
+    limbs_montmul(t, acc, n, ninv, L, lane, x);                 // M mod N
+    limbs_store(Mm, L, lane, x);
+    limbs_montmul(x, acc, n, ninv, L, lane, t);                 // M^2 mod N
+    limbs_store(Yv, L, lane, t);
 }
 
-// x = a * w (n limbs times one word) into t (n + 1 limbs).
-__device__ void mul_word(uint32_t *t, const uint32_t *a, uint32_t w, int n) {
-    uint64_t c = 0;
-    for (int l = 0; l < n; l++) {
-        const uint64_t p = (uint64_t)a[l] * w + c;
-        t[l] = (uint32_t)p;
-        c = p >> 32;
-    }
-    t[n] = (uint32_t)c;
+// s of N - 1 = 2^s d, d odd (N odd, above 1).
+__device__ __forceinline__ int two_power(const uint32_t *N, int L) {
+    int l = 0;
+    uint32_t w = N[0] & ~1u;
+    while (w == 0 && l + 1 < L) w = N[++l];
+    return 32 * l + (w ? __builtin_ctz(w) : 0);
 }
 
-// One workgroup per candidate.  LDS: N, the normalised Nn, two (n + 2)-limb
-// work rows, M mod N and M^2 mod N (shifted), residues of N, of M mod N and
-// of M^2 mod N per channel, G_t and c_i.
+// One workgroup per candidate.  LDS: N, M mod N and M^2 mod N, residues of N, of
+// M mod N and of M^2 mod N per channel, G_t and c_i.  Long divisions by N on one lane
+// took about 700 us for 500 1024-bit candidates, ten times the rest; the chain
+// of some 20 Montgomery products on one wave leaves 79 us for the whole kernel.
+template <int C>
 __global__ __launch_bounds__(kMrThreads) void mr_tables_kernel(MrTablesArgs A) {
     extern __shared__ uint32_t sm[];
     const int K = A.sh.K, L = A.L, tid = threadIdx.x;
     const MrLayout cl{K};
     const uint32_t *__restrict__ cst = A.cst;
-    uint32_t *N = sm, *Nn = N + L, *T1 = Nn + L + 1, *T2 = T1 + L + 2, *Mm = T2 + L + 2, *Yv = Mm + L + 1;
-    uint32_t *nres = Yv + L + 1, *mres = nres + 2 * K, *yres = mres + 2 * K, *G = yres + 2 * K, *cv = G + K;
+    uint32_t *N = sm, *Mm = N + L, *Yv = Mm + L;
+    uint32_t *nres = Yv + L, *mres = nres + 2 * K, *yres = mres + 2 * K, *G = yres + 2 * K, *cv = G + K;
     __shared__ int s_flag;
     const size_t ci = blockIdx.x;
     const uint32_t *src = A.cand + ci * L;
@@ -198,77 +239,15 @@ __global__ __launch_bounds__(kMrThreads) void mr_tables_kernel(MrTablesArgs A) {
     if (tid == 0) s_flag = 0;
     __syncthreads();
 
-    for (int c = tid; c < 2 * K; c += kMrThreads)
-        nres[c] = residue_of(N, L, cst[cl.m() + c], cst[cl.u() + c], cst[cl.r2() + c]);
-    if (tid == 0) {
-        // M mod N and M^2 mod N by long division in the normalised domain
-        // (everything times 2^sh, Nn = N 2^sh with its top bit set), and d, s
-        int n = L;
-        while (n > 1 && N[n - 1] == 0) n--;
-        const int sh = __builtin_clz(N[n - 1]);
-        for (int l = n - 1; l >= 0; l--)
-            Nn[l] = (N[l] << sh) | (sh && l > 0 ? N[l - 1] >> (32 - sh) : 0u);
-        for (int l = 0; l <= n; l++) T1[l] = 0;
-        T1[0] = 1u << sh;                                       // 1 (shifted); N > 1
-        for (int i = 0; i < K; i++) {                           // times each prime of B: M = prod m_i
-            mul_word(T2, T1, cst[cl.m() + i], n);
-            reduce_one(T2, Nn, n);
-            for (int l = 0; l < n; l++) T1[l] = T2[l];
-        }
-        for (int l = 0; l < n; l++) Mm[l] = T1[l];             // M mod N, shifted
-        // M^2 mod N: Y = sum over the limbs z_l of M mod N, top first, of
-        // Y 2^32 + (M mod N) z_l, each step reduced
-        for (int l = 0; l <= n; l++) T1[l] = 0;
-        for (int l = n - 1; l >= 0; l--) {
-            const uint32_t z = (Mm[l] >> sh) | (sh && l + 1 < n ? Mm[l + 1] << (32 - sh) : 0u);   // limb l of M mod N
-            for (int j = n; j > 0; j--) T1[j] = T1[j - 1];      // Y 2^32
-            T1[0] = 0;
-            reduce_one(T1, Nn, n);
-            mul_word(T2, Mm, z, n);                             // (M mod N) z, shifted
-            reduce_one(T2, Nn, n);
-            uint32_t c = 0;
-            for (int j = 0; j < n; j++) {
-                const uint64_t s2 = (uint64_t)T1[j] + T2[j] + c;
-                T1[j] = (uint32_t)s2;
-                c = (uint32_t)(s2 >> 32);
-            }
-            // below 2 Nn: subtract Nn once if it is reached
-            bool ge = c != 0;
-            if (!ge) {
-                ge = true;
-                for (int j = n - 1; j >= 0; j--)
-                    if (T1[j] != Nn[j]) {
-                        ge = T1[j] > Nn[j];
-                        break;
-                    }
-            }
-            if (ge) {
-                uint32_t b = 0;
-                for (int j = 0; j < n; j++) {
-                    const uint32_t v = T1[j], d = v - Nn[j], d2 = d - b;
-                    b = (v < Nn[j]) | (d < b);
-                    T1[j] = d2;
-                }
-            }
-            T1[n] = 0;
-        }
-        // back from the shifted domain
-        for (int l = 0; l < L; l++) {
-            Yv[l] = l < n ? (T1[l] >> sh) | (sh && l + 1 < n ? T1[l + 1] << (32 - sh) : 0u) : 0u;
-            const uint32_t mm = l < n ? (Mm[l] >> sh) | (sh && l + 1 < n ? Mm[l + 1] << (32 - sh) : 0u) : 0u;
-            T2[l] = mm;
-        }
-        for (int l = 0; l < L; l++) Mm[l] = T2[l];
-        // N - 1 = 2^s d (N odd)
-        int s = 0;
-        int l0 = 0;
-        uint32_t w0 = N[0] & ~1u;
-        while (w0 == 0 && l0 + 1 < L) w0 = N[++l0];
-        s = 32 * l0 + (w0 ? __builtin_ctz(w0) : 0);
+    if (tid < 64) {
+        mr_limb_constants<C>(N, cst + cl.mlimbs(), K, L, tid, A.r2 + ci * L, Mm, Yv);
+    } else {
+        for (int c = tid - 64; c < 2 * K; c += kMrThreads - 64)
+            nres[c] = residue_of(N, L, cst[cl.m() + c], cst[cl.u() + c], cst[cl.r2() + c]);
+        const int s = two_power(N, L);
         uint32_t *d = A.dexp + ci * L;
-        for (int l = 0; l < L; l++) {
-            const int bit = 32 * l + s;
-            const int lw = bit >> 5, sb = bit & 31;
+        for (int l = tid - 64; l < L; l += kMrThreads - 64) {
+            const int lw = l + (s >> 5), sb = s & 31;
             const uint32_t lo = lw < L ? (lw == 0 ? N[0] & ~1u : N[lw]) : 0u;
             const uint32_t hi = lw + 1 < L ? N[lw + 1] : 0u;
             d[l] = sb ? (lo >> sb) | (hi << (32 - sb)) : lo;
@@ -374,34 +353,58 @@ __global__ __launch_bounds__(kMrThreads) void mr_tables_kernel(MrTablesArgs A) {
     for (int j = tid; j < L; j += kMrThreads) E[(size_t)j * cols + cols - 1] = j == 0 ? Yv[0] : 0u;
 }
 
-// state[c, r]: 0 undecided, 1 base passed, 2 base failed.  After the
-// exponentiation of step j (j = 0: x = a^d, j > 0: x = x^2) compares each
-// undecided x with 1 and N - 1.
-__global__ void mr_check_kernel(const uint32_t *__restrict__ x, const uint32_t *__restrict__ cand, int L,
-                                int rounds, int count, int step, uint8_t *__restrict__ state) {
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
+// One wave per base: x = a^d mod N on entry; state 1 when x is 1 or N - 1 or one
+// of its s - 1 squares is N - 1, else 2.  The squarings are Montgomery products
+// (limbs_montmul); one grouped exponentiation launch and one comparison per
+// squaring took 75 to 87 us, and the longest s of 500 candidates is about 10; this
+// takes 23 us for 500 1024-bit candidates of 5 bases.
+constexpr int kMrWaves = 4;
+template <int C>
+__global__ __launch_bounds__(64 * kMrWaves) void mr_square_kernel(const uint32_t *__restrict__ x,
+                                                                  const uint32_t *__restrict__ cand,
+                                                                  const uint32_t *__restrict__ r2, int L, int rounds,
+                                                                  int count, uint8_t *__restrict__ state) {
+    const int lane = threadIdx.x & 63;
+    const int idx = (int)blockIdx.x * kMrWaves + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     if (idx >= count * rounds) return;
-    if (state[idx]) return;
-    const int c = idx / rounds;
-    const uint32_t *xr = x + (size_t)idx * L, *N = cand + (size_t)c * L;
-    bool one = xr[0] == 1u, nm1 = xr[0] == N[0] - 1u;   // N odd: N - 1 differs from N in limb 0 only
-    for (int l = 1; l < L; l++) {
-        one = one && xr[l] == 0u;
-        nm1 = nm1 && xr[l] == N[l];
+    const size_t ci = (size_t)(idx / rounds);
+    uint32_t n[C], v[C], one[C], w[C], q[C];
+    limbs_load(cand + ci * L, L, lane, n);
+    limbs_load(x + (size_t)idx * L, L, lane, v);
+    limbs_load(r2 + ci * L, L, lane, q);
+    auto equal = [&](const uint32_t (&a)[C], const uint32_t (&b)[C]) {
+        bool d = false;
+#pragma unroll
+        for (int c = 0; c < C; c++) d = d || a[c] != b[c];
+        return __ballot(d) == 0;
+    };
+#pragma unroll
+    for (int c = 0; c < C; c++) {
+        one[c] = c == 0 && lane == 0 ? 1u : 0u;
+        w[c] = n[c] - one[c];                                   // N odd
     }
-    // s from N: the trailing zero bits of N - 1
-    int s = 0;
-    {
-        int l0 = 0;
-        uint32_t w0 = N[0] & ~1u;
-        while (w0 == 0 && l0 + 1 < L) w0 = N[++l0];
-        s = 32 * l0 + (w0 ? __builtin_ctz(w0) : 0);
+    int st = equal(v, one) || equal(v, w) ? 1 : 0;
+    const int s = two_power(cand + ci * L, L);
+    if (!st && s > 1) {
+        const uint32_t ninv = neg_inverse32(limb_at(n, 0));
+        limbs_montmul(one, q, n, ninv, L, lane, w);             // R mod N
+#pragma unroll
+        for (int c = 0; c < C; c++) one[c] = w[c];
+        limbs_montmul(v, q, n, ninv, L, lane, w);               // x R mod N
+        for (int j = 1; j < s && !st; j++) {
+            limbs_montmul(w, w, n, ninv, L, lane, v);
+#pragma unroll
+            for (int c = 0; c < C; c++) q[c] = w[c] = v[c];
+            if (equal(v, one)) st = 2;                          // 1 without passing -1
+            const uint32_t over = limbs_add(q, one, lane);      // -1: v + 1 = N
+            limbs_reduce_once(q, n, lane, over);
+            uint32_t nz = 0;
+#pragma unroll
+            for (int c = 0; c < C; c++) nz |= q[c];
+            if (__ballot(nz != 0) == 0) st = 1;
+        }
     }
-    uint8_t st = 0;
-    if (nm1 || (step == 0 && one)) st = 1;              // a^(2^j d) = -1, or a^d = 1
-    else if (one) st = 2;                               // 1 reached without passing -1
-    else if (step + 1 >= s) st = 2;                     // no squaring left to reach -1
-    state[idx] = st;
+    if (lane == 0) state[idx] = (uint8_t)(st == 1 ? 1 : 2);
 }
 
 __global__ void mr_verdict_kernel(const uint8_t *__restrict__ state, const uint8_t *__restrict__ flag, int rounds,
@@ -488,33 +491,19 @@ int miller_rabin_gpu(const uint32_t *cand, size_t count, int L, const uint32_t *
     if (rc) return rc;
     const MfmaShape &sh = mb.sh;
     const size_t row = (size_t)rounds * L, cols = sh.ecols();
-    // s of each candidate (host copy: it sets the number of squaring steps)
-    std::vector<int> sv(count);
-    int smax = 0;
-    for (size_t i = 0; i < count; i++) {
-        const uint32_t *N = cand + i * L;
-        int l0 = 0;
-        uint32_t w0 = N[0] & ~1u;
-        while (w0 == 0 && l0 + 1 < L) w0 = N[++l0];
-        sv[i] = 32 * l0 + (w0 ? __builtin_ctz(w0) : 0);
-        smax = std::max(smax, sv[i]);
-    }
-    Scratch d_cand, d_keys, d_entry, d_exp, d_x, d_two, d_flag, d_state, d_verdict;
+    Scratch d_cand, d_keys, d_entry, d_exp, d_x, d_r2, d_flag, d_state, d_verdict, d_jobs, d_table;
     rc = scratch_alloc(d_cand, count * L * sizeof(uint32_t), s);
     if (!rc) rc = scratch_alloc(d_keys, count * sh.key_size() * sizeof(uint32_t), s);
     if (!rc) rc = scratch_alloc(d_entry, count * L * cols * sizeof(uint32_t), s);
     if (!rc) rc = scratch_alloc(d_exp, count * L * sizeof(uint32_t), s);
     if (!rc) rc = scratch_alloc(d_x, count * row * sizeof(uint32_t), s);
-    if (!rc) rc = scratch_alloc(d_two, sizeof(uint32_t), s);
+    if (!rc) rc = scratch_alloc(d_r2, count * L * sizeof(uint32_t), s);
     if (!rc) rc = scratch_alloc(d_flag, count, s);
     if (!rc) rc = scratch_alloc(d_state, count * rounds, s);
     if (!rc) rc = scratch_alloc(d_verdict, count, s);
     if (rc) return rc;
-    const uint32_t two = 2;
     e = hipMemcpyAsync(d_cand.p, cand, count * L * sizeof(uint32_t), hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = hipMemcpyAsync(d_x.p, bases, count * row * sizeof(uint32_t), hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(d_two.p, &two, sizeof(uint32_t), hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = hipMemsetAsync(d_state.p, 0, count * rounds, s);
     if (e != hipSuccess) return hip_fail(e, "miller-rabin set-up copies");
 
     MrTablesArgs ta{};
@@ -523,65 +512,63 @@ int miller_rabin_gpu(const uint32_t *cand, size_t count, int L, const uint32_t *
     ta.keys = (uint32_t *)d_keys.p;
     ta.entry = (uint32_t *)d_entry.p;
     ta.dexp = (uint32_t *)d_exp.p;
+    ta.r2 = (uint32_t *)d_r2.p;
     ta.flag = (uint8_t *)d_flag.p;
     ta.sh = sh;
     ta.L = L;
-    // N, Nn, two work rows, M mod N, M^2 mod N; residues (3 x 2K), G, c
-    const size_t lds = ((size_t)6 * L + 8 + (size_t)8 * sh.K) * sizeof(uint32_t);
-    hipLaunchKernelGGL(mr_tables_kernel, dim3((unsigned)count), dim3(kMrThreads), lds, s, ta);
+    // N, M mod N, M^2 mod N; residues (3 x 2K), G, c
+    const size_t lds = ((size_t)3 * L + (size_t)8 * sh.K) * sizeof(uint32_t);
+    const dim3 tg((unsigned)count), tb(kMrThreads);
+    if (L <= 64) hipLaunchKernelGGL(mr_tables_kernel<1>, tg, tb, lds, s, ta);
+    else if (L <= 128) hipLaunchKernelGGL(mr_tables_kernel<2>, tg, tb, lds, s, ta);
+    else if (L <= 256) hipLaunchKernelGGL(mr_tables_kernel<4>, tg, tb, lds, s, ta);
+    else hipLaunchKernelGGL(mr_tables_kernel<8>, tg, tb, lds, s, ta);
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "miller-rabin table launch");
 
-    std::vector<std::unique_ptr<Scratch>> keep;
-    std::vector<std::vector<MJob>> host_jobs;
+    // x = a^d
+    JobGroup g;
+    g.shape = sh;
+    g.device = dev;
     const int w_d = window_for_bits(32 * L);
-    for (int step = 0; step < std::max(1, smax); step++) {
-        // x = a^d (step 0) or x = x^2 for the candidates that may square again
-        JobGroup g;
-        g.shape = sh;
-        g.device = dev;
-        for (size_t i = 0; i < count; i++) {
-            if (step > 0 && sv[i] <= step) continue;
-            PlannedJob J{};
-            uint32_t *x = (uint32_t *)d_x.p + i * row;
-            J.j.mb = mb.d_mbase;
-            J.j.mk = (const uint32_t *)d_keys.p + i * sh.key_size();
-            J.j.E = (const uint32_t *)d_entry.p + i * L * cols;
-            J.j.exp = step == 0 ? (const uint32_t *)d_exp.p + i * L : (const uint32_t *)d_two.p;
-            J.j.in = x;
-            J.j.out = x;
-            J.j.batch = rounds;
-            J.j.in_limbs = L;
-            J.j.in_stride = L;
-            J.j.L = L;
-            J.j.out_stride = L;
-            J.j.exp_limbs = step == 0 ? L : 1;
-            J.j.exp_stride = 0;
-            J.j.window = step == 0 ? w_d : 1;
-            J.cost = step == 0 ? (size_t)32 * L : 3;
-            g.jobs.push_back(J);
-        }
-        if (g.jobs.empty()) break;
-        finish_group(g);
-        retile_group(g, dev);
-        host_jobs.emplace_back();
-        std::vector<MJob> &js = host_jobs.back();
-        for (const PlannedJob &J : g.jobs) js.push_back(J.j);
-        keep.emplace_back(new Scratch);
-        Scratch &jt = *keep.back();
-        if ((rc = scratch_alloc(jt, js.size() * sizeof(MJob), s))) return rc;
-        if ((e = hipMemcpyAsync(jt.p, js.data(), js.size() * sizeof(MJob), hipMemcpyHostToDevice, s)) != hipSuccess)
-            return hip_fail(e, "hipMemcpyAsync");
-        keep.emplace_back(new Scratch);
-        Scratch &tb = *keep.back();
-        if ((rc = scratch_alloc(tb, g.table_words() * sizeof(uint32_t), s))) return rc;
-        if ((e = launch_group(g, (const MJob *)jt.p, (uint32_t *)tb.p, s)) != hipSuccess)
-            return hip_fail(e, "grouped modexp launch");
-        const int n = (int)(count * rounds);
-        hipLaunchKernelGGL(mr_check_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
-                           (const uint32_t *)d_x.p, (const uint32_t *)d_cand.p, L, rounds, (int)count, step,
-                           (uint8_t *)d_state.p);
-        if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "miller-rabin check launch");
+    for (size_t i = 0; i < count; i++) {
+        PlannedJob J{};
+        uint32_t *x = (uint32_t *)d_x.p + i * row;
+        J.j.mb = mb.d_mbase;
+        J.j.mk = (const uint32_t *)d_keys.p + i * sh.key_size();
+        J.j.E = (const uint32_t *)d_entry.p + i * L * cols;
+        J.j.exp = (const uint32_t *)d_exp.p + i * L;
+        J.j.in = x;
+        J.j.out = x;
+        J.j.batch = rounds;
+        J.j.in_limbs = L;
+        J.j.in_stride = L;
+        J.j.L = L;
+        J.j.out_stride = L;
+        J.j.exp_limbs = L;
+        J.j.exp_stride = 0;
+        J.j.window = w_d;
+        J.cost = (size_t)32 * L;
+        g.jobs.push_back(J);
     }
+    finish_group(g);
+    retile_group(g, dev);
+    std::vector<MJob> js;
+    js.reserve(count);
+    for (const PlannedJob &J : g.jobs) js.push_back(J.j);
+    if ((rc = scratch_alloc(d_jobs, js.size() * sizeof(MJob), s))) return rc;
+    if ((rc = scratch_alloc(d_table, g.table_words() * sizeof(uint32_t), s))) return rc;
+    if ((e = hipMemcpyAsync(d_jobs.p, js.data(), js.size() * sizeof(MJob), hipMemcpyHostToDevice, s)) != hipSuccess)
+        return hip_fail(e, "hipMemcpyAsync");
+    if ((e = launch_group(g, (const MJob *)d_jobs.p, (uint32_t *)d_table.p, s)) != hipSuccess)
+        return hip_fail(e, "grouped modexp launch");
+    const dim3 sg((unsigned)((count * rounds + kMrWaves - 1) / kMrWaves)), sb(64 * kMrWaves);
+    auto squares = L <= 64    ? mr_square_kernel<1>
+                   : L <= 128 ? mr_square_kernel<2>
+                   : L <= 256 ? mr_square_kernel<4>
+                              : mr_square_kernel<8>;
+    hipLaunchKernelGGL(squares, sg, sb, 0, s, (const uint32_t *)d_x.p, (const uint32_t *)d_cand.p,
+                       (const uint32_t *)d_r2.p, L, rounds, (int)count, (uint8_t *)d_state.p);
+    if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "miller-rabin squarings launch");
     hipLaunchKernelGGL(mr_verdict_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, s,
                        (const uint8_t *)d_state.p, (const uint8_t *)d_flag.p, rounds, (int)count,
                        (uint8_t *)d_verdict.p);

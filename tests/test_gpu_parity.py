@@ -994,6 +994,25 @@ def _mr_case(cands, rounds, limbs, seed):
     return want
 
 
+@pytest.mark.parametrize("limbs", [1, 2, 31, 33, 64, 65, 129, 257])
+def test_miller_rabin_limb_words(limbs):
+    """Candidates around the 64-limb words of a lane: full rows, short ones in
+    long rows, N - 1 divisible by high powers of two (squarings up to N - 1 and
+    past it to 1), against the oracle's strong test."""
+    rng = random.Random(limbs)
+    top = 32 * limbs
+    cands = [rng.getrandbits(top) | 1 << (top - 1) | 1, (1 << top) - 1, 65537, 5, 641]
+    cands += [(rng.getrandbits(top - 20 if top > 32 else 8) | 1) << 12 | 1, 3 * (1 << 30) + 1, 193]
+    if limbs <= 2:
+        cands += [gen.random_prime(32 * limbs, rng) for _ in range(4)]
+    if limbs in (31, 33):
+        cands += [(1 << 521) - 1, (1 << 607) - 1, 5 * (1 << 39) + 1]
+    cands = [n for n in cands if n < 1 << top and n > 3]
+    if limbs > 100:
+        cands = cands[:4]
+    _mr_case(cands, 2 if limbs > 64 else 6, limbs, limbs)
+
+
 @pytest.mark.parametrize("bits", [512, 1024])
 def test_miller_rabin_verdicts(bits):
     """Verdicts of the Miller-Rabin step (exponentiations in RNS, one
