@@ -278,13 +278,14 @@ MfmaShape auto_tile(const MfmaShape &sh, size_t tiles, int dev, bool small_jobs)
     return tiles < (size_t)(simds / 4) * per_cu ? alt : sh;
 }
 
-// A launch with no more tiles than SIMDs keeps the split kernel's workgroups all
-// resident: 8,192 RSA-2048 decryptions (1,024 tiles) take 1.55 ms split and 1.83
-// ms on single waves, a lone one 1.00 and 1.69 ms.  One tile more starts a
-// second round of workgroups: 8,200 to 16,384 take 2.29 to 2.59 ms on single waves,
-// 3.27 ms split.
+// A launch with fewer tiles than SIMDs keeps the split kernel's workgroups all
+// resident: 8,000 RSA-2048 decryptions (1,000 tiles) take 1.39 ms split and 1.74
+// ms on single waves, a lone one 0.91 and 1.6 ms.  At exactly one tile per SIMD some
+// workgroups wait for a second round now and then (8,192: 1.53 to 2.0 ms split), hence
+// the sixteenth left out; above it they all do (16,384: 3.2 ms, 2.45 ms on
+// single waves).
 bool split_tiles(const MfmaShape &sh, size_t tiles, int dev) {
-    return sh.split_waves() && tiles <= (size_t)device_simds(dev);
+    return sh.split_waves() && 16 * tiles <= 15 * (size_t)device_simds(dev);
 }
 
 int spread_tile_elems(const MfmaShape &sh, size_t tiles, int dev) {

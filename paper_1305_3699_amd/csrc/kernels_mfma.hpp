@@ -1143,9 +1143,9 @@ void modexp_mfma_kernel(ModexpMfmaLaunch A) {
 }
 
 // The split kernel of a single-wave shape: workgroup t runs tile t (see
-// SplitEngine).  Held to 3 waves per SIMD: 8,192 RSA-2048 decryptions, 1,024
-// workgroups that are then all resident, take 1.55 ms instead of 2.27 ms, a lone
-// one 1.00 ms instead of 0.99 ms.
+// SplitEngine).  Held to 3 waves per SIMD: 8,000 RSA-2048 decryptions, 1,000
+// workgroups that are then all resident, take 1.4 ms instead of 2.2 ms, a lone one
+// the same.
 template <int K, int MT, int WV, bool SQ>
 __global__ __launch_bounds__(64 * WV) __attribute__((amdgpu_waves_per_eu(3))) void modexp_split_kernel(ModexpMfmaLaunch A) {
     using S = MShp<K, 1, MT, 1>;

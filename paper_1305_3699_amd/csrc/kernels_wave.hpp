@@ -43,6 +43,16 @@ struct MLdsOperand {
     __device__ __forceinline__ uint32_t r(int nt) const { return y[(2 * M * NT + nt) * 64]; }
 };
 
+// Values of lane groups 2 and 3, in every lane group: two swaps of rows, about 20
+// cycles where a read through LDS takes over 100, of which k = 17's short products do
+// not hide enough (a lone RSA-1024 decryption 535 -> 514 us).
+__device__ __forceinline__ void lane_groups_23(uint32_t v, uint32_t &g2, uint32_t &g3) {
+    const auto hi = __builtin_amdgcn_permlane32_swap(v, v, false, false);           // [1]: groups 2 3 2 3
+    const auto r = __builtin_amdgcn_permlane16_swap(hi[1], hi[1], false, false);    // [0]: 2 2 2 2, [1]: 3 3 3 3
+    g2 = r[0];
+    g3 = r[1];
+}
+
 template <int K, int MT, int NT, bool SQ>
 struct WaveEngine {
     using S = MShp<K, 1, MT, NT>;
@@ -193,7 +203,9 @@ struct WaveEngine {
     }
     // the redundant row's low word, in every lane of its element
     __device__ __forceinline__ uint32_t redundant(const mfma_v4i &D) const {
-        return (uint32_t)__builtin_amdgcn_ds_bpermute(((lane & 15) + 48) * 4, (int)mfma_combine_lo(D));
+        uint32_t g2, g3;
+        lane_groups_23(mfma_combine_lo(D), g2, g3);
+        return g3;
     }
 
     // Step (i): digits xi of x y.
@@ -259,9 +271,10 @@ struct WaveEngine {
                 if (mt == MT - 1) {
                     if constexpr (WIDE) {
                         // the redundant row is lane group 3's, the estimate group 2's
-                        const uint32_t lo = (redundant(D[nt]) - x.r[nt]) * Mpinv_r;
-                        const int32_t est = __builtin_amdgcn_ds_bpermute(((lane & 15) + 32) * 4, D[nt][0]);
-                        const int32_t h = (est + est_r - (int32_t)(lo >> 18)) >> 14;
+                        uint32_t est, red;
+                        lane_groups_23(lane < 48 ? (uint32_t)D[nt][0] : mfma_combine_lo(D[nt]), est, red);
+                        const uint32_t lo = (red - x.r[nt]) * Mpinv_r;
+                        const int32_t h = ((int32_t)est + est_r - (int32_t)(lo >> 18)) >> 14;
                         alpha_h[nt] = ((uint32_t)h << (32 - kWideShift)) + (lo >> kWideShift);
                         alpha[nt] = lo & ((1u << kWideShift) - 1);
                     } else {

@@ -246,12 +246,12 @@ def test_scaled_and_unscaled_b_residues(bits):
 
 
 @pytest.mark.parametrize("bits,counts,opts", [
-    (1024, [16384], {}), (1024, [16385], {}), (1024, [16403, 1, 65], {}), (1024, [16320, 33, 16], {"group": 32}),
+    (1024, [15360], {}), (1024, [15361], {}), (1024, [16384], {}), (1024, [16385], {}), (1024, [16403, 1, 65], {}), (1024, [16320, 33, 16], {"group": 32}),
     (1024, [5, 17, 47], {}), (1024, [16385, 3], {"unscaled": True}), (1024, [4001], {"unscaled": True}),
     (512, [16387, 1, 64], {}), (512, [17, 2], {"group": 32})])
 def test_single_wave_and_split_launches(bits, counts, opts):
-    """One wave per tile against three (the launch rule's line is one tile of
-    16 elements per SIMD, 16,384 elements on 256 compute units), jobs that end
+    """One wave per tile against three (the launch rule's line is 15 tiles of 16
+    elements per 16 SIMDs, 15,360 elements on 256 compute units), jobs that end
     inside a workgroup's four tiles, both tiles and both residue forms:
     per-element exponents in the first job, shared ones in the others; every
     output equals the channel engine's, sampled rows the oracle's."""
