@@ -264,12 +264,15 @@ MfmaShape auto_tile(const MfmaShape &sh, size_t tiles, int dev, bool small_jobs)
     if (!mfma_shape_for(sh.K, alt, 16) || alt.NT != 1 || alt.W != sh.W || alt.MT != sh.MT) return sh;
     // Single-wave shapes: a wave's registers then hold the first extension's
     // tiles too (16,384 RSA-2048 decryptions 2.53 ms, 2.71 ms with 32 elements)
-    if (sh.W == 1) return alt;
+    if (sh.W == 1 && !sh.team()) return alt;
     // jobs of a few elements each: the 16-element tile needs hardly more
     // workgroups, and each does half the work
     if (small_jobs) return alt;
     const int simds = device_simds(dev);
     if (!simds) return sh;
+    // a team fills its CU: the 16-element tile (2.48 ms for RSA-4096 decryptions)
+    // while its tiles find a CU each, then the 32-element one (4.37 ms)
+    if (sh.team()) return 2 * tiles <= (size_t)(simds / 4) ? alt : sh;
     // the 32-element tile unless its workgroups cannot fill the resident
     // slots of every CU: then the 16-element tile's twice as many
     // workgroups give the SIMDs more waves
@@ -279,18 +282,18 @@ MfmaShape auto_tile(const MfmaShape &sh, size_t tiles, int dev, bool small_jobs)
 }
 
 // A launch with fewer tiles than SIMDs keeps the split kernel's workgroups all
-// resident: 8,000 RSA-2048 decryptions (1,000 tiles) take 1.39 ms split and 1.74
-// ms on single waves, a lone one 0.91 and 1.6 ms.  At exactly one tile per SIMD some
-// workgroups wait for a second round now and then (8,192: 1.53 to 2.0 ms split), hence
-// the sixteenth left out; above it they all do (16,384: 3.2 ms, 2.45 ms on
-// single waves).
+// resident: 8,000 RSA-2048 decryptions (1,000 tiles) take 1.39 ms split and 1.73
+// ms on single waves, a lone one 0.91 and 1.6 ms, 16,000 RSA-1024 encryptions (1,000
+// tiles) 55 and 77 us.  At exactly one tile per SIMD some workgroups wait for a
+// second round now and then (8,192 decryptions: 1.53 to 2.0 ms split), hence the 64th
+// left out; above it they all do (16,384: 3.2 ms, 2.45 ms on single waves).
 bool split_tiles(const MfmaShape &sh, size_t tiles, int dev) {
-    return sh.split_waves() && 16 * tiles <= 15 * (size_t)device_simds(dev);
+    return sh.split_waves() && 64 * tiles <= 63 * (size_t)device_simds(dev);
 }
 
 int spread_tile_elems(const MfmaShape &sh, size_t tiles, int dev) {
     const int simds = device_simds(dev);
-    const int waves = sh.split_waves() ? sh.split_waves() : sh.W;
+    const int waves = sh.team() ? 8 : sh.split_waves() ? sh.split_waves() : sh.W;
     int e = sh.NM();
     while (simds && e > kMinTileElems && tiles * (size_t)waves < (size_t)simds) {
         e /= 2;
@@ -632,7 +635,9 @@ int rns_mont_mul_batch(rns_ctx *ctx, const uint32_t *x, const uint32_t *y, uint3
     const BaseSet &bs = *ctx->plan.base;
     if (ctx->engine == RNS_ENGINE_MATRIX) {
         MfmaShape sh = ctx->mshape;
-        if (!ctx->group_req) sh = auto_tile(sh, (size_t)mfma_tiles(sh, batch), ctx->device);
+        // a single wave's product of 32 elements waits for its loads twice as long
+        // (40,000 products at k = 33: 27 us, of 16 elements 18 us)
+        if (!ctx->group_req || (sh.W == 1 && !sh.team())) sh = auto_tile(sh, (size_t)mfma_tiles(sh, batch), ctx->device);
         MontMulMfmaLaunch a{};
         a.mb = ctx->d_mbase;
         a.mk = ctx->d_mkey;

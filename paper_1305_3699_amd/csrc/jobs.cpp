@@ -191,7 +191,8 @@ void retile_group(JobGroup &g, int dev) {
         t32 += ((size_t)J.j.batch + 31) / 32;
         t16 += ((size_t)J.j.batch + 15) / 16;
     }
-    const MfmaShape t = auto_tile(g.shape, (size_t)g.tiles, dev, 4 * t16 <= 5 * t32);
+    // g.tiles may be spread; a team's rule counts full tiles
+    const MfmaShape t = auto_tile(g.shape, g.shape.team() ? t32 : (size_t)g.tiles, dev, 4 * t16 <= 5 * t32);
     if (t.NT != g.shape.NT) {
         g.shape = t;
         finish_group(g);

@@ -56,6 +56,15 @@ struct MShp {
     // the inputs or limb sums
     static constexpr int SPLIT = LY.split_waves();
     static constexpr int SPLIT_WORDS(int wv) { return 2 * (MT + 1) * 64 + wv * (2 * MT / wv + 1) * 64 + WAVE_IO_WORDS; }
+    // Team shapes (TeamEngine): tiles in LDS and the words of its parts there
+    static constexpr int TEAM_WAVES = 8;
+    static constexpr int TEAM_BASE = MT / TEAM_WAVES, TEAM_EXTRA = MT % TEAM_WAVES;
+    static constexpr int team_tile0(int wave) { return wave * TEAM_BASE + (wave < TEAM_EXTRA ? wave : TEAM_EXTRA); }
+    static constexpr int TEAM_L1 = NT == 2 ? 1 : 0, TEAM_L2 = NT;   // of the three per wave
+    static constexpr int TEAM_TILES = 1 + TEAM_L1 + TEAM_L2;
+    static constexpr int TEAM_OPERANDS = 32 * MT + TEAM_TILES * KSTEPS * 256 + (8 * KSTEPS + 1) * NT * 64;
+    static constexpr int TEAM_IO = TEAM_OPERANDS + (2 * MT + TEAM_WAVES) * NT * 64;
+    static constexpr int TEAM_WORDS = TEAM_IO + 16 * NT * (2 * K + 1 > 2 * XSLOTS + 1 ? 2 * K + 1 : 2 * XSLOTS + 1);
     // Single-wave shapes: waves of a workgroup, the LDS words each needs (16
     // elements' inputs, then a product's second operand, then 16 elements'
     // limb sums), and the words of the constants they share
@@ -1142,6 +1151,19 @@ void modexp_mfma_kernel(ModexpMfmaLaunch A) {
     }
 }
 
+template <int K, int MT, int NT, bool SQ>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void modexp_team_kernel(ModexpMfmaLaunch A) {
+    using S = MShp<K, 1, MT, NT>;
+    __shared__ __attribute__((aligned(16))) uint32_t lds[S::TEAM_WORDS];
+    const MJob J = mjob_of<&MJob::group0>(A, (int)blockIdx.x);
+    const int e0 = ((int)blockIdx.x - J.group0) * mjob_tile_elems(J, 16 * NT);
+    // both branches run the same barriers
+    if (__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) < S::TEAM_EXTRA)
+        modexp_team_tile<K, MT, NT, SQ, S::TEAM_BASE + 1>(J, e0, lds, A.table, blockIdx.x, A.max_window);
+    else
+        modexp_team_tile<K, MT, NT, SQ, S::TEAM_BASE>(J, e0, lds, A.table, blockIdx.x, A.max_window);
+}
+
 // The split kernel of a single-wave shape: workgroup t runs tile t (see
 // SplitEngine).  Held to 3 waves per SIMD: 8,000 RSA-2048 decryptions, 1,000
 // workgroups that are then all resident, take 1.4 ms instead of 2.2 ms, a lone one
@@ -1173,19 +1195,28 @@ template <int K, int W, int MT, int NT>
 hipError_t launch_modexp_mfma_t(const ModexpMfmaLaunch &a, hipStream_t s) {
     using S = MShp<K, W, MT, NT>;
     if (a.tiles <= 0) return hipSuccess;
-    if constexpr (S::SPLIT > 0) {
+    if constexpr (S::SPLIT > 0)
         if (a.split) return launch_modexp_split_t<K, MT, S::SPLIT>(a, s);
-    }
-    if constexpr (S::LY.sq_ok() && !S::A2_GLOBAL && !S::C_LDS) {
-        if (a.scaled) {
+    if constexpr (S::LY.team()) {
+        if (a.scaled)
+            hipLaunchKernelGGL((modexp_team_kernel<K, MT, NT, true>), dim3((unsigned)a.tiles), dim3(512), 0, s, a);
+        else
+            hipLaunchKernelGGL((modexp_team_kernel<K, MT, NT, false>), dim3((unsigned)a.tiles), dim3(512), 0, s, a);
+    } else if constexpr (S::LY.sq_ok() && !S::A2_GLOBAL && !S::C_LDS) {
+        if (a.scaled)
             hipLaunchKernelGGL((modexp_mfma_kernel<K, W, MT, NT, true>), dim3((unsigned)a.groups), dim3(S::THREADS), 0, s,
                                a);
-            return hipGetLastError();
-        }
+        else
+            hipLaunchKernelGGL((modexp_mfma_kernel<K, W, MT, NT, false>), dim3((unsigned)a.groups), dim3(S::THREADS), 0, s,
+                               a);
+    } else {
+        hipLaunchKernelGGL((modexp_mfma_kernel<K, W, MT, NT, false>), dim3((unsigned)a.groups), dim3(S::THREADS), 0, s, a);
     }
-    hipLaunchKernelGGL((modexp_mfma_kernel<K, W, MT, NT, false>), dim3((unsigned)a.groups), dim3(S::THREADS), 0, s, a);
     return hipGetLastError();
 }
+
+// v - f mod m of residues (MLayout::mmfix).
+__device__ __forceinline__ uint32_t mm_less(uint32_t v, uint32_t f, uint32_t m) { return v - f + (v < f ? m : 0u); }
 
 // One RNS Montgomery product per element on the matrix cores, for the
 // standalone call: residues in and out channel-major ([2K+1][batch]: B, B',
@@ -1207,16 +1238,6 @@ __global__ __launch_bounds__((MShp<K, W, MT, NT>::THREADS)) void montmul_mfma_ke
     const int tile = S::WAVE ? (int)blockIdx.x * S::WAVE_GROUP + wv : (int)blockIdx.x;
     const int lane = threadIdx.x & 63;
     const int g = lane >> 4;
-    std::conditional_t<S::WAVE, WaveEngine<K, MT, NT, false>, MConstOf<K, W, MT, NT>> C;
-    if constexpr (S::WAVE) {
-        C.setup(mb, mk, lds, lane);
-        __syncthreads();
-        C.load_tiles();
-    } else {
-        mfma_setup<K, W, MT, NT>(mb, mk, lds, wave, lane, C);
-        mfma_rows<K, W, MT, NT>(lds);
-        mfma_load_tiles<K, W, MT, NT>(mb, mk, lds, wave, lane, C);
-    }
     const int te = A.tile_elems > 0 && A.tile_elems < S::NM ? A.tile_elems : S::NM;
     const size_t B = (size_t)A.batch;
     int elem[NT];
@@ -1227,30 +1248,52 @@ __global__ __launch_bounds__((MShp<K, W, MT, NT>::THREADS)) void montmul_mfma_ke
         elem[nt] = tile * te + n;
         ok[nt] = n < te && elem[nt] < A.batch;
     }
+    std::conditional_t<S::WAVE, WaveEngine<K, MT, NT, false>, MConstOf<K, W, MT, NT>> C;
+    if constexpr (!S::WAVE) {
+        mfma_setup<K, W, MT, NT>(mb, mk, lds, wave, lane, C);
+        mfma_rows<K, W, MT, NT>(lds);
+        mfma_load_tiles<K, W, MT, NT>(mb, mk, lds, wave, lane, C);
+    }
+    // single-wave shapes load the operands before they wait for the tiles
     MState<MT, NT> a, b;
 #pragma unroll
     for (int mt = 0; mt < MT; mt++) {
-        const size_t sl = (size_t)wave * MT + mt;
         const int ch = wave * S::CH + 4 * mt + g;
         const bool real = (4 * mt + g != 4 * MT - 1) && ch < K;
-        const uint32_t inB = mb[S::LY.mmconv() + (sl * 3 + 0) * 64 + lane];
-        const uint32_t inP = mb[S::LY.mmconv() + (sl * 3 + 1) * 64 + lane];
-        const MSlotB sb = C.slotB(mt);
-        const MSlotP sp = C.slotP(mt);
 #pragma unroll
         for (int nt = 0; nt < NT; nt++) {
             const bool ld = real && ok[nt];
             const size_t e = (size_t)elem[nt];
-            a.b[mt][nt] = mulredc(ld ? x[(size_t)ch * B + e] : 0u, inB, sb.m, sb.u);   // x R mod m
-            b.b[mt][nt] = mulredc(ld ? y[(size_t)ch * B + e] : 0u, inB, sb.m, sb.u);
-            a.p[mt][nt] = mulredc(ld ? x[(size_t)(K + ch) * B + e] : 0u, inP, sp.m, sp.u);   // x R M^-1 mod m'
-            b.p[mt][nt] = mulredc(ld ? y[(size_t)(K + ch) * B + e] : 0u, inP, sp.m, sp.u);
+            a.b[mt][nt] = ld ? x[(size_t)ch * B + e] : 0u;
+            b.b[mt][nt] = ld ? y[(size_t)ch * B + e] : 0u;
+            a.p[mt][nt] = ld ? x[(size_t)(K + ch) * B + e] : 0u;
+            b.p[mt][nt] = ld ? y[(size_t)(K + ch) * B + e] : 0u;
         }
     }
 #pragma unroll
     for (int nt = 0; nt < NT; nt++) {
         a.r[nt] = ok[nt] ? x[(size_t)2 * K * B + elem[nt]] : 0u;
         b.r[nt] = ok[nt] ? y[(size_t)2 * K * B + elem[nt]] : 0u;
+    }
+    if constexpr (S::WAVE) {
+        C.setup(mb, mk, lds, lane);
+        __syncthreads();
+        C.load_tiles();
+    }
+#pragma unroll
+    for (int mt = 0; mt < MT; mt++) {
+        const size_t sl = (size_t)wave * MT + mt;
+        const uint32_t inB = mb[S::LY.mmconv() + (sl * 3 + 0) * 64 + lane];
+        const uint32_t inP = mb[S::LY.mmconv() + (sl * 3 + 1) * 64 + lane];
+        const MSlotB sb = C.slotB(mt);
+        const MSlotP sp = C.slotP(mt);
+#pragma unroll
+        for (int nt = 0; nt < NT; nt++) {
+            a.b[mt][nt] = mulredc(a.b[mt][nt], inB, sb.m, sb.u);                       // x R mod m
+            b.b[mt][nt] = mulredc(b.b[mt][nt], inB, sb.m, sb.u);
+            a.p[mt][nt] = mulredc(a.p[mt][nt], inP, sp.m, sp.u);                       // x R M^-1 mod m'
+            b.p[mt][nt] = mulredc(b.p[mt][nt], inP, sp.m, sp.u);
+        }
     }
     if constexpr (S::WAVE) {
         C.x = a;
@@ -1271,21 +1314,125 @@ __global__ __launch_bounds__((MShp<K, W, MT, NT>::THREADS)) void montmul_mfma_ke
         for (int nt = 0; nt < NT; nt++) {
             if (!real || !ok[nt]) continue;
             const size_t e = (size_t)elem[nt];
-            out[(size_t)ch * B + e] = mulredc(a.b[mt][nt], 1u, sb.m, sb.u);
-            out[(size_t)(K + ch) * B + e] = mulredc(a.p[mt][nt], outP, sp.m, sp.u);
+            uint32_t vb = mulredc(a.b[mt][nt], 1u, sb.m, sb.u), vp = mulredc(a.p[mt][nt], outP, sp.m, sp.u);
+            if constexpr (S::LY.wide()) {
+                vb = mm_less(vb, mk[S::LY.mmfix() + (sl * 2 + 0) * 64 + lane], sb.m);
+                vp = mm_less(vp, mk[S::LY.mmfix() + (sl * 2 + 1) * 64 + lane], sp.m);
+            }
+            out[(size_t)ch * B + e] = vb;
+            out[(size_t)(K + ch) * B + e] = vp;
         }
     }
     if (wave == 0 && g == 0)
 #pragma unroll
         for (int nt = 0; nt < NT; nt++)
-            if (ok[nt]) out[(size_t)2 * K * B + elem[nt]] = a.r[nt];
+            if (ok[nt]) out[(size_t)2 * K * B + elem[nt]] = a.r[nt] - (S::LY.wide() ? mk[S::LY.kscal() + 2] : 0u);
+}
+
+// The same on a team: the part of a wave with TW tiles.
+template <int K, int MT, int NT, int TW>
+__device__ __forceinline__ void montmul_team_part(const MontMulMfmaLaunch &A, uint32_t *lds) {
+    using S = MShp<K, 1, MT, NT>;
+    const gu32 *__restrict__ mb = (const gu32 *)A.mb;
+    const gu32 *__restrict__ mk = (const gu32 *)A.mk;
+    const gu32 *__restrict__ x = (const gu32 *)A.x;
+    const gu32 *__restrict__ y = (const gu32 *)A.y;
+    gu32 *__restrict__ out = (gu32 *)A.out;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+    const int te = A.tile_elems > 0 && A.tile_elems < S::NM ? A.tile_elems : S::NM;
+    const size_t B = (size_t)A.batch;
+    int elem[NT];
+    bool ok[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; nt++) {
+        const int n = 16 * nt + (lane & 15);
+        elem[nt] = (int)blockIdx.x * te + n;
+        ok[nt] = n < te && elem[nt] < A.batch;
+    }
+    const int tile0 = S::team_tile0(wave);
+    MState<TW, NT> a, b;                            // the operands first, as above
+#pragma unroll
+    for (int t = 0; t < TW; t++) {
+        const int ch = 4 * (tile0 + t) + (lane >> 4);
+#pragma unroll
+        for (int nt = 0; nt < NT; nt++) {
+            const bool ld = ch < K && ok[nt];
+            const size_t e = (size_t)elem[nt];
+            a.b[t][nt] = ld ? x[(size_t)ch * B + e] : 0u;
+            b.b[t][nt] = ld ? y[(size_t)ch * B + e] : 0u;
+            a.p[t][nt] = ld ? x[(size_t)(K + ch) * B + e] : 0u;
+            b.p[t][nt] = ld ? y[(size_t)(K + ch) * B + e] : 0u;
+        }
+    }
+#pragma unroll
+    for (int nt = 0; nt < NT; nt++) {
+        a.r[nt] = ok[nt] ? x[(size_t)2 * K * B + elem[nt]] : 0u;
+        b.r[nt] = ok[nt] ? y[(size_t)2 * K * B + elem[nt]] : 0u;
+    }
+    TeamEngine<K, MT, NT, false, TW> C;
+    C.setup(mb, mk, lds, wave, lane);
+    __syncthreads();
+    C.load_constants(lds);
+    C.load_tiles(mb, mk);
+#pragma unroll
+    for (int t = 0; t < TW; t++) {
+        const size_t sl = (size_t)tile0 + t;
+        const uint32_t inB = mb[S::LY.mmconv() + (sl * 3 + 0) * 64 + lane];
+        const uint32_t inP = mb[S::LY.mmconv() + (sl * 3 + 1) * 64 + lane];
+        const MSlotB sb = C.slotB(t);
+        const MSlotP sp = C.slotP(t);
+#pragma unroll
+        for (int nt = 0; nt < NT; nt++) {
+            C.x.b[t][nt] = mulredc(a.b[t][nt], inB, sb.m, sb.u);
+            b.b[t][nt] = mulredc(b.b[t][nt], inB, sb.m, sb.u);
+            C.x.p[t][nt] = mulredc(a.p[t][nt], inP, sp.m, sp.u);
+            b.p[t][nt] = mulredc(b.p[t][nt], inP, sp.m, sp.u);
+        }
+    }
+#pragma unroll
+    for (int nt = 0; nt < NT; nt++) C.x.r[nt] = a.r[nt];
+    C.template product<true>(MRegOperand<TW, NT>{b});
+#pragma unroll
+    for (int t = 0; t < TW; t++) {
+        const size_t sl = (size_t)C.tile0 + t;
+        const int ch = 4 * (int)sl + (lane >> 4);
+        const uint32_t outP = mb[S::LY.mmconv() + (sl * 3 + 2) * 64 + lane];
+        const MSlotB sb = C.slotB(t);
+        const MSlotP sp = C.slotP(t);
+#pragma unroll
+        for (int nt = 0; nt < NT; nt++) {
+            if (ch >= K || !ok[nt]) continue;
+            const size_t e = (size_t)elem[nt];
+            out[(size_t)ch * B + e] = mm_less(mulredc(C.x.b[t][nt], 1u, sb.m, sb.u),
+                                              mk[S::LY.mmfix() + (sl * 2 + 0) * 64 + lane], sb.m);
+            out[(size_t)(K + ch) * B + e] = mm_less(mulredc(C.x.p[t][nt], outP, sp.m, sp.u),
+                                                    mk[S::LY.mmfix() + (sl * 2 + 1) * 64 + lane], sp.m);
+        }
+    }
+    if (wave == S::TEAM_WAVES - 1 && lane < 16)   // the last wave keeps the redundant residue
+#pragma unroll
+        for (int nt = 0; nt < NT; nt++)
+            if (ok[nt]) out[(size_t)2 * K * B + elem[nt]] = C.x.r[nt] - mk[S::LY.kscal() + 2];
+}
+
+template <int K, int MT, int NT>
+__global__ __launch_bounds__(512) void montmul_team_kernel(MontMulMfmaLaunch A) {
+    using S = MShp<K, 1, MT, NT>;
+    __shared__ __attribute__((aligned(16))) uint32_t lds[S::TEAM_OPERANDS];
+    if (__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) < S::TEAM_EXTRA)
+        montmul_team_part<K, MT, NT, S::TEAM_BASE + 1>(A, lds);
+    else
+        montmul_team_part<K, MT, NT, S::TEAM_BASE>(A, lds);
 }
 
 template <int K, int W, int MT, int NT>
 hipError_t launch_montmul_mfma_t(const MontMulMfmaLaunch &a, hipStream_t s) {
     using S = MShp<K, W, MT, NT>;
     if (a.tiles <= 0) return hipSuccess;
-    hipLaunchKernelGGL((montmul_mfma_kernel<K, W, MT, NT>), dim3((unsigned)S::LY.groups(a.tiles)), dim3(S::THREADS), 0, s, a);
+    if constexpr (S::LY.team())
+        hipLaunchKernelGGL((montmul_team_kernel<K, MT, NT>), dim3((unsigned)a.tiles), dim3(512), 0, s, a);
+    else
+        hipLaunchKernelGGL((montmul_mfma_kernel<K, W, MT, NT>), dim3((unsigned)S::LY.groups(a.tiles)), dim3(S::THREADS), 0, s, a);
     return hipGetLastError();
 }
 
@@ -1294,6 +1441,7 @@ template <int K, int W, int MT, int NT>
 int mfma_blocks_per_cu_t() {
     int n = 0;
     using S = MShp<K, W, MT, NT>;
+    if constexpr (!S::LY.team())
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, modexp_mfma_kernel<K, W, MT, NT, false>, S::THREADS, 0) != hipSuccess)
         return 0;
     return n * (S::WAVE ? S::WAVE_GROUP : 1);

@@ -53,6 +53,30 @@ __device__ __forceinline__ void lane_groups_23(uint32_t v, uint32_t &g2, uint32_
     g3 = r[1];
 }
 
+// The slots' constants into LDS, [MT][4 lane groups][2][4]: B {m, m^-1 (SQ: -m^-1)
+// mod 2^32, nu, c (wide: nu2)}, B' {m, m^-1, H, 0 (wide: m 2^OSH)}.
+template <int K, int MT, int NT, bool SQ>
+__device__ __forceinline__ void wave_constants(const gu32 *__restrict__ mb, const gu32 *__restrict__ mk, uint32_t *c,
+                                               int threads) {
+    using S = MShp<K, 1, MT, NT>;
+    constexpr bool WIDE = SQ && S::LY.wide();
+    for (int i = threadIdx.x; i < MT * 32; i += threads) {
+        const int f = i & 7, mt = i >> 5, ln = 16 * ((i >> 3) & 3);
+        uint32_t v = 0;
+        if (f < 4) {
+            if (f < 2 || !SQ) v = f < 3 ? mb[S::LY.slotB() + (mt * 3 + f) * 64 + ln] : mk[S::LY.slotC() + mt * 64 + ln];
+            else v = mk[S::LY.sqB() + (mt * 4 + (f == 2 ? 0 : 3)) * 64 + ln];
+            if (SQ && f == 1) v = 0u - v;
+        } else if (f < 6 || !WIDE) {
+            if (f < 7) v = mb[S::LY.slotP() + (mt * 4 + (f - 4)) * 64 + ln];
+        } else {
+            const uint64_t off = (uint64_t)mb[S::LY.slotP() + mt * 4 * 64 + ln] << S::OSH;
+            v = f == 6 ? (uint32_t)off : (uint32_t)(off >> 32);
+        }
+        c[i] = v;
+    }
+}
+
 template <int K, int MT, int NT, bool SQ>
 struct WaveEngine {
     using S = MShp<K, 1, MT, NT>;
@@ -83,8 +107,6 @@ struct WaveEngine {
 
     Digits d2[NT];                       // xi' (WIDE: the kept residues) of the last product
 
-    // A slot's constants: B {m, m^-1 (SQ: -m^-1) mod 2^32, nu, c (WIDE: nu2)}, B'
-    // {m, m^-1, H, 0 (WIDE: m 2^OSH)}.
     __device__ __forceinline__ uint4 cB(int mt) const { return *(const uint4 *)(cl + 32 * mt); }
     __device__ __forceinline__ uint4 cP(int mt) const { return *(const uint4 *)(cl + 32 * mt + 4); }
     __device__ __forceinline__ MSlotB slotB(int mt) const {
@@ -110,21 +132,7 @@ struct WaveEngine {
         A1 = t + lane;
         A2 = t + NQ + lane;
         uint32_t *c = lds + 2 * NQ * 4;
-        for (int i = threadIdx.x; i < MT * 32; i += 64 * S::WAVE_GROUP) {
-            const int f = i & 7, mt = i >> 5, ln = 16 * ((i >> 3) & 3);
-            uint32_t v = 0;
-            if (f < 4) {
-                if (f < 2 || !SQ) v = f < 3 ? mb[S::LY.slotB() + (mt * 3 + f) * 64 + ln] : mk[S::LY.slotC() + mt * 64 + ln];
-                else v = mk[S::LY.sqB() + (mt * 4 + (f == 2 ? 0 : 3)) * 64 + ln];
-                if (SQ && f == 1) v = 0u - v;
-            } else if (f < 6 || !WIDE) {
-                if (f < 7) v = mb[S::LY.slotP() + (mt * 4 + (f - 4)) * 64 + ln];
-            } else {
-                const uint64_t off = (uint64_t)mb[S::LY.slotP() + mt * 4 * 64 + ln] << S::OSH;
-                v = f == 6 ? (uint32_t)off : (uint32_t)(off >> 32);
-            }
-            c[i] = v;
-        }
+        wave_constants<K, MT, NT, SQ>(mb, mk, c, 64 * S::WAVE_GROUP);
         cl = c + 8 * (lane >> 4);
         Mpinv_r = mb[S::LY.bscal() + 0];
         Minv_r = mb[S::LY.bscal() + 1];
@@ -440,6 +448,219 @@ struct SplitEngine {
     }
 };
 
+// The product on a team of 8 waves (k = 65 and 66), for bases whose tiles do not fit
+// one wave's share of LDS: a wave has MT / 8 tiles, the first MT % 8 one more, so
+// that at k = 65 a SIMD's two waves hold at most five of the 17 (six waves of three,
+// as before, left two SIMDs with six).  Tiles are in registers but, at three per
+// wave, L1 + L2 of the wave's and, for every wave, the redundant one, which all
+// compute: those are in LDS.  Digit words pass through LDS as [k-step][lane][4],
+// the layout of the operands.  Otherwise as SplitEngine.
+//
+// With both extensions' tiles split over six waves of 11 channels and a redundant
+// row each, without the wide form -> this: RSA-4096, one decryption 3.05 -> 2.48 ms,
+// 4,096 in 4.98 -> 4.37 ms; 10,007 RSA-2048 encryptions 145 -> 130 us.
+template <int K, int MT, int NT, bool SQ, int TW>
+struct TeamEngine {
+    using S = MShp<K, 1, MT, NT>;
+    static constexpr int KS = S::KSTEPS, WV = S::TEAM_WAVES;
+    // tiles of the first and second extension kept in LDS, not in registers
+    static constexpr int L1 = TW == 3 ? S::TEAM_L1 : 0, L2 = TW == 3 ? S::TEAM_L2 : 0;
+    static constexpr int T1 = TW - L1, T2 = TW - L2;
+    static_assert(S::LY.wide() && 4 * KS > MT, "a digit word for the offset");
+
+    mfma_v4i A1[T1][KS], A2[T2][KS];
+    const mfma_v4i *lt;                        // LDS tiles: the second extension's last, the first wave's L2, its L1; + lane
+    uint4 cb[TW], cp[TW];                      // slot constants (wave_constants)
+    uint32_t Mpinv_r, Minv_r, N_r;
+    int32_t est_r, kf[4];
+    MState<TW, NT> x;
+    int lane, wave, tile0;
+    uint32_t *buf;                             // [2][NT][KS][64][4] digit words, [NT][64] redundant residues, + 4 lane
+
+    __device__ __forceinline__ MSlotB slotB(int t) const {
+        return MSlotB{cb[t].x, SQ ? 0u - cb[t].y : cb[t].y, cb[t].z, cb[t].w};
+    }
+    __device__ __forceinline__ MSlotP slotP(int t) const { return MSlotP{cp[t].x, cp[t].y, cp[t].z, 0u}; }
+
+    // lds: the constants and tiles, then the exchange buffer; a barrier and
+    // load_constants follow.
+    __device__ __forceinline__ void setup(const gu32 *__restrict__ mb, const gu32 *__restrict__ mk, uint32_t *lds, int wv, int l) {
+        lane = l;
+        wave = wv;
+        tile0 = S::team_tile0(wv);
+        wave_constants<K, MT, NT, SQ>(mb, mk, lds, 64 * WV);
+        mfma_v4i *t = (mfma_v4i *)(lds + 32 * MT);
+        lt = t + lane;
+        gcv4i *a1 = (gcv4i *)(mk + S::LY.a1()), *a2 = (gcv4i *)(SQ ? mk + S::LY.a2s() : mb + S::LY.a2());
+        for (int i = threadIdx.x; i < S::TEAM_TILES * KS * 64; i += 64 * WV) {
+            const int z = i / (KS * 64), r = i % (KS * 64);
+            t[i] = z == 0              ? a2[(MT - 1) * KS * 64 + r]
+                   : z <= S::TEAM_L2 ? a2[(3 - S::TEAM_L2 + z - 1) * KS * 64 + r]
+                                      : a1[(3 - S::TEAM_L1 + z - 1 - S::TEAM_L2) * KS * 64 + r];
+        }
+        buf = lds + 32 * MT + S::TEAM_TILES * KS * 256 + 4 * lane;
+        hp = mb + S::LY.slotP() + (tile0 * 4 + 2) * 64 + lane;
+        for (int i = threadIdx.x; i < 2 * NT * (4 * KS - MT) * 64; i += 64 * WV) {   // the offset digit
+            const int z = i / 64, wd = MT + z % (4 * KS - MT), h = z / (4 * KS - MT);
+            (buf - 4 * lane)[(h * KS + wd / 4) * 256 + (i % 64) * 4 + wd % 4] = 1u;
+        }
+        Mpinv_r = mb[S::LY.bscal() + 0];
+        Minv_r = mb[S::LY.bscal() + 1];
+        N_r = mk[S::LY.kscal() + 0];
+        est_r = (int32_t)mk[S::LY.kscal() + 1];
+#pragma unroll
+        for (int b = 0; b < 4; b++) {
+            kf[b] = 1 << (8 * b);
+            asm volatile("" : "+s"(kf[b]));
+        }
+    }
+    __device__ __forceinline__ void load_constants(const uint32_t *lds) {
+#pragma unroll
+        for (int t = 0; t < TW; t++) {
+            const uint32_t *c = lds + 32 * (tile0 + t) + 8 * (lane >> 4);
+            cb[t] = *(const uint4 *)c;
+            cp[t] = *(const uint4 *)(c + 4);
+        }
+    }
+    __device__ __forceinline__ void load_tiles(const gu32 *__restrict__ mb, const gu32 *__restrict__ mk) {
+        gcv4i *a1 = (gcv4i *)(mk + S::LY.a1()), *a2 = (gcv4i *)(SQ ? mk + S::LY.a2s() : mb + S::LY.a2());
+#pragma unroll
+        for (int ks = 0; ks < KS; ks++) {
+#pragma unroll
+            for (int t = 0; t < TW; t++) {
+                if (t < T1) A1[t < T1 ? t : 0][ks] = mfma_tile_load(a1, (tile0 + t) * KS + ks, 16u * lane);
+                if (t < T2) A2[t < T2 ? t : 0][ks] = mfma_tile_load(a2, (tile0 + t) * KS + ks, 16u * lane);
+            }
+        }
+    }
+    // All digit words of this lane, as the operands of the k-steps.
+    __device__ __forceinline__ void gather(int which, mfma_v4i (&w)[NT][KS]) const {
+#pragma unroll
+        for (int nt = 0; nt < NT; nt++)
+#pragma unroll
+            for (int ks = 0; ks < KS; ks++) w[nt][ks] = *(const mfma_v4i *)(buf + ((which * NT + nt) * KS + ks) * 256);
+    }
+    __device__ __forceinline__ void publish(int which, int t, int nt, uint32_t v) const {
+        const int mt = tile0 + t;
+        buf[((which * NT + nt) * KS + mt / 4) * 256 + mt % 4] = mfma_pack(v);
+    }
+    __device__ __forceinline__ uint32_t *shared_r(int nt) const { return buf - 3 * lane + (2 * KS * NT * 4 + nt) * 64; }
+    // FULL = false: the exit product, which leaves the digits xi' in the second buffer
+    template <bool FULL, class Y>
+    __device__ __forceinline__ void product(const Y &y) {
+        int zo;                                  // see WaveEngine::extension
+        asm volatile("s_mov_b32 %0, 0" : "=s"(zo));
+        const mfma_v4i *lz = lt + zo;
+#pragma unroll
+        for (int t = 0; t < TW; t++) {
+            const uint4 c = cb[t];
+#pragma unroll
+            for (int nt = 0; nt < NT; nt++) {
+                uint32_t xi;
+                if constexpr (SQ) xi = redc_any((uint64_t)x.b[t][nt] * y.b(t, nt), c.x, c.y);
+                else xi = mulredc(mulredc(x.b[t][nt], y.b(t, nt), c.x, c.y), c.w, c.x, c.y);
+                publish(0, t, nt, xi);
+            }
+        }
+        __syncthreads();
+        mfma_v4i w[NT][KS], D[TW][NT], R[NT];
+        gather(0, w);
+#pragma unroll
+        for (int t = 0; t < TW; t++)
+#pragma unroll
+            for (int nt = 0; nt < NT; nt++) D[t][nt] = mfma_v4i{0, 0, 0, 0};
+#pragma unroll
+        for (int ks = 0; ks < KS; ks++)
+#pragma unroll
+            for (int t = 0; t < TW; t++) {
+                const mfma_v4i a = t < T1 ? A1[t < T1 ? t : 0][ks] : lz[((1 + L2 + t - T1) * KS + ks) * 64];
+#pragma unroll
+                for (int nt = 0; nt < NT; nt++)
+                    D[t][nt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, w[nt][ks], D[t][nt], 0, 0, 0);
+            }
+        uint32_t lo1[NT];
+        if (wave == WV - 1)
+#pragma unroll
+            for (int nt = 0; nt < NT; nt++)
+                lo1[nt] = (uint32_t)__builtin_amdgcn_ds_bpermute(((lane & 15) + 48) * 4, (int)mfma_combine_lo(D[TW - 1][nt]));
+#pragma unroll
+        for (int t = 0; t < TW; t++) {
+            const uint4 c = cp[t];
+            const uint64_t off = SQ ? ((uint64_t)c.w << 32) | c.z : (uint64_t)c.x << S::OSH;
+            uint32_t H = c.z;
+            // the exit takes xi' = r H, whose factor the wide form has no place for
+            if (SQ && !FULL) H = ((const gu32 *)hp)[t * 4 * 64];
+#pragma unroll
+            for (int nt = 0; nt < NT; nt++) {
+                const uint64_t T = mfma_accumulate<S::PAIR_I32>(D[t][nt], (uint64_t)x.p[t][nt] * y.p(t, nt) + off, kf);
+                const uint32_t r = redc((uint32_t)T, (uint32_t)(T >> 32), c.x, c.y);
+                x.p[t][nt] = r;
+                publish(1, t, nt, SQ && FULL ? r : mulredc(r, H, c.x, c.y));
+            }
+        }
+        if (wave == WV - 1)
+#pragma unroll
+            for (int nt = 0; nt < NT; nt++) {
+                x.r[nt] = (x.r[nt] * y.r(nt) + lo1[nt] * N_r) * Minv_r;
+                *shared_r(nt) = x.r[nt];
+            }
+        __syncthreads();
+        if constexpr (!FULL) return;
+        gather(1, w);
+#pragma unroll
+        for (int nt = 0; nt < NT; nt++) R[nt] = mfma_v4i{0, 0, 0, 0};
+#pragma unroll
+        for (int t = 0; t < TW; t++)
+#pragma unroll
+            for (int nt = 0; nt < NT; nt++) D[t][nt] = mfma_v4i{0, 0, 0, 0};
+#pragma unroll
+        for (int ks = 0; ks < KS; ks++)
+#pragma unroll
+            for (int nt = 0; nt < NT; nt++)
+                R[nt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(lz[ks * 64], w[nt][ks], R[nt], 0, 0, 0);
+#pragma unroll
+        for (int ks = 0; ks < KS; ks++)
+#pragma unroll
+            for (int t = 0; t < TW; t++) {
+                const mfma_v4i a = t < T2 ? A2[t < T2 ? t : 0][ks] : lz[((1 + t - T2) * KS + ks) * 64];
+#pragma unroll
+                for (int nt = 0; nt < NT; nt++)
+                    D[t][nt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, w[nt][ks], D[t][nt], 0, 0, 0);
+            }
+        uint32_t al[NT], ah[NT];
+#pragma unroll
+        for (int nt = 0; nt < NT; nt++) {
+            const uint32_t rr = *shared_r(nt);
+            const uint32_t lo =
+                ((uint32_t)__builtin_amdgcn_ds_bpermute(((lane & 15) + 48) * 4, (int)mfma_combine_lo(R[nt])) - rr) * Mpinv_r;
+            al[nt] = lo, ah[nt] = 0;
+            if constexpr (SQ) {
+                const int32_t est = __builtin_amdgcn_ds_bpermute(((lane & 15) + 32) * 4, R[nt][0]);
+                const int32_t h = (est + est_r - (int32_t)(lo >> 18)) >> 14;
+                ah[nt] = ((uint32_t)h << (32 - kWideShift)) + (lo >> kWideShift);
+                al[nt] = lo & ((1u << kWideShift) - 1);
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < TW; t++) {
+            const uint4 c = cb[t];
+#pragma unroll
+            for (int nt = 0; nt < NT; nt++) {
+                if constexpr (SQ) {
+                    const uint64_t T = mfma_accumulate<S::PAIR_I32>(
+                        D[t][nt], (uint64_t)al[nt] * c.z + (uint64_t)ah[nt] * c.w, kf);
+                    x.b[t][nt] = TW > S::TEAM_BASE && t == 0 ? redc_any(T, c.x, c.y) : redc_small(T, c.x, c.y);
+                } else {
+                    const uint64_t T = mfma_accumulate<S::PAIR_I32>(
+                        D[t][nt], (uint64_t)al[nt] * c.z + ((uint64_t)c.x << S::OSH), kf);
+                    x.b[t][nt] = redc((uint32_t)T, (uint32_t)(T >> 32), c.x, c.y);
+                }
+            }
+        }
+    }
+    const gu32 *hp;                            // H of this lane's slots (base table), [TW][4][64]
+};
+
 // The second operand 1 (see mstate_unit) of the tiles from tile0 on, into an
 // LDS operand buffer (+ lane).
 template <int K, int MT, bool SQ, int M, int NT, class E>
@@ -702,6 +923,68 @@ __device__ __forceinline__ void modexp_split_tile(const MJob &J, int e0, uint32_
     __syncthreads();
     const int left = J.batch - e0, te = mjob_tile_elems(J, 16);
     mfma_exit_limbs<K, 1, MT, 1>(mb, mk, tsum, rl, w.Mpinv_r, wave, WV, lane, J, e0, left < te ? left : te);
+}
+
+// One tile of exponentiation job J on a team: the part of a wave with TW tiles.
+template <int K, int MT, int NT, bool SQ, int TW>
+__device__ __forceinline__ void modexp_team_tile(const MJob &J, int e0, uint32_t *__restrict__ lds,
+                                                  uint32_t *__restrict__ table, size_t slot, int max_window) {
+    using S = MShp<K, 1, MT, NT>;
+    constexpr int WV = S::TEAM_WAVES;
+    const gu32 *__restrict__ mb = (const gu32 *)J.mb;
+    const gu32 *__restrict__ mk = (const gu32 *)J.mk;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int lane = threadIdx.x & 63;
+    uint32_t *yl = lds + S::TEAM_OPERANDS + (2 * S::team_tile0(wave) + wave) * NT * 64;
+    uint32_t *io = lds + S::TEAM_IO;
+    TeamEngine<K, MT, NT, SQ, TW> w;
+    w.setup(mb, mk, lds, wave, lane);
+    mfma_stage_inputs<WV, 16 * NT>(J, e0, io, wave, lane);
+    __syncthreads();
+    w.load_constants(lds);
+    {
+        uint32_t mB[TW], uB[TW], mP[TW], uP[TW];
+#pragma unroll
+        for (int t = 0; t < TW; t++) {
+            const MSlotB sb = w.slotB(t);
+            const MSlotP sp = w.slotP(t);
+            mB[t] = sb.m, uB[t] = sb.u, mP[t] = sp.m, uP[t] = sp.u;
+        }
+        mfma_entry<S::ECOLS, 4 * MT, TW, NT>(J, io, w.tile0, lane, mB, uB, mP, uP, w.x);
+    }
+    w.load_tiles(mb, mk);
+    wave_exponent<K, MT, SQ, TW, NT>(J, e0, w, w.tile0, lane,
+                                     (gu32 *)table + (slot << max_window) * (S::SLOTS * 64) + w.tile0 * 2 * NT * 64 + lane,
+                                     yl, wave == WV - 1);
+
+    // leave the RNS: the last product's digits xi' are in the exchange buffer
+    mfma_v4i d[NT][S::KSTEPS];
+    w.gather(1, d);
+    gcv4i *xt = (gcv4i *)(mb + S::LY.xt());
+    uint64_t *tsum = (uint64_t *)io;
+    uint32_t *rl = io + 2 * 16 * NT * S::XSLOTS;
+#pragma unroll
+    for (int t = 0; t < TW; t++) {
+        mfma_v4i D[NT];
+#pragma unroll
+        for (int nt = 0; nt < NT; nt++) D[nt] = mfma_v4i{0, 0, 0, 0};
+#pragma unroll
+        for (int ks = 0; ks < S::KSTEPS; ks++) {
+            const mfma_v4i a = mfma_tile_load(xt, (w.tile0 + t) * S::KSTEPS + ks, 16u * lane);
+#pragma unroll
+            for (int nt = 0; nt < NT; nt++) D[nt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, d[nt][ks], D[nt], 0, 0, 0);
+        }
+#pragma unroll
+        for (int nt = 0; nt < NT; nt++)
+            tsum[(16 * nt + (lane & 15)) * S::XSLOTS + 4 * (w.tile0 + t) + (lane >> 4)] =
+                mfma_accumulate<S::PAIR_I32>(D[nt], kExitOffset, w.kf);
+    }
+    if (wave == WV - 1 && lane < 16)
+#pragma unroll
+        for (int nt = 0; nt < NT; nt++) rl[16 * nt + lane] = w.x.r[nt];
+    __syncthreads();
+    const int left = J.batch - e0, te = mjob_tile_elems(J, 16 * NT);
+    mfma_exit_limbs<K, 1, MT, NT>(mb, mk, tsum, rl, w.Mpinv_r, wave, WV, lane, J, e0, left < te ? left : te);
 }
 
 }  // namespace rnsrsa

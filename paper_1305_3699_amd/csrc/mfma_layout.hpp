@@ -80,9 +80,11 @@ struct MLayout {
     int K, W, MT, NT;
     // A tile is the 16 NT elements of a workgroup or, in a single-wave shape, of
     // one of its waves; the workgroups of a job of `tiles` tiles.
-    constexpr int groups(int tiles) const { return W == 1 ? (tiles + kWaveGroup - 1) / kWaveGroup : tiles; }
+    constexpr int groups(int tiles) const { return W == 1 && !team() ? (tiles + kWaveGroup - 1) / kWaveGroup : tiles; }
     // Waves of a tile in the split kernel of a single-wave shape (0: it has none).
     constexpr int split_waves() const { return W == 1 && NT == 1 && MT == 9 ? 3 : 0; }
+    // Whether a tile is a workgroup's of 8 waves all the same (TeamEngine).
+    constexpr bool team() const { return W == 1 && MT == 17; }
     constexpr int CH() const { return 4 * MT - 1; }                 // prime channels per wave
     constexpr int KSTEPS() const { return (4 * K + 1 + 63) / 64; }  // 64-deep steps: 4 digits/channel + offset
     constexpr int KCH() const { return KSTEPS() * 16; }             // channels covered by the steps
@@ -144,7 +146,11 @@ struct MLayout {
     // (M mod N) R s (one), nu2 s (wide form)
     constexpr size_t a2s() const { return kscal() + 4; }
     constexpr size_t sqB() const { return a2s() + (sq_ok() ? tiles() : 0); }
-    constexpr size_t key_size() const { return sqB() + (sq_ok() ? (size_t)W * MT * 4 * 64 : 0); }
+    // wide shapes: [MT][2][64] t N mod m_i and mod m'_i by slot (t N mod 2^32 is
+    // kscal[2]), with t the sigma_i = -1: the unscaled product of a wide key
+    // leaves t N more than its definition, as the first extension's offset is 2 m_i M_i there
+    constexpr size_t mmfix() const { return sqB() + (sq_ok() ? (size_t)W * MT * 4 * 64 : 0); }
+    constexpr size_t key_size() const { return mmfix() + (wide() ? (size_t)MT * 2 * 64 : 0); }
     // entry table: per input limb [W*4*MT B slots | W*4*MT B' slots | redundant]
     constexpr size_t ecols() const { return (size_t)2 * W * 4 * MT + 1; }
 };

@@ -418,6 +418,15 @@ MfmaTables make_mfma_tables(const ModPlan &mp, const MfmaShape &sh, bool with_ba
             out.key[ly.kscal() + 1] = (uint32_t)(int32_t)llroundl(bias) + (1u << 13) +
                                       ((uint32_t)kWideOffset >> (32 - kWideShift) << 14);
         }
+        if (wide) {
+            uint32_t t = 0;
+            for (int i = 0; i < K; i++) t += sgn[i] < 0 ? 1 : 0;
+            const Limbs tN = bn_mul(N, Limbs{t});
+            out.key[ly.kscal() + 2] = bn_low(tN);
+            fill_slots(sh, out.key.data() + ly.mmfix(), 2 * 64, [&](int c) { return okc(c) ? bn_mod_word(tN, bs.B[c]) : 0u; });
+            fill_slots(sh, out.key.data() + ly.mmfix() + 64, 2 * 64,
+                       [&](int c) { return okc(c) ? bn_mod_word(tN, bs.Bp[c]) : 0u; });
+        }
         const size_t fq = (size_t)4 * 64;      // [W][MT][4][64]
         fill_slots(sh, out.key.data() + ly.sqB() + 3 * 64, fq, [&](int t) -> uint32_t { return wide && okc(t) ? nu2[t] : 0; });
         fill_slots(sh, out.key.data() + ly.sqB() + 0 * 64, fq, [&](int t) -> uint32_t {

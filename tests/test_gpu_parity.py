@@ -246,12 +246,12 @@ def test_scaled_and_unscaled_b_residues(bits):
 
 
 @pytest.mark.parametrize("bits,counts,opts", [
-    (1024, [15360], {}), (1024, [15361], {}), (1024, [16384], {}), (1024, [16385], {}), (1024, [16403, 1, 65], {}), (1024, [16320, 33, 16], {"group": 32}),
+    (1024, [16128], {}), (1024, [16129], {}), (1024, [16384], {}), (1024, [16385], {}), (1024, [16403, 1, 65], {}), (1024, [16320, 33, 16], {"group": 32}),
     (1024, [5, 17, 47], {}), (1024, [16385, 3], {"unscaled": True}), (1024, [4001], {"unscaled": True}),
     (512, [16387, 1, 64], {}), (512, [17, 2], {"group": 32})])
 def test_single_wave_and_split_launches(bits, counts, opts):
-    """One wave per tile against three (the launch rule's line is 15 tiles of 16
-    elements per 16 SIMDs, 15,360 elements on 256 compute units), jobs that end
+    """One wave per tile against three (the launch rule's line is 63 tiles of 16
+    elements per 64 SIMDs, 16,128 elements on 256 compute units), jobs that end
     inside a workgroup's four tiles, both tiles and both residue forms:
     per-element exponents in the first job, shared ones in the others; every
     output equals the channel engine's, sampled rows the oracle's."""
@@ -343,6 +343,65 @@ def test_garner_in_limbs(half, pbits, count):
     for o, w in zip(ops, want):
         assert np.array_equal(_host(o[3]), w)
     b.close()
+
+
+@pytest.mark.parametrize("bits,counts,opts", [
+    (2048, [1], {}), (2048, [4096], {}), (2048, [4097], {}), (2048, [4097, 31, 33], {}), (2048, [50, 7], {"group": 16}),
+    (2048, [33], {"group": 32, "unscaled": True}), (2048, [4099, 2], {"unscaled": True}), (2080, [40, 1], {}),
+    (2080, [33], {"unscaled": True})])
+def test_team_launches(bits, counts, opts):
+    """The bases of 65 and 66 channels, a tile per team of eight waves, around
+    the launch rule's line (one tile of 16 elements per compute unit, 4,096
+    elements on 256): both tiles and residue forms, ragged ends; per-element
+    exponents in the first job, shared ones in the others; every output equals
+    the channel engine's, sampled rows the oracle's, and so do standalone
+    products."""
+    from paper_1305_3699_amd import ENGINE_CHANNEL, modexp_jobs
+    rng = random.Random(bits + sum(counts))
+    L = bits // 32
+    jobs, refs, mods = [], [], []
+    for i, n in enumerate(counts):
+        N = rng.getrandbits(bits) | (1 << (bits - 1)) | 1
+        bases = np.frombuffer(rng.randbytes(4 * n * L), dtype=np.uint32).reshape(n, L).copy()
+        bases[:, -1] &= 0x7FFFFFFF
+        bases[-1] = gen.to_limbs([[N - 1, 0, 1][i % 3]], L)[0]
+        e = (np.frombuffer(rng.randbytes(4 * n), dtype=np.uint32).reshape(n, 1).copy() if i == 0
+             else gen.to_limbs(rng.getrandbits(70), 3)[0])
+        ctx, ref = _ctx(N, L, **opts), _ctx(N, L, engine=ENGINE_CHANNEL)
+        assert ctx.info["k"] == bits // 32 + 1 and ctx.info["group"] == opts.get("group", 32)
+        jobs.append((ctx, _dev(bases), _dev(e)))
+        refs.append(_run_modexp(ref, bases, e))
+        mods.append((N, bases, e))
+    outs = [_host(o) for o in modexp_jobs(jobs)] if len(jobs) > 1 else [_host(jobs[0][0].modexp(*jobs[0][1:]))]
+    for got, want, (N, bases, e) in zip(outs, refs, mods):
+        assert np.array_equal(got, want)
+        idx = sorted({0, len(bases) - 1, len(bases) // 2})
+        assert np.array_equal(got[idx], oracle.modexp_batch(bases[idx], e[idx] if e.ndim == 2 else e,
+                                                            gen.to_limbs(N, L)[0]))
+    k, n, N = bits // 32 + 1, max(counts), mods[0][0]
+    pr = _indep_base(k, seed=gen.config_seed(6, 4) + k)
+    vals = [rng.randrange((k + 1) * N) for _ in range(2 * min(n, 70))]
+    full = lambda vs: np.array([[v % m for v in vs] for m in pr + [1 << 32]], dtype=np.uint32)
+    half = len(vals) // 2
+    got = _host(_ctx(N, L, primes=pr, **opts).mont_mul(_dev(full(vals[:half])), _dev(full(vals[half:]))))
+    want = full([rns_ref.mont_mul(a, b, N, pr[:k]) for a, b in zip(vals[:half], vals[half:])])
+    assert np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("bits,n,group", [(512, 40, 0), (1024, 67, 0), (1024, 33, 32), (2048, 35, 0), (2048, 17, 16)])
+def test_mont_mul_default_context(bits, n, group):
+    """The standalone product on the default bases, whose keys hold the scaled
+    form: residues exactly as the definition gives them."""
+    rng = random.Random(bits + n)
+    N = rng.getrandbits(bits) | (1 << (bits - 1)) | 1
+    ctx = _ctx(N, bits // 32, group=group)
+    assert ctx.info["scaled"] == 1
+    pr, k = ctx.primes, ctx.info["k"]
+    X = [rng.randrange(1, (k + 1) * N) for _ in range(n)]
+    Y = [rng.randrange(1, (k + 1) * N) for _ in range(n)]
+    res = lambda vs: np.array([[v % m for v in vs] for m in list(pr) + [1 << 32]], dtype=np.uint32)
+    got = _host(ctx.mont_mul(_dev(res(X)), _dev(res(Y))))
+    assert np.array_equal(got, res([rns_ref.mont_mul(x, y, N, pr[:k]) for x, y in zip(X, Y)]))
 
 
 @pytest.mark.parametrize("bits,k", [(64, 3), (128, 5)])
