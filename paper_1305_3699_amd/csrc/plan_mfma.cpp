@@ -35,8 +35,6 @@ int8_t digit(int64_t V, int b) {
     return (int8_t)((int)((u >> (8 * b)) & 0xFFu) - 128);
 }
 
-uint32_t pow2_mod(uint32_t e, uint32_t m) { return powmod32(2, e, m); }
-
 // A square root of a modulo the odd prime p (Tonelli-Shanks; p = 3 mod 4 in
 // one step), or false when a is not a square mod p.
 bool sqrt_mod(uint32_t a, uint32_t p, uint32_t *root) {
@@ -192,7 +190,10 @@ template <class F>
 void fill_slots(const MfmaShape &sh, uint32_t *dst, size_t field_stride, F f) {
     for (int w = 0; w < sh.W; w++)
         for (int mt = 0; mt < sh.MT; mt++)
-            for (int l = 0; l < 64; l++) dst[((size_t)w * sh.MT + mt) * field_stride + l] = f(mfma_slot_channel(sh, w, mt, l / 16));
+            for (int g = 0; g < 4; g++) {
+                const uint32_t v = f(mfma_slot_channel(sh, w, mt, g));
+                std::fill_n(dst + ((size_t)w * sh.MT + mt) * field_stride + 16 * g, 16, v);
+            }
 }
 
 }  // namespace
@@ -268,7 +269,7 @@ MfmaTables make_mfma_tables(const ModPlan &mp, const MfmaShape &sh, bool with_ba
     // Values of the two extensions' constant matrices, [t + 1][i][a] for output
     // channel t (-1: the redundant row), input channel i (K: the offset
     // column, digit a = 0 only) and digit a, computed once: the residues of
-    // M_i = M / m_i modulo a prime m are prod(B) mod m times (m_i mod m)^-1,
+    // M_i = M / m_i modulo a prime m are products of those before and after m_i,
     // and modulo 2^32 prod(B) times m_i^-1 (m_i odd).
     //
     // The digit words carry xi - kDigitBias; the offset column (input channel K,
@@ -303,17 +304,22 @@ MfmaTables make_mfma_tables(const ModPlan &mp, const MfmaShape &sh, bool with_ba
         V[(size_t)K * 4] = balanced32(off_lo);
         for (int t = 0; t < K; t++) {
             const uint32_t m = outm[t], f = scale(t);
-            const uint32_t P = prod_mod32(in, m);
+            uint32_t fa[4];                                            // 2^(8 a) f
+            for (int a = 0; a < 4; a++) fa[a] = mulmod32((1u << (8 * a)) % m, f, m);
+            std::vector<uint32_t> after(K + 1, 1u);                    // products of the inputs from i on
+            for (int i = K - 1; i >= 0; i--) after[i] = mulmod32(after[i + 1], in[i] % m, m);
+            uint32_t before = 1;
             uint64_t off = 0;
             int64_t *row = V.data() + (size_t)(t + 1) * KK;
             for (int i = 0; i < K; i++) {
-                uint32_t mi = mulmod32(P, invmod32(in[i] % m, m), m);
+                uint32_t mi = mulmod32(before, after[i + 1], m);
+                before = mulmod32(before, in[i] % m, m);
                 if (wgt) mi = mulmod32(mi, (*wgt)[i] % m, m);
                 const uint32_t ci = sig[i] < 0 && mi ? m - mi : mi;
                 off = (off + mulmod32(kDigitBias % m, ci, m)) % m;
                 if (sig[i] < 0) off = (off + mulmod32(mulmod32(off_sig, in[i] % m, m), mi, m)) % m;
                 for (int a = 0; a < 4; a++)
-                    row[(size_t)i * 4 + a] = balanced(mulmod32(mulmod32(ci, pow2_mod(8 * a, m), m), f, m), m);
+                    row[(size_t)i * 4 + a] = balanced(mulmod32(ci, fa[a], m), m);
             }
             uint32_t o = mulmod32((uint32_t)off, f, m);
             if (sub) o = (uint32_t)(((uint64_t)o + m - sub(t) % m) % m);
