@@ -270,9 +270,14 @@ MfmaShape auto_tile(const MfmaShape &sh, size_t tiles, int dev, bool small_jobs)
     if (small_jobs) return alt;
     const int simds = device_simds(dev);
     if (!simds) return sh;
-    // a team fills its CU: the 16-element tile (2.48 ms for RSA-4096 decryptions)
-    // while its tiles find a CU each, then the 32-element one (4.37 ms)
-    if (sh.team()) return 2 * tiles <= (size_t)(simds / 4) ? alt : sh;
+    // a team fills its CU, and a round of 16-element tiles takes 4/7 of the time of
+    // one of 32-element tiles (RSA-4096 decryptions: 2.48 and 4.37 ms): the one
+    // whose rounds end first (10,007 RSA-2048 encryptions: 3 of the short rounds 115
+    // us, 2 of the long ones 128; 5,000 RSA-4096 decryptions 7.6 and 8.7 ms)
+    if (sh.team()) {
+        const size_t cus = (size_t)simds / 4, r32 = (tiles + cus - 1) / cus, r16 = (2 * tiles + cus - 1) / cus;
+        return 7 * r32 > 4 * r16 ? alt : sh;
+    }
     // the 32-element tile unless its workgroups cannot fill the resident
     // slots of every CU: then the 16-element tile's twice as many
     // workgroups give the SIMDs more waves

@@ -346,7 +346,7 @@ def test_garner_in_limbs(half, pbits, count):
 
 
 @pytest.mark.parametrize("bits,counts,opts", [
-    (2048, [1], {}), (2048, [4096], {}), (2048, [4097], {}), (2048, [4097, 31, 33], {}), (2048, [50, 7], {"group": 16}),
+    (2048, [1], {}), (2048, [4096], {}), (2048, [4097], {}), (2048, [8225], {}), (2048, [4097, 31, 33], {}), (2048, [50, 7], {"group": 16}),
     (2048, [33], {"group": 32, "unscaled": True}), (2048, [4099, 2], {"unscaled": True}), (2080, [40, 1], {}),
     (2080, [33], {"unscaled": True})])
 def test_team_launches(bits, counts, opts):
