@@ -31,6 +31,8 @@ PEAK_MUL_PER_S = 256 * 64 * 2.4e9
 PEAK_I8_OPS_PER_S = 5.0e15
 ENGINE_NAMES = {1: "channel", 2: "matrix"}
 KERNEL_SOURCES = ["paper_1305_3699_amd/csrc/kernels_impl.hpp", "paper_1305_3699_amd/csrc/arith.hpp",
+                  "paper_1305_3699_amd/csrc/kernels_wave.hpp", "paper_1305_3699_amd/csrc/garner.cpp",
+                  "paper_1305_3699_amd/csrc/limbs.hpp",
                   "paper_1305_3699_amd/csrc/kernel_configs.inc", "paper_1305_3699_amd/csrc/kernels_mfma.hpp",
                   "paper_1305_3699_amd/csrc/mfma_layout.hpp", "paper_1305_3699_amd/csrc/kernel_configs_mfma.inc",
                   "paper_1305_3699_amd/build.py"]

@@ -298,8 +298,8 @@ int rsa_decrypt(const rsa_key *key, const uint32_t *c, uint32_t *m, size_t batch
  *   the window table of each exponentiation (2^w entries of the kernel's
  *   residue slots, a little over 2k+1 words, rounded up to whole workgroup
  *   tiles), two of them for CRT, plus 8 * half_limbs bytes of CRT
- *   intermediates.  RSA-2048 CRT (k = 33): about 43 KB per ciphertext at
- *   window 6 and 22 KB at window 5, i.e. up to about 1,500 and 3,000
+ *   intermediates.  RSA-2048 CRT (k = 33): about 39 KB per ciphertext at
+ *   window 6 and 20 KB at window 5, i.e. up to about 1,700 and 3,400
  *   ciphertexts per call.
  *   Sharing: every call on one device uses the same array, which keeps the
  *   last call's contents; calls that overlap on one device (two streams,
