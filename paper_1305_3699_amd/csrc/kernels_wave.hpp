@@ -15,13 +15,13 @@
 // so a single wave keeps both units busy, with two tiles' results in registers
 // instead of all of them.
 //
-// What bounds it: the vector instructions, about 13 of a slot's 26 being
-// quarter-rate multiply-adds; the matrix instructions (27 of 16 cycles per
-// product at k = 33) run beside them.  Three waves with three tiles each, digits
+// What bounds it: vector issue, about 330 instructions a product at k = 33, a third
+// of them quarter-rate multiply-adds, beside 54 matrix instructions of 16 cycles.
+// Three waves with three tiles each, digits
 // exchanged through LDS between two barriers, kept the vector unit 58% and the
 // matrix cores 28% busy, hardly at the same time.  RSA-2048 CRT decryptions
-// (k = 33): 16,384 in 3.17 -> 2.53 ms, 32,768 in 6.96 -> 4.95 ms; RSA-1024 (k =
-// 17) 16,384 in 1.04 -> 0.79 ms, 32,768 in 2.13 -> 1.42 ms.
+// (k = 33): 16,384 in 3.17 -> 2.45 ms, 32,768 in 6.96 -> 4.93 ms; RSA-1024 (k =
+// 17) 16,384 in 1.04 -> 0.70 ms.
 #pragma once
 
 namespace rnsrsa {
@@ -312,8 +312,8 @@ struct WaveEngine {
 // residue with its digits xi', and the other waves compute the second
 // extension's last tile (redundant and estimate rows) too, so a product has
 // two barriers.  A product's chain (two contractions, two reductions, two
-// exchanges) bounds it, 0.80 us alone on its SIMDs; a lone RSA-2048 decryption
-// takes 1.00 ms here and 1.69 ms on one wave.
+// exchanges) bounds it, 0.75 us alone on its SIMDs; a lone RSA-2048 decryption
+// takes 0.91 ms here and 1.6 ms on one wave.
 template <int K, int MT, int WV, bool SQ>
 struct SplitEngine {
     static constexpr int NT = 1, TW = MT / WV;
