@@ -72,6 +72,7 @@ struct MShp {
     static constexpr int WAVE_IO_WORDS = 16 * (2 * K + 1) > (2 * XSLOTS + 1) * 16 ? 16 * (2 * K + 1) : (2 * XSLOTS + 1) * 16;
     static constexpr int WAVE_WORDS = ((WAVE_IO_WORDS > SLOTS * 64 ? WAVE_IO_WORDS : SLOTS * 64) + 3) & ~3;
     static constexpr int WAVE_TILE_WORDS = 2 * MT * KSTEPS * 64 * 4 + MT * 32;
+    static constexpr int WAVE_MM_WORDS = (NT == 1 ? 1 : 2) * MT * KSTEPS * 64 * 4 + MT * 32;   // a standalone product's
     static constexpr int WORK_WORDS = EXIT_WORDS > BUF_WORDS ? EXIT_WORDS : BUF_WORDS;
     // Where the second extension's constant tiles (the same for every key of
     // the base pair) live: registers for 32-element tiles with few k-steps;
@@ -1226,7 +1227,7 @@ __device__ __forceinline__ uint32_t mm_less(uint32_t v, uint32_t f, uint32_t m) 
 template <int K, int W, int MT, int NT>
 __global__ __launch_bounds__((MShp<K, W, MT, NT>::THREADS)) void montmul_mfma_kernel(MontMulMfmaLaunch A) {
     using S = MShp<K, W, MT, NT>;
-    __shared__ __attribute__((aligned(16))) uint32_t lds[S::LDS_WORDS];
+    __shared__ __attribute__((aligned(16))) uint32_t lds[S::WAVE ? S::WAVE_MM_WORDS : S::LDS_WORDS];
     const gu32 *__restrict__ mb = (const gu32 *)A.mb;
     const gu32 *__restrict__ mk = (const gu32 *)A.mk;
     const gu32 *__restrict__ x = (const gu32 *)A.x;
@@ -1248,7 +1249,7 @@ __global__ __launch_bounds__((MShp<K, W, MT, NT>::THREADS)) void montmul_mfma_ke
         elem[nt] = tile * te + n;
         ok[nt] = n < te && elem[nt] < A.batch;
     }
-    std::conditional_t<S::WAVE, WaveEngine<K, MT, NT, false>, MConstOf<K, W, MT, NT>> C;
+    std::conditional_t<S::WAVE, WaveEngine<K, MT, NT, false, true>, MConstOf<K, W, MT, NT>> C;
     if constexpr (!S::WAVE) {
         mfma_setup<K, W, MT, NT>(mb, mk, lds, wave, lane, C);
         mfma_rows<K, W, MT, NT>(lds);

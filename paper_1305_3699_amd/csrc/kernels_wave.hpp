@@ -77,7 +77,7 @@ __device__ __forceinline__ void wave_constants(const gu32 *__restrict__ mb, cons
     }
 }
 
-template <int K, int MT, int NT, bool SQ>
+template <int K, int MT, int NT, bool SQ, bool ONCE = false>
 struct WaveEngine {
     using S = MShp<K, 1, MT, NT>;
     static constexpr int KS = S::KSTEPS;
@@ -86,7 +86,11 @@ struct WaveEngine {
 
     const mfma_v4i *A1, *A2;             // LDS: the extensions' tiles [MT][KS][64], + lane
     mfma_v4i R1[MT][KS];                 // A1REG: the first extension's in registers
-    static constexpr bool A1REG = NT == 1;
+    // ONCE: a single product, whose tiles of the first extension come from global
+    // memory: 29 instead of 76 KB of LDS and 144 instead of 232 registers let three
+    // waves share a SIMD (40,000 products at k = 33: 17.9 -> 15.2 us, 65,536: 24.6 -> 22.4)
+    static constexpr bool A1GLOBAL = NT == 1 && ONCE, A1REG = NT == 1 && !ONCE;
+    gcv4i *A1g;
     const uint32_t *cl;                  // LDS: the slots' constants [MT][4][2][4], + this lane group's
     uint32_t Mpinv_r, Minv_r, N_r;
     int32_t est_r;                       // the wide form's estimate constant
@@ -126,12 +130,13 @@ struct WaveEngine {
         gcv4i *a1 = (gcv4i *)(mk + S::LY.a1()), *a2 = (gcv4i *)(SQ ? mk + S::LY.a2s() : mb + S::LY.a2());
         mfma_v4i *t = (mfma_v4i *)lds;
         for (int i = threadIdx.x; i < NQ; i += 64 * S::WAVE_GROUP) {
-            t[i] = a1[i];
-            t[NQ + i] = a2[i];
+            t[i] = a2[i];
+            if (!A1GLOBAL) t[NQ + i] = a1[i];
         }
-        A1 = t + lane;
-        A2 = t + NQ + lane;
-        uint32_t *c = lds + 2 * NQ * 4;
+        A2 = t + lane;
+        A1 = t + NQ + lane;
+        A1g = a1 + lane;
+        uint32_t *c = lds + (A1GLOBAL ? 1 : 2) * NQ * 4;
         wave_constants<K, MT, NT, SQ>(mb, mk, c, 64 * S::WAVE_GROUP);
         cl = c + 8 * (lane >> 4);
         Mpinv_r = mb[S::LY.bscal() + 0];
@@ -164,7 +169,13 @@ struct WaveEngine {
 #pragma unroll
                 for (int ks = 0; ks < KS; ks++) R1[mt][ks] = A1[(mt * KS + ks) * 64];
     }
-    template <bool REG, class L, class F>
+    template <bool FIRST>
+    __device__ __forceinline__ mfma_v4i tile(const mfma_v4i *A, int mt, int ks) const {
+        if constexpr (FIRST && A1REG) return R1[mt][ks];
+        else if constexpr (FIRST && A1GLOBAL) return A1g[(mt * KS + ks) * 64];
+        else return A[(mt * KS + ks) * 64];
+    }
+    template <bool FIRST, class L, class F>
     __device__ __forceinline__ void extension(const mfma_v4i *A, const Digits (&d)[NT], L load, F use) const {
         // an opaque zero: the tiles never change, and without it the compiler
         // reads all of them ahead of the exponent loop and spills them
@@ -178,7 +189,7 @@ struct WaveEngine {
 #pragma unroll
         for (int t = 0; t < G && t < MT; t++)
 #pragma unroll
-            for (int ks = 0; ks < KS; ks++) a[0][t][ks] = REG ? R1[order(t)][ks] : A[(order(t) * KS + ks) * 64];
+            for (int ks = 0; ks < KS; ks++) a[0][t][ks] = tile<FIRST>(A, order(t), ks);
 #pragma unroll
         for (int i = 0; i <= STEPS; i++) {
 #pragma unroll
@@ -186,7 +197,7 @@ struct WaveEngine {
                 if ((i + 1) * G + t < MT)
 #pragma unroll
                     for (int ks = 0; ks < KS; ks++)
-                        a[(i + 1) & 1][t][ks] = REG ? R1[order((i + 1) * G + t)][ks] : A[(order((i + 1) * G + t) * KS + ks) * 64];
+                        a[(i + 1) & 1][t][ks] = tile<FIRST>(A, order((i + 1) * G + t), ks);
 #pragma unroll
             for (int t = 0; t < G; t++)
                 if (i * G + t < MT) c[i & 1][t] = load(order(i * G + t));
@@ -258,7 +269,7 @@ struct WaveEngine {
             for (int nt = 0; nt < NT; nt++) l.y[nt] = y.p(mt, nt);
             return l;
         };
-        extension<A1REG>(A1, d1, loadP, [&](int mt, const LoadP &l, const mfma_v4i (&D)[NT]) {   // (ii), (iii)
+        extension<true>(A1, d1, loadP, [&](int mt, const LoadP &l, const mfma_v4i (&D)[NT]) {   // (ii), (iii)
             const uint32_t m = l.c.x, u = l.c.y;
             const uint64_t off = WIDE ? ((uint64_t)l.c.w << 32) | l.c.z : (uint64_t)m << S::OSH;
 #pragma unroll
