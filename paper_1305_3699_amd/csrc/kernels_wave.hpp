@@ -235,8 +235,12 @@ struct WaveEngine {
             const uint4 c = cB(mt);
 #pragma unroll
             for (int nt = 0; nt < NT; nt++) {
-                if constexpr (SQ) {
+                if constexpr (WIDE) {
                     d[nt].set(mt, redc_any((uint64_t)x.b[mt][nt] * y.b(mt, nt), c.x, c.y));
+                } else if constexpr (SQ) {
+                    // below the prime: the narrow offset is one m_i M_i, so a digit above m_i
+                    // with sigma_i = -1 could make the quotient, and the result, negative
+                    d[nt].set(mt, mulredc(x.b[mt][nt], y.b(mt, nt), c.x, 0u - c.y));
                 } else {
                     d[nt].set(mt, mulredc(mulredc(x.b[mt][nt], y.b(mt, nt), c.x, c.y), c.w, c.x, c.y));
                 }

@@ -404,6 +404,22 @@ def test_mont_mul_default_context(bits, n, group):
     assert np.array_equal(got, res([rns_ref.mont_mul(x, y, N, pr[:k]) for x, y in zip(X, Y)]))
 
 
+@pytest.mark.parametrize("opts", [{"prime_range": 1, "prime_seed": 5}, {"prime_range": 1, "prime_seed": 11},
+                                  {"primes": [2147483659, 2147483743, 2147483783, 2147483867, 2147483887, 2147483951]}])
+def test_modexp_k3_primes_far_below_2_32(opts):
+    """k = 3 on bases whose primes are far below 2^32, full-range draws and primes
+    just above 2^31: powers (every e from 0 to 3, and a random one) equal the
+    oracle's."""
+    rng = random.Random(99)
+    N = rng.getrandbits(62) | (1 << 61) | 1
+    ctx = _ctx(N, 2, **opts)
+    assert ctx.info["k"] == 3 and ctx.info["scaled"] == 1
+    bases = gen.to_limbs([rng.randrange(N) for _ in range(2000)] + [0, 1, N - 1, N, (1 << 64) - 1], 2)
+    for e in [0, 1, 2, 3, rng.getrandbits(62)]:
+        e = gen.to_limbs(e, 2)[0]
+        assert np.array_equal(_run_modexp(ctx, bases, e), oracle.modexp_batch(bases, e, gen.to_limbs(N, 2)[0]))
+
+
 @pytest.mark.parametrize("bits,k", [(64, 3), (128, 5)])
 def test_scaled_b_residues_primes_1_mod_4(bits, k):
     """The kernel's scaled form on an explicit base whose B primes are all
