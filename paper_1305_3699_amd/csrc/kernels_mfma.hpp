@@ -142,6 +142,7 @@ struct MConst {
     gcv4i *a1mem;            // its first-extension tiles in global memory (A1_GLOBAL shapes)
     uint32_t loff;           // lane * 16: the lane's byte offset in a tile
     uint32_t mB[MT], uB[MT], nuB[MT], cB[MT];
+    uint32_t zB[MT];         // standalone product: MLayout::zdig
     uint32_t mP[MT], uP[MT], HP[MT];
     const uint32_t *cl;      // CL: this lane group's constants in LDS, tile mt at cl + 32 mt
     uint32_t Mpinv_r, Minv_r, N_r;
@@ -287,7 +288,7 @@ __device__ __forceinline__ int mfma_digit_col(int wave, int mt, int g) {
 // the channel's sign sigma_i), published as the B operand of the first
 // extension.  With the B residues kept scaled (SQ: x R s_i, s_i^2 =
 // sigma_i c_i R^-1) that is one REDC of the two operands, else two.
-template <int K, int W, int MT, int NT, bool SQ = false>
+template <int K, int W, int MT, int NT, bool SQ = false, bool ONCE = false>
 __device__ __forceinline__ void mfma_publish_xi(const MConstOf<K, W, MT, NT> &C,
                                                 const MState<MT, NT> &x, const MState<MT, NT> &y, uint32_t *buf1,
                                                 int wave, int lane) {
@@ -300,7 +301,8 @@ __device__ __forceinline__ void mfma_publish_xi(const MConstOf<K, W, MT, NT> &C,
         for (int nt = 0; nt < NT; nt++) {
             const MSlotB sb = C.slotB(mt);
             const uint32_t t = mulredc(x.b[mt][nt], y.b[mt][nt], sb.m, sb.u);   // x y 2^32, or sigma x y c_i (SQ)
-            const uint32_t xi = SQ ? t : mulredc(t, sb.c, sb.m, sb.u);         // sigma x y c_i
+            uint32_t xi = SQ ? t : mulredc(t, sb.c, sb.m, sb.u);               // sigma x y c_i
+            if (ONCE && S::LY.sq_ok() && xi == 0) xi = C.zB[mt];
             buf1[(16 * nt + (lane & 15)) * S::BROW + col] = mfma_pack(xi);
         }
     }
@@ -310,14 +312,15 @@ __device__ __forceinline__ void mfma_publish_xi(const MConstOf<K, W, MT, NT> &C,
 // full == false the second extension is skipped (the caller leaves the RNS
 // from the xi' digits in buf2).  x.r receives the new redundant residue.
 // SQ: B residues kept scaled by s_i (C then holds the scaled second
-// extension and nu, so the result comes out scaled as well).
-template <int K, int W, int MT, int NT, bool SQ = false>
+// extension and nu, so the result comes out scaled as well).  ONCE: the
+// standalone product.
+template <int K, int W, int MT, int NT, bool SQ = false, bool ONCE = false>
 __device__ __forceinline__ void mfma_mm(const MConstOf<K, W, MT, NT> &C, MState<MT, NT> &x,
                                         const MState<MT, NT> &y, uint32_t *buf1, uint32_t *buf2, int wave, int lane,
                                         bool full) {
     using S = MShp<K, W, MT, NT>;
     const int g = lane >> 4;
-    mfma_publish_xi<K, W, MT, NT, SQ>(C, x, y, buf1, wave, lane);
+    mfma_publish_xi<K, W, MT, NT, SQ, ONCE>(C, x, y, buf1, wave, lane);
     __syncthreads();
 
     // (ii) first extension on the matrix cores: q^'' N M^-1 (scaled) in each B'
@@ -1254,6 +1257,9 @@ __global__ __launch_bounds__((MShp<K, W, MT, NT>::THREADS)) void montmul_mfma_ke
         mfma_setup<K, W, MT, NT>(mb, mk, lds, wave, lane, C);
         mfma_rows<K, W, MT, NT>(lds);
         mfma_load_tiles<K, W, MT, NT>(mb, mk, lds, wave, lane, C);
+#pragma unroll
+        for (int mt = 0; mt < MT; mt++)
+            C.zB[mt] = S::LY.sq_ok() ? mk[S::LY.zdig() + ((size_t)wave * MT + mt) * 64 + lane] : 0u;
     }
     // single-wave shapes load the operands before they wait for the tiles
     MState<MT, NT> a, b;
@@ -1301,7 +1307,7 @@ __global__ __launch_bounds__((MShp<K, W, MT, NT>::THREADS)) void montmul_mfma_ke
         C.template product<true>(MRegOperand<MT, NT>{b});
         a = C.x;
     } else {
-        mfma_mm<K, W, MT, NT>(C, a, b, lds, lds + S::NM * S::BROW, wave, lane, true);
+        mfma_mm<K, W, MT, NT, false, true>(C, a, b, lds, lds + S::NM * S::BROW, wave, lane, true);
     }
 #pragma unroll
     for (int mt = 0; mt < MT; mt++) {
@@ -1370,7 +1376,7 @@ __device__ __forceinline__ void montmul_team_part(const MontMulMfmaLaunch &A, ui
         a.r[nt] = ok[nt] ? x[(size_t)2 * K * B + elem[nt]] : 0u;
         b.r[nt] = ok[nt] ? y[(size_t)2 * K * B + elem[nt]] : 0u;
     }
-    TeamEngine<K, MT, NT, false, TW> C;
+    TeamEngine<K, MT, NT, false, TW, true> C;
     C.setup(mb, mk, lds, wave, lane);
     __syncthreads();
     C.load_constants(lds);

@@ -54,8 +54,8 @@ __device__ __forceinline__ void lane_groups_23(uint32_t v, uint32_t &g2, uint32_
 }
 
 // The slots' constants into LDS, [MT][4 lane groups][2][4]: B {m, m^-1 (SQ: -m^-1)
-// mod 2^32, nu, c (wide: nu2)}, B' {m, m^-1, H, 0 (wide: m 2^OSH)}.
-template <int K, int MT, int NT, bool SQ>
+// mod 2^32, nu, c (wide: nu2)}, B' {m, m^-1, H, 0 (ONCE: MLayout::zdig; wide: m 2^OSH)}.
+template <int K, int MT, int NT, bool SQ, bool ONCE = false>
 __device__ __forceinline__ void wave_constants(const gu32 *__restrict__ mb, const gu32 *__restrict__ mk, uint32_t *c,
                                                int threads) {
     using S = MShp<K, 1, MT, NT>;
@@ -69,6 +69,7 @@ __device__ __forceinline__ void wave_constants(const gu32 *__restrict__ mb, cons
             if (SQ && f == 1) v = 0u - v;
         } else if (f < 6 || !WIDE) {
             if (f < 7) v = mb[S::LY.slotP() + (mt * 4 + (f - 4)) * 64 + ln];
+            else if (ONCE) v = mk[S::LY.zdig() + mt * 64 + ln];
         } else {
             const uint64_t off = (uint64_t)mb[S::LY.slotP() + mt * 4 * 64 + ln] << S::OSH;
             v = f == 6 ? (uint32_t)off : (uint32_t)(off >> 32);
@@ -137,7 +138,7 @@ struct WaveEngine {
         A1 = t + NQ + lane;
         A1g = a1 + lane;
         uint32_t *c = lds + (A1GLOBAL ? 1 : 2) * NQ * 4;
-        wave_constants<K, MT, NT, SQ>(mb, mk, c, 64 * S::WAVE_GROUP);
+        wave_constants<K, MT, NT, SQ, ONCE>(mb, mk, c, 64 * S::WAVE_GROUP);
         cl = c + 8 * (lane >> 4);
         Mpinv_r = mb[S::LY.bscal() + 0];
         Minv_r = mb[S::LY.bscal() + 1];
@@ -242,7 +243,9 @@ struct WaveEngine {
                     // with sigma_i = -1 could make the quotient, and the result, negative
                     d[nt].set(mt, mulredc(x.b[mt][nt], y.b(mt, nt), c.x, 0u - c.y));
                 } else {
-                    d[nt].set(mt, mulredc(mulredc(x.b[mt][nt], y.b(mt, nt), c.x, c.y), c.w, c.x, c.y));
+                    uint32_t xi = mulredc(mulredc(x.b[mt][nt], y.b(mt, nt), c.x, c.y), c.w, c.x, c.y);
+                    if (ONCE && xi == 0) xi = cP(mt).w;
+                    d[nt].set(mt, xi);
                 }
             }
         }
@@ -474,7 +477,7 @@ struct SplitEngine {
 // With both extensions' tiles split over six waves of 11 channels and a redundant
 // row each, without the wide form -> this: RSA-4096, one decryption 3.05 -> 2.48 ms,
 // 4,096 in 4.98 -> 4.37 ms; 10,007 RSA-2048 encryptions 145 -> 130 us.
-template <int K, int MT, int NT, bool SQ, int TW>
+template <int K, int MT, int NT, bool SQ, int TW, bool ONCE = false>
 struct TeamEngine {
     using S = MShp<K, 1, MT, NT>;
     static constexpr int KS = S::KSTEPS, WV = S::TEAM_WAVES;
@@ -503,7 +506,7 @@ struct TeamEngine {
         lane = l;
         wave = wv;
         tile0 = S::team_tile0(wv);
-        wave_constants<K, MT, NT, SQ>(mb, mk, lds, 64 * WV);
+        wave_constants<K, MT, NT, SQ, ONCE>(mb, mk, lds, 64 * WV);
         mfma_v4i *t = (mfma_v4i *)(lds + 32 * MT);
         lt = t + lane;
         gcv4i *a1 = (gcv4i *)(mk + S::LY.a1()), *a2 = (gcv4i *)(SQ ? mk + S::LY.a2s() : mb + S::LY.a2());
@@ -574,6 +577,7 @@ struct TeamEngine {
                 uint32_t xi;
                 if constexpr (SQ) xi = redc_any((uint64_t)x.b[t][nt] * y.b(t, nt), c.x, c.y);
                 else xi = mulredc(mulredc(x.b[t][nt], y.b(t, nt), c.x, c.y), c.w, c.x, c.y);
+                if (ONCE && xi == 0) xi = cp[t].w;
                 publish(0, t, nt, xi);
             }
         }

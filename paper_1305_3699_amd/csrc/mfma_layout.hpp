@@ -150,7 +150,11 @@ struct MLayout {
     // kscal[2]), with t the sigma_i = -1: the unscaled product of a wide key
     // leaves t N more than its definition, as the first extension's offset is 2 m_i M_i there
     constexpr size_t mmfix() const { return sqB() + (sq_ok() ? (size_t)W * MT * 4 * 64 : 0); }
-    constexpr size_t key_size() const { return mmfix() + (wide() ? (size_t)MT * 2 * 64 : 0); }
+    // scaled form: [W][MT][64] the digit that stands for xi_i = 0 in the standalone
+    // product, whose digits are unscaled: m_i for sigma_i = -1 (0 would count as
+    // xi_i = m_i and leave N more than the definition), else 0
+    constexpr size_t zdig() const { return mmfix() + (wide() ? (size_t)MT * 2 * 64 : 0); }
+    constexpr size_t key_size() const { return zdig() + (sq_ok() ? (size_t)W * MT * 64 : 0); }
     // entry table: per input limb [W*4*MT B slots | W*4*MT B' slots | redundant]
     constexpr size_t ecols() const { return (size_t)2 * W * 4 * MT + 1; }
 };

@@ -433,6 +433,7 @@ MfmaTables make_mfma_tables(const ModPlan &mp, const MfmaShape &sh, bool with_ba
             fill_slots(sh, out.key.data() + ly.mmfix() + 64, 2 * 64,
                        [&](int c) { return okc(c) ? bn_mod_word(tN, bs.Bp[c]) : 0u; });
         }
+        fill_slots(sh, out.key.data() + ly.zdig(), 64, [&](int t) { return okc(t) && sgn[t] < 0 ? bs.B[t] : 0u; });
         const size_t fq = (size_t)4 * 64;      // [W][MT][4][64]
         fill_slots(sh, out.key.data() + ly.sqB() + 3 * 64, fq, [&](int t) -> uint32_t { return wide && okc(t) ? nu2[t] : 0; });
         fill_slots(sh, out.key.data() + ly.sqB() + 0 * 64, fq, [&](int t) -> uint32_t {

@@ -404,6 +404,28 @@ def test_mont_mul_default_context(bits, n, group):
     assert np.array_equal(got, res([rns_ref.mont_mul(x, y, N, pr[:k]) for x, y in zip(X, Y)]))
 
 
+@pytest.mark.parametrize("bits,n,group", [(512, 40, 0), (1024, 67, 0), (1024, 33, 32), (1536, 21, 0), (1536, 40, 32),
+                                          (2048, 35, 0), (2048, 17, 16), (2080, 18, 0)])
+def test_mont_mul_zero_digits(bits, n, group):
+    """Operands that vanish modulo channel primes of B, from one prime up to all
+    of them (the quotient digits there are zero), X = 0 and Y = 0: residues
+    exactly as the definition gives them, on keys that hold the scaled form."""
+    rng = random.Random(bits * 7 + n)
+    N = rng.getrandbits(bits) | (1 << (bits - 1)) | 1
+    ctx = _ctx(N, bits // 32, group=group)
+    assert ctx.info["scaled"] == 1
+    pr, k = ctx.primes, ctx.info["k"]
+    X, Y = [0, 0, N - 1, 1], [0, N - 1, 0, 0]
+    while len(X) < n:
+        m = math.prod(rng.sample(list(pr[:k]), rng.choice([1, 1, 2, k // 2])))
+        a, b = m * rng.randrange(1, (k + 1) * N // m), rng.randrange((k + 1) * N)
+        X.append(a if len(X) % 2 else b)
+        Y.append(b if len(Y) % 2 else a)
+    res = lambda vs: np.array([[v % m for v in vs] for m in list(pr) + [1 << 32]], dtype=np.uint32)
+    got = _host(ctx.mont_mul(_dev(res(X)), _dev(res(Y))))
+    assert np.array_equal(got, res([rns_ref.mont_mul(x, y, N, pr[:k]) for x, y in zip(X, Y)]))
+
+
 @pytest.mark.parametrize("opts", [{"prime_range": 1, "prime_seed": 5}, {"prime_range": 1, "prime_seed": 11},
                                   {"primes": [2147483659, 2147483743, 2147483783, 2147483867, 2147483887, 2147483951]}])
 def test_modexp_k3_primes_far_below_2_32(opts):
