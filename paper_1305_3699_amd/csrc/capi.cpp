@@ -210,7 +210,7 @@ int ctx_from_plan(ModPlan &&mp, int window, int engine_req, int group, rns_ctx *
         else if ((rc = device_mfma_base(c->plan.base, c->mshape, t.base, &c->d_mbase)))
             return rc;
         if ((rc = upload(t.key, &c->d_mkey))) return rc;
-        c->mscaled = t.scaled;
+        c->mform = t.form();
         std::vector<uint32_t> Em = make_mfma_entry_table(c->plan, c->mshape, {c->plan.R2}, c->plan.L);
         if ((rc = upload(Em, &c->d_mentry))) return rc;
     }
@@ -374,7 +374,7 @@ int run_modexp(const rns_ctx *c0, const rns_ctx *c1, const uint32_t *E0, const u
         a.groups = sh.groups(per_job) * njobs;
         a.split = split_tiles(sh, (size_t)a.tiles, c0->device);
         a.max_window = c0->window;
-        a.scaled = c0->mscaled && (njobs < 2 || c1->mscaled);
+        a.form = njobs < 2 || c1->mform == c0->mform ? c0->mform : kPlain;
         Scratch table;
         if (!table_buf) {
             int rc = scratch_alloc(table, modexp_scratch_bytes(c0, njobs, batch, spread), s);
@@ -503,7 +503,7 @@ int rns_get_info(const rns_ctx *ctx, rns_info *info) {
     info->mod_bits = (int)bn_bits(ctx->plan.N);
     info->engine = ctx->engine;
     info->group = 64;
-    info->scaled = ctx->mscaled ? 1 : 0;
+    info->scaled = ctx->mform != kPlain ? 1 : 0;
     if (ctx->engine == RNS_ENGINE_MATRIX) {
         info->waves = ctx->mshape.W;
         info->group = ctx->mshape.NM();
@@ -579,9 +579,8 @@ int rns_modexp_jobs(const rns_job *jobs, size_t njobs, void *hip_stream) {
                 g.shape = sh;
                 g.device = dev;
                 g.auto_tile = c->group_req == 0;
-                g.scaled = true;
             }
-            g.scaled = g.scaled && c->mscaled;
+            g.take_form(c->mform);
             PlannedJob J{};
             J.j.mb = c->d_mbase;
             J.j.mk = c->d_mkey;

@@ -26,7 +26,7 @@ struct MCtx {
     bool sq;    // B residues kept scaled (x R s_i): the key holds the scaled form
     bool wide;  // with the wide second extension (kWideShift)
 
-    MCtx(const MfmaTables &t, bool scaled) : T(t), ly(t.shape), K(t.shape.K), sq(scaled && t.scaled), wide(sq && t.shape.wide()) {
+    MCtx(const MfmaTables &t, bool scaled) : T(t), ly(t.shape), K(t.shape.K), sq(scaled && t.scaled), wide(sq && t.wide) {
         const int SW = 4 * ly.MT, KK = 64 * ly.KSTEPS();
         A1.assign((size_t)ly.W * SW * 4 * KK, 0);
         A2.assign((size_t)ly.W * SW * 4 * KK, 0);

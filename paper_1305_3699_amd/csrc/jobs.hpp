@@ -48,7 +48,9 @@ struct JobGroup {
     std::vector<PlannedJob> jobs;
     int tiles = 0, groups = 0;
     int max_window = 1;
-    bool scaled = false;    // every job's key holds the scaled form (the kernel keeps B residues scaled)
+    int form = kPlain;      // MForm of the launch: the jobs' keys' one form, kPlain if they differ
+    // For each job's key form, before the job is added.
+    void take_form(int f) { form = jobs.empty() || form == f ? f : (int)kPlain; }
     size_t table_words() const { return modexp_mfma_table_words(shape, max_window, (size_t)tiles); }
 };
 

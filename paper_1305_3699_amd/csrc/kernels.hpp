@@ -98,7 +98,7 @@ struct ModexpMfmaLaunch {
     bool split;          // run the split kernel, one workgroup per tile
     int max_window;      // window table slots hold 2^max_window entries
     uint32_t *table;     // scratch: modexp_mfma_table_words(shape, max_window, tiles) words
-    int scaled;          // every job's key keeps scaled B residues (MfmaTables::scaled)
+    int form;            // MForm: how the kernel keeps the B residues, kPlain or every job's key's form
 };
 
 // One RNS Montgomery product per element on the matrix cores (the

@@ -1135,7 +1135,7 @@ __device__ __forceinline__ MJob mjob_of(const ModexpMfmaLaunch &A, int group) {
 // from a counter costs 15-35 more VGPRs per lane here, as the compiler keeps
 // the per-lane addresses of the tile body live across it; the hardware
 // dispatcher refills the CUs as workgroups finish instead.)
-template <int K, int W, int MT, int NT, bool SQ>
+template <int K, int W, int MT, int NT, int F>
 __global__ __launch_bounds__((MShp<K, W, MT, NT>::THREADS)) __attribute__((amdgpu_waves_per_eu(MShp<K, W, MT, NT>::WAVES_PER_EU)))
 void modexp_mfma_kernel(ModexpMfmaLaunch A) {
     using S = MShp<K, W, MT, NT>;
@@ -1146,16 +1146,16 @@ void modexp_mfma_kernel(ModexpMfmaLaunch A) {
     if constexpr (W == 1) {
         const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
         tile = tile * S::WAVE_GROUP + wave;
-        modexp_wave_tile<K, MT, NT, SQ>(J, tile * mjob_tile_elems(J, S::NM), lds,
+        modexp_wave_tile<K, MT, NT, F>(J, tile * mjob_tile_elems(J, S::NM), lds,
                                         lds + S::WAVE_TILE_WORDS + wave * S::WAVE_WORDS, A.table,
                                         (size_t)(J.tile0 + tile), A.max_window);
     } else {
-        modexp_mfma_tile<K, W, MT, NT, SQ>(J, tile * mjob_tile_elems(J, S::NM), lds, A.table, blockIdx.x,
+        modexp_mfma_tile<K, W, MT, NT, F != kPlain>(J, tile * mjob_tile_elems(J, S::NM), lds, A.table, blockIdx.x,
                                            A.max_window, ylds);
     }
 }
 
-template <int K, int MT, int NT, bool SQ>
+template <int K, int MT, int NT, int F>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void modexp_team_kernel(ModexpMfmaLaunch A) {
     using S = MShp<K, 1, MT, NT>;
     __shared__ __attribute__((aligned(16))) uint32_t lds[S::TEAM_WORDS];
@@ -1163,30 +1163,30 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void m
     const int e0 = ((int)blockIdx.x - J.group0) * mjob_tile_elems(J, 16 * NT);
     // both branches run the same barriers
     if (__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) < S::TEAM_EXTRA)
-        modexp_team_tile<K, MT, NT, SQ, S::TEAM_BASE + 1>(J, e0, lds, A.table, blockIdx.x, A.max_window);
+        modexp_team_tile<K, MT, NT, F, S::TEAM_BASE + 1>(J, e0, lds, A.table, blockIdx.x, A.max_window);
     else
-        modexp_team_tile<K, MT, NT, SQ, S::TEAM_BASE>(J, e0, lds, A.table, blockIdx.x, A.max_window);
+        modexp_team_tile<K, MT, NT, F, S::TEAM_BASE>(J, e0, lds, A.table, blockIdx.x, A.max_window);
 }
 
 // The split kernel of a single-wave shape: workgroup t runs tile t (see
 // SplitEngine).  Held to 3 waves per SIMD: 8,000 RSA-2048 decryptions, 1,000
 // workgroups that are then all resident, take 1.4 ms instead of 2.2 ms, a lone one
 // the same.
-template <int K, int MT, int WV, bool SQ>
+template <int K, int MT, int WV, int F>
 __global__ __launch_bounds__(64 * WV) __attribute__((amdgpu_waves_per_eu(3))) void modexp_split_kernel(ModexpMfmaLaunch A) {
     using S = MShp<K, 1, MT, 1>;
     __shared__ __attribute__((aligned(16))) uint32_t lds[S::SPLIT_WORDS(WV)];
     const MJob J = mjob_of<&MJob::tile0>(A, (int)blockIdx.x);
     const int e0 = ((int)blockIdx.x - J.tile0) * mjob_tile_elems(J, 16);
-    modexp_split_tile<K, MT, WV, SQ>(J, e0, lds, A.table, blockIdx.x, A.max_window);
+    modexp_split_tile<K, MT, WV, F>(J, e0, lds, A.table, blockIdx.x, A.max_window);
 }
 
 template <int K, int MT, int WV>
 hipError_t launch_modexp_split_t(const ModexpMfmaLaunch &a, hipStream_t s) {
-    if (a.scaled)
-        hipLaunchKernelGGL((modexp_split_kernel<K, MT, WV, true>), dim3((unsigned)a.tiles), dim3(64 * WV), 0, s, a);
-    else
-        hipLaunchKernelGGL((modexp_split_kernel<K, MT, WV, false>), dim3((unsigned)a.tiles), dim3(64 * WV), 0, s, a);
+    const auto kernel = a.form == kWide     ? modexp_split_kernel<K, MT, WV, kWide>
+                        : a.form == kScaled ? modexp_split_kernel<K, MT, WV, kScaled>
+                                            : modexp_split_kernel<K, MT, WV, kPlain>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)a.tiles), dim3(64 * WV), 0, s, a);
     return hipGetLastError();
 }
 // compiled in a unit of its own, with the default instruction scheduler
@@ -1202,19 +1202,17 @@ hipError_t launch_modexp_mfma_t(const ModexpMfmaLaunch &a, hipStream_t s) {
     if constexpr (S::SPLIT > 0)
         if (a.split) return launch_modexp_split_t<K, MT, S::SPLIT>(a, s);
     if constexpr (S::LY.team()) {
-        if (a.scaled)
-            hipLaunchKernelGGL((modexp_team_kernel<K, MT, NT, true>), dim3((unsigned)a.tiles), dim3(512), 0, s, a);
-        else
-            hipLaunchKernelGGL((modexp_team_kernel<K, MT, NT, false>), dim3((unsigned)a.tiles), dim3(512), 0, s, a);
-    } else if constexpr (S::LY.sq_ok() && !S::A2_GLOBAL && !S::C_LDS) {
-        if (a.scaled)
-            hipLaunchKernelGGL((modexp_mfma_kernel<K, W, MT, NT, true>), dim3((unsigned)a.groups), dim3(S::THREADS), 0, s,
-                               a);
-        else
-            hipLaunchKernelGGL((modexp_mfma_kernel<K, W, MT, NT, false>), dim3((unsigned)a.groups), dim3(S::THREADS), 0, s,
-                               a);
+        const auto kernel = a.form == kWide     ? modexp_team_kernel<K, MT, NT, kWide>
+                            : a.form == kScaled ? modexp_team_kernel<K, MT, NT, kScaled>
+                                                : modexp_team_kernel<K, MT, NT, kPlain>;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)a.tiles), dim3(512), 0, s, a);
     } else {
-        hipLaunchKernelGGL((modexp_mfma_kernel<K, W, MT, NT, false>), dim3((unsigned)a.groups), dim3(S::THREADS), 0, s, a);
+        auto kernel = modexp_mfma_kernel<K, W, MT, NT, kPlain>;
+        if constexpr (S::LY.sq_ok() && !S::A2_GLOBAL && !S::C_LDS)
+            if (a.form == kScaled) kernel = modexp_mfma_kernel<K, W, MT, NT, kScaled>;
+        if constexpr (S::LY.wide())
+            if (a.form == kWide) kernel = modexp_mfma_kernel<K, W, MT, NT, kWide>;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)a.groups), dim3(S::THREADS), 0, s, a);
     }
     return hipGetLastError();
 }
@@ -1252,7 +1250,7 @@ __global__ __launch_bounds__((MShp<K, W, MT, NT>::THREADS)) void montmul_mfma_ke
         elem[nt] = tile * te + n;
         ok[nt] = n < te && elem[nt] < A.batch;
     }
-    std::conditional_t<S::WAVE, WaveEngine<K, MT, NT, false, true>, MConstOf<K, W, MT, NT>> C;
+    std::conditional_t<S::WAVE, WaveEngine<K, MT, NT, kPlain, true>, MConstOf<K, W, MT, NT>> C;
     if constexpr (!S::WAVE) {
         mfma_setup<K, W, MT, NT>(mb, mk, lds, wave, lane, C);
         mfma_rows<K, W, MT, NT>(lds);
@@ -1376,7 +1374,7 @@ __device__ __forceinline__ void montmul_team_part(const MontMulMfmaLaunch &A, ui
         a.r[nt] = ok[nt] ? x[(size_t)2 * K * B + elem[nt]] : 0u;
         b.r[nt] = ok[nt] ? y[(size_t)2 * K * B + elem[nt]] : 0u;
     }
-    TeamEngine<K, MT, NT, false, TW, true> C;
+    TeamEngine<K, MT, NT, kPlain, TW, true> C;
     C.setup(mb, mk, lds, wave, lane);
     __syncthreads();
     C.load_constants(lds);
@@ -1449,7 +1447,7 @@ int mfma_blocks_per_cu_t() {
     int n = 0;
     using S = MShp<K, W, MT, NT>;
     if constexpr (!S::LY.team())
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, modexp_mfma_kernel<K, W, MT, NT, false>, S::THREADS, 0) != hipSuccess)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, modexp_mfma_kernel<K, W, MT, NT, kPlain>, S::THREADS, 0) != hipSuccess)
         return 0;
     return n * (S::WAVE ? S::WAVE_GROUP : 1);
 }

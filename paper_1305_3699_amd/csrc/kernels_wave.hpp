@@ -55,11 +55,11 @@ __device__ __forceinline__ void lane_groups_23(uint32_t v, uint32_t &g2, uint32_
 
 // The slots' constants into LDS, [MT][4 lane groups][2][4]: B {m, m^-1 (SQ: -m^-1)
 // mod 2^32, nu, c (wide: nu2)}, B' {m, m^-1, H, 0 (ONCE: MLayout::zdig; wide: m 2^OSH)}.
-template <int K, int MT, int NT, bool SQ, bool ONCE = false>
+template <int K, int MT, int NT, int F, bool ONCE = false>
 __device__ __forceinline__ void wave_constants(const gu32 *__restrict__ mb, const gu32 *__restrict__ mk, uint32_t *c,
                                                int threads) {
     using S = MShp<K, 1, MT, NT>;
-    constexpr bool WIDE = SQ && S::LY.wide();
+    constexpr bool SQ = F != kPlain, WIDE = F == kWide;
     for (int i = threadIdx.x; i < MT * 32; i += threads) {
         const int f = i & 7, mt = i >> 5, ln = 16 * ((i >> 3) & 3);
         uint32_t v = 0;
@@ -78,12 +78,14 @@ __device__ __forceinline__ void wave_constants(const gu32 *__restrict__ mb, cons
     }
 }
 
-template <int K, int MT, int NT, bool SQ, bool ONCE = false>
+// F: MForm
+template <int K, int MT, int NT, int F, bool ONCE = false>
 struct WaveEngine {
     using S = MShp<K, 1, MT, NT>;
     static constexpr int KS = S::KSTEPS;
     static_assert(4 * KS > MT, "a digit word for the offset after the last tile");
-    static constexpr bool WIDE = SQ && S::LY.wide();   // see kWideShift
+    static constexpr bool SQ = F != kPlain, WIDE = F == kWide;   // see kWideShift
+    static_assert(!WIDE || S::LY.wide(), "a slot for the estimate row");
 
     const mfma_v4i *A1, *A2;             // LDS: the extensions' tiles [MT][KS][64], + lane
     mfma_v4i R1[MT][KS];                 // A1REG: the first extension's in registers
@@ -138,7 +140,7 @@ struct WaveEngine {
         A1 = t + NQ + lane;
         A1g = a1 + lane;
         uint32_t *c = lds + (A1GLOBAL ? 1 : 2) * NQ * 4;
-        wave_constants<K, MT, NT, SQ, ONCE>(mb, mk, c, 64 * S::WAVE_GROUP);
+        wave_constants<K, MT, NT, F, ONCE>(mb, mk, c, 64 * S::WAVE_GROUP);
         cl = c + 8 * (lane >> 4);
         Mpinv_r = mb[S::LY.bscal() + 0];
         Minv_r = mb[S::LY.bscal() + 1];
@@ -176,8 +178,8 @@ struct WaveEngine {
         else if constexpr (FIRST && A1GLOBAL) return A1g[(mt * KS + ks) * 64];
         else return A[(mt * KS + ks) * 64];
     }
-    template <bool FIRST, class L, class F>
-    __device__ __forceinline__ void extension(const mfma_v4i *A, const Digits (&d)[NT], L load, F use) const {
+    template <bool FIRST, class L, class U>
+    __device__ __forceinline__ void extension(const mfma_v4i *A, const Digits (&d)[NT], L load, U use) const {
         // an opaque zero: the tiles never change, and without it the compiler
         // reads all of them ahead of the exponent loop and spills them
         int zo;
@@ -253,8 +255,7 @@ struct WaveEngine {
     // One product x <- x y M^-1 (y may be x).  FULL = false stops after the
     // B' residues and, without scaled B residues, leaves the digits xi' in d2.
     //
-    // With scaled B residues (SQ) the second extension is the wide one (WIDE; but
-    // for k = 3, which has no slot for the estimate row): its digits are the kept B' residues, which saves the
+    // With the wide second extension (WIDE) its digits are the kept B' residues, which saves the
     // multiplication by H and its reduction; step (iv)'s sum is small, so
     // that its reduction needs no correction (but in the first tile, where the
     // primes are closest to 2^32); B residues may exceed their prime.
@@ -332,9 +333,10 @@ struct WaveEngine {
 // two barriers.  A product's chain (two contractions, two reductions, two
 // exchanges) bounds it, 0.75 us alone on its SIMDs; a lone RSA-2048 decryption
 // takes 0.91 ms here and 1.6 ms on one wave.
-template <int K, int MT, int WV, bool SQ>
+template <int K, int MT, int WV, int F>
 struct SplitEngine {
     static constexpr int NT = 1, TW = MT / WV;
+    static constexpr bool SQ = F != kPlain, WIDE = F == kWide;
     using S = MShp<K, 1, MT, 1>;
     static constexpr int KS = S::KSTEPS;
     static_assert(S::LY.wide() && MT == WV * TW && 4 * KS > MT, "whole tiles per wave, a digit word for the offset");
@@ -361,7 +363,7 @@ struct SplitEngine {
             const uint32_t u = mb[S::LY.slotB() + (mt * 3 + 1) * 64 + lane];
             cb[t].y = SQ ? 0u - u : u;
             cb[t].z = SQ ? mk[S::LY.sqB() + (mt * 4 + 0) * 64 + lane] : mb[S::LY.slotB() + (mt * 3 + 2) * 64 + lane];
-            cb[t].w = SQ ? mk[S::LY.sqB() + (mt * 4 + 3) * 64 + lane] : mk[S::LY.slotC() + mt * 64 + lane];
+            cb[t].w = WIDE ? mk[S::LY.sqB() + (mt * 4 + 3) * 64 + lane] : mk[S::LY.slotC() + mt * 64 + lane];
             cp[t].x = mb[S::LY.slotP() + (mt * 4 + 0) * 64 + lane];
             cp[t].y = mb[S::LY.slotP() + (mt * 4 + 1) * 64 + lane];
             cp[t].z = mb[S::LY.slotP() + (mt * 4 + 2) * 64 + lane];
@@ -402,7 +404,8 @@ struct SplitEngine {
 #pragma unroll
         for (int t = 0; t < TW; t++) {
             uint32_t xi;
-            if constexpr (SQ) xi = redc_any((uint64_t)x.b[t][0] * y.b(t, 0), cb[t].x, cb[t].y);
+            if constexpr (WIDE) xi = redc_any((uint64_t)x.b[t][0] * y.b(t, 0), cb[t].x, cb[t].y);
+            else if constexpr (SQ) xi = mulredc(x.b[t][0], y.b(t, 0), cb[t].x, 0u - cb[t].y);
             else xi = mulredc(mulredc(x.b[t][0], y.b(t, 0), cb[t].x, cb[t].y), cb[t].w, cb[t].x, cb[t].y);
             publish(0, t, xi);
         }
@@ -424,7 +427,7 @@ struct SplitEngine {
                 D[t], (uint64_t)x.p[t][0] * y.p(t, 0) + ((uint64_t)m << S::OSH), kf);
             const uint32_t r = redc((uint32_t)T, (uint32_t)(T >> 32), m, u);
             x.p[t][0] = r;
-            publish(1, t, SQ && FULL ? r : mulredc(r, cp[t].z, m, u));
+            publish(1, t, WIDE && FULL ? r : mulredc(r, cp[t].z, m, u));
         }
         if (wave == WV - 1) {
             x.r[0] = (x.r[0] * y.r(0) + lo1 * N_r) * Minv_r;
@@ -446,7 +449,7 @@ struct SplitEngine {
         const uint32_t lo =
             ((uint32_t)__builtin_amdgcn_ds_bpermute(((lane & 15) + 48) * 4, (int)mfma_combine_lo(R)) - rr) * Mpinv_r;
         uint32_t al = lo, ah = 0;
-        if constexpr (SQ) {
+        if constexpr (WIDE) {
             const int32_t est = __builtin_amdgcn_ds_bpermute(((lane & 15) + 32) * 4, R[0]);
             const int32_t h = (est + est_r - (int32_t)(lo >> 18)) >> 14;
             ah = ((uint32_t)h << (32 - kWideShift)) + (lo >> kWideShift);
@@ -455,12 +458,12 @@ struct SplitEngine {
 #pragma unroll
         for (int t = 0; t < TW; t++) {
             const uint32_t m = cb[t].x;
-            if constexpr (SQ) {
+            if constexpr (WIDE) {
                 const uint64_t T = mfma_accumulate<S::PAIR_I32>(D[t], (uint64_t)al * cb[t].z + (uint64_t)ah * cb[t].w, kf);
                 x.b[t][0] = t == 0 ? redc_any(T, m, cb[t].y) : redc_small(T, m, cb[t].y);
             } else {
                 const uint64_t T = mfma_accumulate<S::PAIR_I32>(D[t], (uint64_t)al * cb[t].z + ((uint64_t)m << S::OSH), kf);
-                x.b[t][0] = redc((uint32_t)T, (uint32_t)(T >> 32), m, cb[t].y);
+                x.b[t][0] = redc((uint32_t)T, (uint32_t)(T >> 32), m, SQ ? 0u - cb[t].y : cb[t].y);
             }
         }
     }
@@ -477,9 +480,10 @@ struct SplitEngine {
 // With both extensions' tiles split over six waves of 11 channels and a redundant
 // row each, without the wide form -> this: RSA-4096, one decryption 3.05 -> 2.48 ms,
 // 4,096 in 4.98 -> 4.37 ms; 10,007 RSA-2048 encryptions 145 -> 130 us.
-template <int K, int MT, int NT, bool SQ, int TW, bool ONCE = false>
+template <int K, int MT, int NT, int F, int TW, bool ONCE = false>
 struct TeamEngine {
     using S = MShp<K, 1, MT, NT>;
+    static constexpr bool SQ = F != kPlain, WIDE = F == kWide;
     static constexpr int KS = S::KSTEPS, WV = S::TEAM_WAVES;
     // tiles of the first and second extension kept in LDS, not in registers
     static constexpr int L1 = TW == 3 ? S::TEAM_L1 : 0, L2 = TW == 3 ? S::TEAM_L2 : 0;
@@ -506,7 +510,7 @@ struct TeamEngine {
         lane = l;
         wave = wv;
         tile0 = S::team_tile0(wv);
-        wave_constants<K, MT, NT, SQ, ONCE>(mb, mk, lds, 64 * WV);
+        wave_constants<K, MT, NT, F, ONCE>(mb, mk, lds, 64 * WV);
         mfma_v4i *t = (mfma_v4i *)(lds + 32 * MT);
         lt = t + lane;
         gcv4i *a1 = (gcv4i *)(mk + S::LY.a1()), *a2 = (gcv4i *)(SQ ? mk + S::LY.a2s() : mb + S::LY.a2());
@@ -575,7 +579,8 @@ struct TeamEngine {
 #pragma unroll
             for (int nt = 0; nt < NT; nt++) {
                 uint32_t xi;
-                if constexpr (SQ) xi = redc_any((uint64_t)x.b[t][nt] * y.b(t, nt), c.x, c.y);
+                if constexpr (WIDE) xi = redc_any((uint64_t)x.b[t][nt] * y.b(t, nt), c.x, c.y);
+                else if constexpr (SQ) xi = mulredc(x.b[t][nt], y.b(t, nt), c.x, 0u - c.y);
                 else xi = mulredc(mulredc(x.b[t][nt], y.b(t, nt), c.x, c.y), c.w, c.x, c.y);
                 if (ONCE && xi == 0) xi = cp[t].w;
                 publish(0, t, nt, xi);
@@ -605,16 +610,16 @@ struct TeamEngine {
 #pragma unroll
         for (int t = 0; t < TW; t++) {
             const uint4 c = cp[t];
-            const uint64_t off = SQ ? ((uint64_t)c.w << 32) | c.z : (uint64_t)c.x << S::OSH;
+            const uint64_t off = WIDE ? ((uint64_t)c.w << 32) | c.z : (uint64_t)c.x << S::OSH;
             uint32_t H = c.z;
             // the exit takes xi' = r H, whose factor the wide form has no place for
-            if (SQ && !FULL) H = ((const gu32 *)hp)[t * 4 * 64];
+            if (WIDE && !FULL) H = ((const gu32 *)hp)[t * 4 * 64];
 #pragma unroll
             for (int nt = 0; nt < NT; nt++) {
                 const uint64_t T = mfma_accumulate<S::PAIR_I32>(D[t][nt], (uint64_t)x.p[t][nt] * y.p(t, nt) + off, kf);
                 const uint32_t r = redc((uint32_t)T, (uint32_t)(T >> 32), c.x, c.y);
                 x.p[t][nt] = r;
-                publish(1, t, nt, SQ && FULL ? r : mulredc(r, H, c.x, c.y));
+                publish(1, t, nt, WIDE && FULL ? r : mulredc(r, H, c.x, c.y));
             }
         }
         if (wave == WV - 1)
@@ -653,7 +658,7 @@ struct TeamEngine {
             const uint32_t lo =
                 ((uint32_t)__builtin_amdgcn_ds_bpermute(((lane & 15) + 48) * 4, (int)mfma_combine_lo(R[nt])) - rr) * Mpinv_r;
             al[nt] = lo, ah[nt] = 0;
-            if constexpr (SQ) {
+            if constexpr (WIDE) {
                 const int32_t est = __builtin_amdgcn_ds_bpermute(((lane & 15) + 32) * 4, R[nt][0]);
                 const int32_t h = (est + est_r - (int32_t)(lo >> 18)) >> 14;
                 ah[nt] = ((uint32_t)h << (32 - kWideShift)) + (lo >> kWideShift);
@@ -665,14 +670,14 @@ struct TeamEngine {
             const uint4 c = cb[t];
 #pragma unroll
             for (int nt = 0; nt < NT; nt++) {
-                if constexpr (SQ) {
+                if constexpr (WIDE) {
                     const uint64_t T = mfma_accumulate<S::PAIR_I32>(
                         D[t][nt], (uint64_t)al[nt] * c.z + (uint64_t)ah[nt] * c.w, kf);
                     x.b[t][nt] = TW > S::TEAM_BASE && t == 0 ? redc_any(T, c.x, c.y) : redc_small(T, c.x, c.y);
                 } else {
                     const uint64_t T = mfma_accumulate<S::PAIR_I32>(
                         D[t][nt], (uint64_t)al[nt] * c.z + ((uint64_t)c.x << S::OSH), kf);
-                    x.b[t][nt] = redc((uint32_t)T, (uint32_t)(T >> 32), c.x, c.y);
+                    x.b[t][nt] = redc((uint32_t)T, (uint32_t)(T >> 32), c.x, SQ ? 0u - c.y : c.y);
                 }
             }
         }
@@ -830,14 +835,14 @@ __device__ __forceinline__ void wave_exponent(const MJob &J, int e0, E &w, int t
 
 // One tile of exponentiation job J on one wave.  lds: the workgroup's tiles; wl:
 // this wave's part, for the inputs, the operands and the exit.
-template <int K, int MT, int NT, bool SQ>
+template <int K, int MT, int NT, int F>
 __device__ __forceinline__ void modexp_wave_tile(const MJob &J, int e0, uint32_t *__restrict__ lds, uint32_t *__restrict__ wl,
                                                  uint32_t *__restrict__ table, size_t slot, int max_window) {
     using S = MShp<K, 1, MT, NT>;
     const gu32 *__restrict__ mb = (const gu32 *)J.mb;
     const gu32 *__restrict__ mk = (const gu32 *)J.mk;
     const int lane = threadIdx.x & 63;
-    WaveEngine<K, MT, NT, SQ> w;
+    WaveEngine<K, MT, NT, F> w;
     w.setup(mb, mk, lds, lane);
     __syncthreads();
     const int te = mjob_tile_elems(J, S::NM);
@@ -845,7 +850,7 @@ __device__ __forceinline__ void modexp_wave_tile(const MJob &J, int e0, uint32_t
     MState<MT, NT> &a = w.x;
     wave_entry<K, MT, NT>(J, e0, wl, lane, w, a);
     w.load_tiles();
-    wave_exponent<K, MT, SQ, MT, NT>(J, e0, w, 0, lane, (gu32 *)table + (slot << max_window) * (S::SLOTS * 64) + lane, wl, true);
+    wave_exponent<K, MT, F != kPlain, MT, NT>(J, e0, w, 0, lane, (gu32 *)table + (slot << max_window) * (S::SLOTS * 64) + lane, wl, true);
 
     // leave the RNS (see mfma_exit), one group of 16 elements at a time
     if constexpr (decltype(w)::WIDE) {                           // the digits xi' = r (M'_t)^-1
@@ -890,7 +895,7 @@ __device__ __forceinline__ void modexp_wave_tile(const MJob &J, int e0, uint32_t
 }
 
 // The same over the WV waves of a workgroup (16 elements).
-template <int K, int MT, int WV, bool SQ>
+template <int K, int MT, int WV, int F>
 __device__ __forceinline__ void modexp_split_tile(const MJob &J, int e0, uint32_t *__restrict__ lds,
                                                   uint32_t *__restrict__ table, size_t slot, int max_window) {
     using S = MShp<K, 1, MT, 1>;
@@ -901,7 +906,7 @@ __device__ __forceinline__ void modexp_split_tile(const MJob &J, int e0, uint32_
     const int lane = threadIdx.x & 63;
     uint32_t *yl = lds + 2 * (MT + 1) * 64 + wave * (2 * TW + 1) * 64;
     uint32_t *io = lds + 2 * (MT + 1) * 64 + WV * (2 * TW + 1) * 64;
-    SplitEngine<K, MT, WV, SQ> w;
+    SplitEngine<K, MT, WV, F> w;
     w.setup(mb, mk, lds, wave, lane);
     mfma_stage_inputs<WV, 16>(J, e0, io, wave, lane);
     __syncthreads();
@@ -916,7 +921,7 @@ __device__ __forceinline__ void modexp_split_tile(const MJob &J, int e0, uint32_
         mfma_entry<S::ECOLS, 4 * MT, TW, 1>(J, io, wave * TW, lane, mB, uB, mP, uP, w.x);
     }
     w.load_tiles(mb, mk);
-    wave_exponent<K, MT, SQ, TW, 1>(J, e0, w, wave * TW, lane,
+    wave_exponent<K, MT, F != kPlain, TW, 1>(J, e0, w, wave * TW, lane,
                                     (gu32 *)table + (slot << max_window) * (S::SLOTS * 64) + wave * 2 * TW * 64 + lane,
                                     yl, wave == WV - 1);
 
@@ -945,7 +950,7 @@ __device__ __forceinline__ void modexp_split_tile(const MJob &J, int e0, uint32_
 }
 
 // One tile of exponentiation job J on a team: the part of a wave with TW tiles.
-template <int K, int MT, int NT, bool SQ, int TW>
+template <int K, int MT, int NT, int F, int TW>
 __device__ __forceinline__ void modexp_team_tile(const MJob &J, int e0, uint32_t *__restrict__ lds,
                                                   uint32_t *__restrict__ table, size_t slot, int max_window) {
     using S = MShp<K, 1, MT, NT>;
@@ -956,7 +961,7 @@ __device__ __forceinline__ void modexp_team_tile(const MJob &J, int e0, uint32_t
     const int lane = threadIdx.x & 63;
     uint32_t *yl = lds + S::TEAM_OPERANDS + (2 * S::team_tile0(wave) + wave) * NT * 64;
     uint32_t *io = lds + S::TEAM_IO;
-    TeamEngine<K, MT, NT, SQ, TW> w;
+    TeamEngine<K, MT, NT, F, TW> w;
     w.setup(mb, mk, lds, wave, lane);
     mfma_stage_inputs<WV, 16 * NT>(J, e0, io, wave, lane);
     __syncthreads();
@@ -972,7 +977,7 @@ __device__ __forceinline__ void modexp_team_tile(const MJob &J, int e0, uint32_t
         mfma_entry<S::ECOLS, 4 * MT, TW, NT>(J, io, w.tile0, lane, mB, uB, mP, uP, w.x);
     }
     w.load_tiles(mb, mk);
-    wave_exponent<K, MT, SQ, TW, NT>(J, e0, w, w.tile0, lane,
+    wave_exponent<K, MT, F != kPlain, TW, NT>(J, e0, w, w.tile0, lane,
                                      (gu32 *)table + (slot << max_window) * (S::SLOTS * 64) + w.tile0 * 2 * NT * 64 + lane,
                                      yl, wave == WV - 1);
 

@@ -62,6 +62,11 @@ constexpr uint64_t kExitOffset = 1ull << 50;
 // Waves of a workgroup of a single-wave shape (they share the constant tiles).
 constexpr int kWaveGroup = 4;
 
+// How a key's B residues are kept: x R, or x R s_i (see MLayout::sq_ok), the latter
+// with the narrow second extension or the wide one.  A key's tables hold one of
+// the scaled forms, or none, and serve kPlain in any case.
+enum MForm { kPlain = 0, kScaled = 1, kWide = 2 };
+
 // Wide second extension of the scaled form in single-wave shapes.  The digits
 // of B' are the kept residues zeta_t = x R M^-1 mod m'_t themselves, with
 // weights W_t = M'_t g_t, g_t = (M'_t)^-1 (R M^-1)^-1 mod m'_t, so that
@@ -138,7 +143,7 @@ struct MLayout {
     // per key, so only shapes whose tiles sit in registers or LDS (at most
     // 5 k-steps) take it.
     constexpr bool sq_ok() const { return KSTEPS() <= 5; }
-    // Whether the scaled form's second extension is the wide one; its estimate
+    // Whether the scaled form's second extension can be the wide one; its estimate
     // row is slot 4 MT - 2, before the redundant one.
     constexpr bool wide() const { return W == 1 && K <= 4 * MT - 2; }
     // scaled form (sq_ok shapes): [W][MT][KSTEPS][64][4] second extension

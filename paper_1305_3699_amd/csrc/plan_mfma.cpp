@@ -259,7 +259,9 @@ MfmaTables make_mfma_tables(const ModPlan &mp, const MfmaShape &sh, bool with_ba
                 nu2[i] = m - nu2[i];
             }
         }
-        out.scaled = wide = wide_fits(mp, ly, nu2, gsum);
+        // a base whose primes lie too close to 2^32 (at k = 65 most draws) keeps the
+        // scaled form with the narrow second extension
+        out.wide = wide = wide_fits(mp, ly, nu2, gsum);
     }
     if (!out.scaled) {
         std::fill(sgn.begin(), sgn.end(), 1);

@@ -32,6 +32,8 @@ struct MfmaTables {
     // channel had a square root s_i of sigma_i c_i R^-1 for sigma_i = 1 or
     // -1.  Either way the key also serves the unscaled form.
     bool scaled = false;
+    bool wide = false;           // with the wide second extension (kWideShift)
+    int form() const { return !scaled ? kPlain : wide ? kWide : kScaled; }
 };
 
 // Matrix-core kernel shape for K: the first listed whose workgroup serves

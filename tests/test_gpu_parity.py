@@ -279,6 +279,36 @@ def test_single_wave_and_split_launches(bits, counts, opts):
                                                             gen.to_limbs(N, L)[0]))
 
 
+@pytest.mark.parametrize("bits,n,opts", [
+    (1024, 33, {"prime_seed": 4}), (1024, 16403, {"prime_seed": 4}), (1024, 16320, {"prime_seed": 35, "group": 32}),
+    (2048, 17, {"prime_seed": 1}), (2048, 4097, {"prime_seed": 2}), (2048, 33, {"prime_seed": 3, "group": 16}),
+    (2080, 40, {"prime_seed": 1})])
+def test_narrow_scaled_form(bits, n, opts):
+    """Drawn bases with primes too close to 2^32 for the wide second extension
+    keep the scaled form with the narrow one: split, single-wave and team
+    kernels, both tiles, shared and per-element exponents, alone and grouped
+    with a key of the wide form; outputs equal the channel engine's, sampled
+    rows the oracle's."""
+    from paper_1305_3699_amd import ENGINE_CHANNEL, modexp_jobs
+    rng = random.Random(bits + n)
+    L = bits // 32
+    N = rng.getrandbits(bits) | (1 << (bits - 1)) | 1
+    ctx, wide = _ctx(N, L, **opts), _ctx(N, L, group=opts.get("group", 0))
+    assert ctx.info["scaled"] == 1 and wide.info["scaled"] == 1 and ctx.primes != wide.primes
+    bases = np.frombuffer(rng.randbytes(4 * n * L), dtype=np.uint32).reshape(n, L).copy()
+    bases[:, -1] &= 0x7FFFFFFF
+    bases[-1], bases[0] = gen.to_limbs([N - 1, 0], L)
+    each = np.frombuffer(rng.randbytes(4 * n), dtype=np.uint32).reshape(n, 1).copy()
+    idx = sorted({0, n - 1, n // 2})
+    for e in (gen.to_limbs(rng.getrandbits(90), 3)[0], each):
+        want = _run_modexp(_ctx(N, L, engine=ENGINE_CHANNEL), bases, e)
+        assert np.array_equal(want[idx], oracle.modexp_batch(bases[idx], e[idx] if e.ndim == 2 else e,
+                                                             gen.to_limbs(N, L)[0]))
+        assert np.array_equal(_run_modexp(ctx, bases, e), want)
+        for o in modexp_jobs([(ctx, _dev(bases), _dev(e)), (wide, _dev(bases), _dev(e))]):
+            assert np.array_equal(_host(o), want)
+
+
 @pytest.mark.parametrize("bits", [96, 1024, 2048])
 @pytest.mark.parametrize("limbs", [1, 2, 3])
 def test_window_width_by_exponent(bits, limbs):

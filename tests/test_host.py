@@ -173,6 +173,28 @@ def test_scaled_b_residues_selection():
     assert Plan(key.n, 32, prime_range=rnsrsa.PRIMES_FULL, prime_seed=gen.config_seed(1, 4)).info["scaled"] == 1
 
 
+@pytest.mark.parametrize("bits", [1024, 2048, 2080])
+def test_scaled_form_of_every_draw(bits):
+    """The scaled form does not depend on the draw: bases with many primes close
+    to 2^32, where the wide second extension does not fit, keep it too."""
+    N = random.Random(bits).getrandbits(bits) | (1 << (bits - 1)) | 1
+    for seed in range(40):
+        assert Plan(N, bits // 32, prime_seed=seed).info["scaled"] == 1, seed
+
+
+@pytest.mark.parametrize("bits,seed", [(1024, 4), (1024, 35), (2048, 1)])
+def test_emul_narrow_scaled_form(bits, seed):
+    """The host model on drawn bases that keep the narrow second extension
+    equals the oracle's pow."""
+    rng = random.Random(bits + seed)
+    N = rng.getrandbits(bits) | (1 << (bits - 1)) | 1
+    p = Plan(N, bits // 32, prime_seed=seed)
+    assert p.info["scaled"] == 1
+    bases = gen.to_limbs([rng.getrandbits(bits) for _ in range(4)] + [0, 1, N - 1], bits // 32)
+    e = gen.to_limbs(rng.getrandbits(64) | 1, 2)[0]
+    assert np.array_equal(p.emul_modexp(bases, e), oracle.modexp_batch(bases, e, gen.to_limbs(N, bits // 32)[0]))
+
+
 @pytest.mark.parametrize("bits,window,unscaled", [(64, 3, True), (1024, 5, True), (2048, 4, True),
                                                   (1024, 6, False), (2048, 5, False)])
 def test_emul_modexp_scaled_and_unscaled(bits, window, unscaled):
