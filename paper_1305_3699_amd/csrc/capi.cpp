@@ -296,11 +296,20 @@ bool split_tiles(const MfmaShape &sh, size_t tiles, int dev) {
     return sh.split_waves() && 64 * tiles <= 63 * (size_t)device_simds(dev);
 }
 
+// Shapes with W = 1 spread only while the launch keeps within one workgroup per CU
+// (a team's, a split tile's three waves, four single waves), so that every wave
+// has its SIMD to itself: 8,000 1024-bit powers mod a 512-bit n (500 tiles, k = 17)
+// take 531 us as 1,000 tiles and 658 us as 2,000; 3,001 powers with exponents of
+// their own at k = 33 (188 split tiles) 959 us as they are and 1,130 us as 376; 16,000
+// with 32-element tiles 2.65 and 5.3 ms.  Within that room it shortens the entry
+// and the exit: 1,000 powers with e = 65537, spread and not, 26 and 32 us (k = 2), 30
+// and 39 (k = 9), 30 and 34 (k = 17), 39.6 and 39.8 (k = 65); long exponents gain
+// nothing (k = 33: 908 and 905 us).
 int spread_tile_elems(const MfmaShape &sh, size_t tiles, int dev) {
     const int simds = device_simds(dev);
-    const int waves = sh.team() ? 8 : sh.split_waves() ? sh.split_waves() : sh.W;
+    const size_t room = sh.W == 1 && !sh.team() && !sh.split_waves() ? (size_t)simds : (size_t)simds / 4;
     int e = sh.NM();
-    while (simds && e > kMinTileElems && tiles * (size_t)waves < (size_t)simds) {
+    while (simds && e > kMinTileElems && (sh.W == 1 ? 2 * tiles < room : tiles * (size_t)sh.W < (size_t)simds)) {
         e /= 2;
         tiles *= 2;
     }

@@ -135,9 +135,10 @@ bool split_tiles(const MfmaShape &sh, size_t tiles, int dev);
 // Elements per tile for a matrix-core launch of `tiles` full tiles of shape
 // sh on device dev: 0 (all 16*NT columns) unless the launch would leave
 // SIMDs without a wave; then the largest of 16*NT/2, /4, ... down to
-// kMinTileElems that gives every SIMD a wave.  A workgroup's time does not
-// depend on how many of its columns are real, so on an underfilled GPU
-// spreading the elements over more workgroups shortens the launch.
+// kMinTileElems that gives every SIMD a wave (shapes with W = 1: that leaves
+// every CU at most one workgroup).  A workgroup's products do not depend on how
+// many of its columns are real, so on an underfilled GPU spreading the
+// elements over more workgroups shortens the launch.
 int spread_tile_elems(const MfmaShape &sh, size_t tiles, int dev);
 // A context for odd modulus N of L limbs with the default options (smallest
 // base, default engine and tile).  Owned by the caller (delete).

@@ -309,6 +309,24 @@ def test_narrow_scaled_form(bits, n, opts):
             assert np.array_equal(_host(o), want)
 
 
+@pytest.mark.parametrize("bits,n,opts", [(bits, n, opts) for bits, opts, tile, lines in [
+    (256, {}, 32, (64, 128, 256, 512)), (512, {}, 16, (128, 512)), (1024, {}, 16, (32, 64, 128)),
+    (1024, {"group": 32}, 32, (512,)), (2048, {"group": 16}, 16, (64, 128))]
+    for line in lines for n in (tile * (line - 1) + 1, tile * line + 1)])
+def test_spread_launches(bits, n, opts):
+    """Small launches around the lines where their tiles are spread over more waves
+    (tiles times two, four, ... below one workgroup per compute unit, for 256 of
+    them): outputs equal the channel engine's."""
+    from paper_1305_3699_amd import ENGINE_CHANNEL
+    rng = random.Random(n)
+    N, L = rng.getrandbits(bits) | (1 << (bits - 1)) | 1, bits // 32
+    bases = np.frombuffer(rng.randbytes(4 * n * L), dtype=np.uint32).reshape(n, L).copy()
+    bases[:, -1] &= 0x7FFFFFFF
+    e = gen.to_limbs(rng.getrandbits(40) | 1, 2)[0]
+    assert np.array_equal(_run_modexp(_ctx(N, L, **opts), bases, e),
+                          _run_modexp(_ctx(N, L, engine=ENGINE_CHANNEL), bases, e))
+
+
 @pytest.mark.parametrize("bits", [96, 1024, 2048])
 @pytest.mark.parametrize("limbs", [1, 2, 3])
 def test_window_width_by_exponent(bits, limbs):
