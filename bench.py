@@ -91,16 +91,17 @@ def wide_muls_per_mm(k: int) -> int:
 
 
 def kernel_shape(info: dict) -> tuple:
-    """Template arguments of the exponentiation kernel that serves info."""
+    """Template arguments of the exponentiation kernel that serves info: the
+    matrix-core shape of the reported tile, or k's one shape where that tile
+    has no kernel (k = 17 and 33 run 16 elements per tile in any case)."""
     if info["engine"] != 2:
         return (info["k"], info["waves"])
     import re
     txt = open(os.path.join(ROOT, "paper_1305_3699_amd/csrc/kernel_configs_mfma.inc")).read()
-    for m in re.finditer(r"RNSRSA_MSHAPE\((\d+),\s*(\d+),\s*(\d+),\s*(\d+)\)", txt):
-        k, w, mt, nt = (int(v) for v in m.groups())
-        if k == info["k"] and w == info["waves"] and 16 * nt == info["group"]:
-            return (k, w, mt, nt)
-    return (info["k"], info["waves"])
+    found = [tuple(int(v) for v in m.groups())
+             for m in re.finditer(r"RNSRSA_MSHAPE\((\d+),\s*(\d+),\s*(\d+),\s*(\d+)\)", txt)]
+    found = [s for s in found if s[0] == info["k"] and s[1] == info["waves"]]
+    return next((s for s in found if 16 * s[3] == info["group"]), found[0] if found else (info["k"], info["waves"]))
 
 
 def probe_alu_rate(op: int):
@@ -312,7 +313,7 @@ def run(args, key, ref=None) -> dict:
             "waves": info["waves"],
             "window": info["window"],
             "engine": ENGINE_NAMES[info["engine"]],
-            "group": info["group"],
+            "group": 16 * kernel_shape(info)[3] if info["engine"] == 2 else info["group"],
             "scaled_b": bool(info["scaled"]),
         },
         "latency_ms": {"p50": round(p50, 4), "p99": round(p99, 4), "what": "one step (batch of %d)" % B},

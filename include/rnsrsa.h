@@ -95,16 +95,19 @@ enum rns_prime_range {
  *               the channel engine (or RNS_EUNSUPPORTED if the matrix engine
  *               was requested or k = 513, which has no channel kernel).
  *               Full-range draws at k = 257 usually fail it.
- *   engine      rns_engine (0 = auto).  The Garner step of CRT decryption
- *               always uses the channel kernels; k = 513 runs on the matrix
- *               engine only (the channel engine returns RNS_EUNSUPPORTED
- *               there).
- *   group       matrix-core engine: preferred elements per workgroup, 16 or
- *               32, used by every launch (a k without a kernel of that size
- *               uses its default).  0: the default for k, except that a
- *               launch too small to give the GPU 1.5 resident waves per SIMD
- *               with 32-element workgroups takes 16-element ones.
- *               rns_info.group reports the requested or default size.
+ *   engine      rns_engine (0 = auto); k = 513 runs on the matrix engine only
+ *               (the channel engine returns RNS_EUNSUPPORTED there).  The
+ *               Garner step of CRT decryption runs in limbs on either engine
+ *               for odd p, on the channel kernels for even p.
+ *   group       matrix-core engine: preferred elements per tile, 16 or 32,
+ *               used by every launch; a k without a kernel of that size uses
+ *               its default, and k = 17 and 33 run 16 elements per tile in any
+ *               case, the faster size for every launch.  0: by the size of
+ *               the launch where k has both kernels: 32 at k = 97 and 129 once
+ *               such tiles fill every compute unit's resident slots, 16 at k
+ *               = 49, and at k = 65 the size whose rounds over the compute
+ *               units end first.  rns_info.group reports the requested or
+ *               default size (32 for k = 17 and 33).
  *   unscaled    matrix-core engine, k <= 66: 1 keeps the B residues in the
  *               plain Montgomery form x 2^32 mod m_i.  0 (default): they
  *               are kept as x 2^32 s_i mod m_i with s_i^2 = +-c_i 2^-32
@@ -135,12 +138,17 @@ typedef struct rns_opts {
 
 typedef struct rns_info {
     int k;              /* channels per base */
-    int waves;          /* wavefronts per workgroup */
+    int waves;          /* wavefronts that the base's channels are split over: per
+                           workgroup, but on the matrix engine 1 at k <= 33, where a
+                           workgroup has four such wavefronts (three, one tile, in
+                           small launches at k = 33), and at k = 65 and 66, where a tile
+                           belongs to a team of eight */
     int window;         /* exponent window width */
     int mod_limbs;      /* L */
     int mod_bits;       /* bit length of N */
     int engine;         /* RNS_ENGINE_CHANNEL or RNS_ENGINE_MATRIX */
-    int group;          /* elements served by one workgroup */
+    int group;          /* elements per tile, as requested or the default (see rns_opts);
+                           channel engine: 64 */
     int scaled;         /* 1: the matrix engine keeps this key's B residues scaled */
 } rns_info;
 

@@ -185,7 +185,7 @@ int tune_group(JobGroup &g, bool fixed_window, GroupTimer &tm, float *ms_out) {
     std::vector<MLayout> cands;
     for (int nt : {1, 2}) {
         MfmaShape sh;
-        if (mfma_shape_for(g.shape.K, sh, 16 * nt) && sh.W == g.shape.W && sh.MT == g.shape.MT && sh.NT == nt)
+        if (mfma_launch_shape(g.shape.K, sh, 16 * nt) && sh.W == g.shape.W && sh.MT == g.shape.MT && sh.NT == nt)
             cands.push_back(sh);
     }
     float best = 0;

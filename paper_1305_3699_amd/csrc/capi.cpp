@@ -202,6 +202,8 @@ int ctx_from_plan(ModPlan &&mp, int window, int engine_req, int group, rns_ctx *
     if ((rc = upload(E, &c->d_entry))) return rc;
     if (c->engine == RNS_ENGINE_MATRIX) {
         mfma_shape_for(c->plan.base->K, c->mshape, group);
+        c->group_info = c->mshape.NM();
+        mfma_launch_shape(c->plan.base->K, c->mshape, group);
         // the base table is built only when no context has uploaded it yet
         uint32_t *resident = resident_mfma_base(c->plan.base.get(), c->mshape);
         MfmaTables t = make_mfma_tables(c->plan, c->mshape, resident == nullptr, allow_scaled);
@@ -262,9 +264,6 @@ MfmaShape auto_tile(const MfmaShape &sh, size_t tiles, int dev, bool small_jobs)
     if (sh.NT != 2) return sh;
     MfmaShape alt;
     if (!mfma_shape_for(sh.K, alt, 16) || alt.NT != 1 || alt.W != sh.W || alt.MT != sh.MT) return sh;
-    // Single-wave shapes: a wave's registers then hold the first extension's
-    // tiles too (16,384 RSA-2048 decryptions 2.53 ms, 2.71 ms with 32 elements)
-    if (sh.W == 1 && !sh.team()) return alt;
     // jobs of a few elements each: the 16-element tile needs hardly more
     // workgroups, and each does half the work
     if (small_jobs) return alt;
@@ -515,7 +514,7 @@ int rns_get_info(const rns_ctx *ctx, rns_info *info) {
     info->scaled = ctx->mform != kPlain ? 1 : 0;
     if (ctx->engine == RNS_ENGINE_MATRIX) {
         info->waves = ctx->mshape.W;
-        info->group = ctx->mshape.NM();
+        info->group = ctx->group_info;
     }
     return ok();
 }
@@ -648,9 +647,7 @@ int rns_mont_mul_batch(rns_ctx *ctx, const uint32_t *x, const uint32_t *y, uint3
     const BaseSet &bs = *ctx->plan.base;
     if (ctx->engine == RNS_ENGINE_MATRIX) {
         MfmaShape sh = ctx->mshape;
-        // a single wave's product of 32 elements waits for its loads twice as long
-        // (40,000 products at k = 33: 27 us, of 16 elements 18 us)
-        if (!ctx->group_req || (sh.W == 1 && !sh.team())) sh = auto_tile(sh, (size_t)mfma_tiles(sh, batch), ctx->device);
+        if (!ctx->group_req) sh = auto_tile(sh, (size_t)mfma_tiles(sh, batch), ctx->device);
         MontMulMfmaLaunch a{};
         a.mb = ctx->d_mbase;
         a.mk = ctx->d_mkey;

@@ -60,6 +60,7 @@ struct rns_ctx {
     // matrix-core engine
     rnsrsa::MfmaShape mshape{};  // default tile
     int group_req = 0;            // tile asked for at set-up (0: chosen per launch)
+    int group_info = 0;           // the tile reported: asked for, or k's default
     uint32_t *d_mbase = nullptr;  // shared, owned by the process-wide cache
     uint32_t *d_mkey = nullptr;
     uint32_t *d_mentry = nullptr;

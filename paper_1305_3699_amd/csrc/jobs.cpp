@@ -129,7 +129,7 @@ int plan_jobs(const std::vector<PlannedOp> &ops, int fixed_w, JobPlan &P) {
             g.device = c->device;
             if (const int nt = tuned_nt(sh)) {
                 MfmaShape t;
-                if (mfma_shape_for(sh.K, t, 16 * nt) && t.W == sh.W && t.MT == sh.MT && t.NT == nt) g.shape = t;
+                if (mfma_launch_shape(sh.K, t, 16 * nt) && t.W == sh.W && t.MT == sh.MT && t.NT == nt) g.shape = t;
                 g.auto_tile = false;
             }
         }

@@ -460,7 +460,7 @@ int mr_base(int L, int dev, MrBase *out) {
     MrBase b;
     b.bs = mp.base;
     const BaseSet &bs = *b.bs;
-    bool fits = mfma_shape_for(bs.K, b.sh, 0);
+    bool fits = mfma_launch_shape(bs.K, b.sh, 0);
     for (uint32_t m : bs.B) fits = fits && mfma_prime_fits(m, bs.K, false);
     for (uint32_t m : bs.Bp) fits = fits && mfma_prime_fits(m, bs.K, true);
     if (!fits) return api::fail(RNS_EUNSUPPORTED, "the base of these candidates has no matrix-engine kernel");

@@ -15,10 +15,20 @@ bool mfma_shape_for(int K, MfmaShape &out, int group) {
         out = MfmaShape{k, w, mt, nt};                                 \
         return true;                                                   \
     }
+#define RNSRSA_MTABLES RNSRSA_MSHAPE
 #include "kernel_configs_mfma.inc"
 #undef RNSRSA_MSHAPE
     }
     return false;
+}
+
+bool mfma_launch_shape(int K, MfmaShape &out, int group) {
+    if (!mfma_shape_for(K, out, group)) return false;
+#define RNSRSA_MSHAPE(k, w, mt, nt) \
+    if (out.K == k && out.W == w && out.MT == mt && out.NT == nt) return true;
+#include "kernel_configs_mfma.inc"
+#undef RNSRSA_MSHAPE
+    return mfma_shape_for(K, out, 16);
 }
 
 namespace {

@@ -40,6 +40,13 @@ struct MfmaTables {
 // `group` elements, else (or for group 0) the first listed for K.
 bool mfma_shape_for(int K, MfmaShape &out, int group = 0);
 
+// The shape that launches run for it: the same, but at k = 17 and 33, where a
+// single wave of 16 elements is the faster one for every launch (its registers
+// hold the first extension's tiles, and a small launch runs split over three
+// waves: 16,384 RSA-2048 decryptions 2.44 and 2.67 ms, 16,000 1024-bit powers 1.37 and
+// 2.65 ms, 32,768 512-bit ones 0.65 and 0.82 ms), the 16-element one also for 32.
+bool mfma_launch_shape(int K, MfmaShape &out, int group = 0);
+
 // with_base = false leaves `base` empty (for a base whose table is already
 // resident) and builds the per-modulus part only; allow_scaled = false
 // builds the unscaled form only (scaled stays false).

@@ -173,6 +173,16 @@ def test_scaled_b_residues_selection():
     assert Plan(key.n, 32, prime_range=rnsrsa.PRIMES_FULL, prime_seed=gen.config_seed(1, 4)).info["scaled"] == 1
 
 
+def test_bench_names_the_launched_shape():
+    """bench.py reports the matrix-core shape that launches run: at k = 17 and 33
+    the 16-element one, whichever size was asked for."""
+    import bench
+    for bits, group, want in ((512, 0, (17, 1, 5, 1)), (1024, 0, (33, 1, 9, 1)), (1024, 16, (33, 1, 9, 1)),
+                              (1024, 32, (33, 1, 9, 1)), (1536, 0, (49, 7, 2, 1)), (1536, 32, (49, 7, 2, 2)),
+                              (2048, 16, (65, 1, 17, 1)), (3072, 0, (97, 9, 3, 2))):
+        assert bench.kernel_shape(Plan((1 << bits) - 1, bits // 32, group=group).info) == want
+
+
 @pytest.mark.parametrize("bits", [1024, 2048, 2080])
 def test_scaled_form_of_every_draw(bits):
     """The scaled form does not depend on the draw: bases with many primes close
