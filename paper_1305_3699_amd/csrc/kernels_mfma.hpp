@@ -71,6 +71,11 @@ struct MShp {
     static constexpr int WAVE_GROUP = kWaveGroup;
     static constexpr int WAVE_IO_WORDS = 16 * (2 * K + 1) > (2 * XSLOTS + 1) * 16 ? 16 * (2 * K + 1) : (2 * XSLOTS + 1) * 16;
     static constexpr int WAVE_WORDS = ((WAVE_IO_WORDS > SLOTS * 64 ? WAVE_IO_WORDS : SLOTS * 64) + 3) & ~3;
+    // The smallest bases: a wave's part of LDS holds all its elements' inputs and limb
+    // sums, not only 16 elements', and the exit takes one element per lane
+    static constexpr bool WAVE_WHOLE = WAVE && K <= 9;
+    static_assert(!WAVE_WHOLE || (NM <= 64 && NM * (2 * K + 1) <= WAVE_WORDS && NM * (2 * XSLOTS + 1) <= WAVE_WORDS),
+                  "inputs and limb sums of the whole tile");
     static constexpr int WAVE_TILE_WORDS = 2 * MT * KSTEPS * 64 * 4 + MT * 32;
     static constexpr int WAVE_MM_WORDS = (NT == 1 ? 1 : 2) * MT * KSTEPS * 64 * 4 + MT * 32;   // a standalone product's
     static constexpr int WORK_WORDS = EXIT_WORDS > BUF_WORDS ? EXIT_WORDS : BUF_WORDS;
@@ -637,6 +642,63 @@ __device__ __forceinline__ void mfma_exit_limbs(const gu32 *__restrict__ mb, con
     }
 }
 
+// The same for the smallest bases (k <= 9), one element per lane: their numbers fill
+// few lanes of a wave, and a wave takes a number's 200 instructions for each of
+// its 32 elements in turn, longer than a short exponent's products.  Limbs rippled
+// one by one, from the sums and ~M', ~N as in the other form.  300,000 powers, one
+// wave per element -> this: k = 2 180 -> 142 us, k = 3 274 -> 235, k = 5 626 -> 589.
+template <int K, int W, int MT, int NT>
+__device__ __forceinline__ void mfma_exit_lanes(const gu32 *__restrict__ mb, const gu32 *__restrict__ mk,
+                                                const uint64_t *tsum, const uint32_t *rl, uint32_t Mpinv_r, int lane,
+                                                const MJob &J, int e0, int ne) {
+    using S = MShp<K, W, MT, NT>;
+    if (lane >= ne) return;
+    uint32_t N[K + 1], v[K + 1];
+    int t = 0;
+#pragma unroll
+    for (int l = 0; l <= K; l++) {
+        N[l] = l < K ? mk[S::LY.Nl() + l] : 0u;
+        if (N[l]) t = l;
+    }
+    auto at = [&](const uint32_t (&x)[K + 1], int l) {           // 0 outside
+        uint32_t r = 0;
+#pragma unroll
+        for (int i = 0; i <= K; i++) r = i == l ? x[i] : r;
+        return r;
+    };
+    const uint64_t *T = tsum + lane * S::XSLOTS;
+    const uint32_t alpha = ((uint32_t)T[0] - rl[lane]) * Mpinv_r;                                // in [0, K)
+    uint64_t cy = alpha;
+#pragma unroll
+    for (int l = 0; l <= K; l++) {
+        const uint64_t s = T[l] + (uint64_t)alpha * (uint32_t)~mb[S::LY.MpF() + l] + cy;
+        v[l] = (uint32_t)s;
+        cy = s >> 32;
+    }
+    const double nd = (double)at(N, t) + (double)at(N, t - 1) * 0x1p-32;
+    const double q0 = limbs_estimate(at(v, t + 1), at(v, t), at(v, t - 1), nd);
+    const uint32_t q = q0 > 0.0 ? (uint32_t)q0 : 0u;
+    cy = q;
+#pragma unroll
+    for (int l = 0; l <= K; l++) {
+        const uint64_t s = v[l] + (uint64_t)q * (uint32_t)~N[l] + cy;
+        v[l] = (uint32_t)s;
+        cy = s >> 32;
+    }
+    uint32_t d[K + 1];
+    cy = 1;
+#pragma unroll
+    for (int l = 0; l <= K; l++) {
+        const uint64_t s = (uint64_t)v[l] + (uint32_t)~N[l] + cy;
+        d[l] = (uint32_t)s;
+        cy = s >> 32;
+    }
+    gu32 *__restrict__ o = (gu32 *)J.out + (size_t)(e0 + lane) * J.out_stride;
+#pragma unroll
+    for (int l = 0; l < K; l++)
+        if (l < J.L) o[l] = cy ? d[l] : v[l];
+}
+
 // Leave the RNS: buf2 holds the digits xi' of the exit product, r its
 // redundant residues.  The limb sums of sum_j xi'_j M'_j are one more
 // contraction of those digits, on the matrix cores with the base's exit tiles
@@ -845,7 +907,8 @@ __device__ __forceinline__ void mfma_entry(const MJob &J, const uint32_t *__rest
     }
 }
 
-// The entry of one wave's tile, 16 elements at a time (wl: 16 rows).
+// The entry of one wave's tile, 16 elements at a time (wl: 16 rows), or all at once
+// (WAVE_WHOLE).
 template <int K, int MT, int NT, class C>
 __device__ __forceinline__ void wave_entry(const MJob &J, int e0, uint32_t *__restrict__ wl, int lane, const C &c,
                                            MState<MT, NT> &a) {
@@ -855,6 +918,13 @@ __device__ __forceinline__ void wave_entry(const MJob &J, int e0, uint32_t *__re
         const MSlotB sb = c.slotB(mt);
         const MSlotP sp = c.slotP(mt);
         mB[mt] = sb.m, uB[mt] = sb.u, mP[mt] = sp.m, uP[mt] = sp.u;
+    }
+    if constexpr (MShp<K, 1, MT, NT>::WAVE_WHOLE) {
+        mfma_stage_inputs<1, 16 * NT>(J, e0, wl, 0, lane);
+        wave_sync();
+        mfma_entry<MShp<K, 1, MT, NT>::ECOLS, 4 * MT, MT, NT>(J, wl, 0, lane, mB, uB, mP, uP, a);
+        wave_sync();
+        return;
     }
 #pragma unroll
     for (int nt = 0; nt < NT; nt++) {

@@ -225,6 +225,10 @@ struct WaveEngine {
     }
     // the redundant row's low word, in every lane of its element
     __device__ __forceinline__ uint32_t redundant(const mfma_v4i &D) const {
+        // one tile: few instructions, so the copies that the swaps need count (300,000
+        // powers at k = 3 236 us with them, 213 us through LDS; a lone one 56 us either way)
+        if constexpr (MT == 1)
+            return (uint32_t)__builtin_amdgcn_ds_bpermute(((lane & 15) + 48) * 4, (int)mfma_combine_lo(D));
         uint32_t g2, g3;
         lane_groups_23(mfma_combine_lo(D), g2, g3);
         return g3;
@@ -864,7 +868,7 @@ __device__ __forceinline__ void modexp_wave_tile(const MJob &J, int e0, uint32_t
     }
     gcv4i *xt = (gcv4i *)(mb + S::LY.xt());
     uint64_t *tsum = (uint64_t *)wl;
-    uint32_t *rl = wl + 2 * 16 * S::XSLOTS;
+    uint32_t *rl = wl + 2 * (S::WAVE_WHOLE ? 16 * NT : 16) * S::XSLOTS;
     mfma_v4i D[MT][NT];
 #pragma unroll
     for (int mt = 0; mt < MT; mt++) {
@@ -880,6 +884,20 @@ __device__ __forceinline__ void modexp_wave_tile(const MJob &J, int e0, uint32_t
         }
     }
     const int left = J.batch - e0, ne = left < te ? left : te;
+    if constexpr (S::WAVE_WHOLE) {
+        wave_sync();
+#pragma unroll
+        for (int nt = 0; nt < NT; nt++) {
+#pragma unroll
+            for (int mt = 0; mt < MT; mt++)
+                tsum[(16 * nt + (lane & 15)) * S::XSLOTS + 4 * mt + (lane >> 4)] =
+                    mfma_accumulate<S::PAIR_I32>(D[mt][nt], kExitOffset, w.kf);
+            if (lane < 16) rl[16 * nt + lane] = a.r[nt];
+        }
+        wave_sync();
+        mfma_exit_lanes<K, 1, MT, NT>(mb, mk, tsum, rl, w.Mpinv_r, lane, J, e0, ne);
+        return;
+    }
 #pragma unroll
     for (int nt = 0; nt < NT; nt++) {
         wave_sync();

@@ -104,15 +104,18 @@ __device__ __forceinline__ double limbs_top(const uint32_t (&n)[C], int t) {
     return (double)limb_at(n, t) + (t ? (double)limb_at(n, t - 1) * 0x1p-32 : 0.0);
 }
 
-// floor(v / n) or one less, for v / n < 2^11; t = top_limb(n), nd =
-// limbs_top(n, t) >= 1.  The limbs left out of either top change the
+// An estimate of v / n below 2^11 from three limbs of v, the middle one at n's top,
+// and n's top two as a double, nd >= 1.  The limbs left out of either change the
 // quotient's value by less than 2^11 (2^-31 + 2^-50), so the estimate lowered by
-// 2^-19 is below it by less than 2^-18.
+// 2^-19 is below it by less than 2^-18: its integer part is floor(v / n) or one less.
+__device__ __forceinline__ double limbs_estimate(uint32_t above, uint32_t top, uint32_t below, double nd) {
+    return ((double)above * 0x1p32 + (double)top + (double)below * 0x1p-32) / nd - 0x1p-19;
+}
+
+// floor(v / n) or one less, for v / n < 2^11; t = top_limb(n), nd = limbs_top(n, t).
 template <int C>
 __device__ __forceinline__ uint32_t limbs_quotient(const uint32_t (&v)[C], int t, double nd) {
-    const double x = (double)limb_at(v, t + 1) * 0x1p32 + (double)limb_at(v, t) +
-                     (t ? (double)limb_at(v, t - 1) * 0x1p-32 : 0.0);
-    const double q = x / nd - 0x1p-19;
+    const double q = limbs_estimate(limb_at(v, t + 1), limb_at(v, t), t ? limb_at(v, t - 1) : 0u, nd);
     return (uint32_t)__builtin_amdgcn_readfirstlane(q > 0.0 ? (int)q : 0);
 }
 

@@ -144,8 +144,10 @@ struct MLayout {
     // 5 k-steps) take it.
     constexpr bool sq_ok() const { return KSTEPS() <= 5; }
     // Whether the scaled form's second extension can be the wide one; its estimate
-    // row is slot 4 MT - 2, before the redundant one.
-    constexpr bool wide() const { return W == 1 && K <= 4 * MT - 2; }
+    // row is slot 4 MT - 2, before the redundant one.  Not with one tile, where the
+    // estimate costs what the narrow form's reductions do (k = 2: 130 and 128 vector
+    // instructions a product).
+    constexpr bool wide() const { return W == 1 && MT > 1 && K <= 4 * MT - 2; }
     // scaled form (sq_ok shapes): [W][MT][KSTEPS][64][4] second extension
     // with output row t times s_t, then [W][MT][4][64] nu s, R s (the unit),
     // (M mod N) R s (one), nu2 s (wide form)

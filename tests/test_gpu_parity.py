@@ -327,6 +327,26 @@ def test_spread_launches(bits, n, opts):
                           _run_modexp(_ctx(N, L, engine=ENGINE_CHANNEL), bases, e))
 
 
+@pytest.mark.parametrize("limbs,k", [(1, 2), (2, 3), (3, 5), (4, 5), (7, 9), (8, 9)])
+def test_exit_of_small_bases(limbs, k):
+    """Leaving the bases of up to 9 channels, one element per lane: moduli whose top
+    limb is the first, the last or one between (rows padded with zero limbs),
+    the smallest and largest of each, results 0, 1 and n - 1, ragged ends of a
+    wave's 32 elements; every output equals Python's pow."""
+    rng = random.Random(limbs)
+    moduli = {2, 3, (1 << 32 * limbs) - 1}
+    for l in range(limbs):
+        moduli |= {(1 << 32 * l) + 1, (1 << 32 * (l + 1)) - 1, rng.getrandbits(32 * l + 17) | (1 << 32 * l + 16) | 1}
+    for i, N in enumerate(sorted(m for m in moduli if m > 1)):
+        ctx = _ctx(N, limbs)
+        assert ctx.info["k"] == k
+        n = (1, 33, 48, 67, 130)[i % 5]
+        vals = [[0, 1, N - 1, N, (1 << 32 * limbs) - 1][j] if j < 5 else rng.getrandbits(32 * limbs) for j in range(n)]
+        for e in (1, 2, 65537, rng.getrandbits(40)):
+            got = _run_modexp(ctx, gen.to_limbs(vals, limbs), gen.to_limbs(e, 2)[0])
+            assert oracle.rows_to_ints(got) == [pow(v, e, N) for v in vals], (N, e)
+
+
 @pytest.mark.parametrize("bits", [96, 1024, 2048])
 @pytest.mark.parametrize("limbs", [1, 2, 3])
 def test_window_width_by_exponent(bits, limbs):
