@@ -181,8 +181,8 @@ __device__ __forceinline__ uint32_t td_group(const TdArgs &A, int t, const int *
     return mask;
 }
 
-// Trial division in two passes.  First pass (blockIdx.x: kTdGroup candidates):
-// the first kTdThreads primes, which find a factor in about 85% of random odd
+// Trial division in two passes, in one for few primes.  First pass (blockIdx.x:
+// kTdGroup candidates): the first kTdThreads primes (or all), which find a factor in about 85% of random odd
 // candidates; writes every flag.  Second pass (blockIdx.x: span candidates,
 // blockIdx.y: kTdThreads further primes): only the candidates still flagged,
 // compacted in LDS; clears the flags of those it finds a factor of.
@@ -194,8 +194,7 @@ __global__ __launch_bounds__(kTdThreads) void trial_first_kernel(TdArgs A) {
     if (threadIdx.x < kTdGroup) list[threadIdx.x] = c0 + threadIdx.x;
     if (threadIdx.x == 0) found = 0;
     __syncthreads();
-    const int t = A.p0 + threadIdx.x;
-    if (t < A.p1) {
+    for (int t = A.p0 + (int)threadIdx.x; t < A.p1; t += kTdThreads) {
         const uint32_t mask = td_group(A, t, list, n);
         if (mask) atomicOr(&found, mask);
     }
@@ -463,15 +462,20 @@ int rsa_trial_division(const uint32_t *cand, size_t count, int limbs, int n_prim
     a.limbs = limbs;
     a.count = (int)count;
     a.p0 = 0;
-    a.p1 = std::min(n_primes, kTdThreads);
+    // up to 512 primes in the first pass, two rounds at most (100 1024-bit candidates by
+    // 500 primes 8.2 us, with a second pass 11.1; 20,000 22 us; three rounds for 768
+    // primes 31 us, with a second pass 26)
+    a.p1 = n_primes <= 2 * kTdThreads ? n_primes : kTdThreads;
     hipLaunchKernelGGL(trial_first_kernel, dim3((unsigned)((count + kTdGroup - 1) / kTdGroup)), dim3(kTdThreads), 0,
                        (hipStream_t)hip_stream, a);
-    if (n_primes > kTdThreads) {
+    if (a.p1 < n_primes) {
         // about 15% of the candidates are left: 512 per workgroup fill about
-        // ten groups of 8; fewer candidates are spread wider instead
+        // ten groups of 8; fewer candidates are spread wider instead (128 and 512 per
+        // workgroup, 1024-bit candidates: 1,000 17.6 and 31 us, 20,000 72.6 and 76.8,
+        // 40,000 131.7 and 130.0, 100,000 303 and 268; the same at 64 to 4,096 bits)
         a.p0 = kTdThreads;
         a.p1 = n_primes;
-        a.span = count >= 16384 ? kTdMaxList : 128;
+        a.span = count >= 32768 ? kTdMaxList : 128;
         hipLaunchKernelGGL(trial_rest_kernel,
                            dim3((unsigned)((count + a.span - 1) / a.span),
                                 (unsigned)((n_primes - kTdThreads + kTdThreads - 1) / kTdThreads)),

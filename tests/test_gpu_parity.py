@@ -1149,6 +1149,23 @@ def test_trial_division_edges(limbs, count, n_primes):
     assert [int(v) for v in got] == want
 
 
+@pytest.mark.parametrize("count,n_primes", [(33, 511), (33, 512), (33, 513), (32767, 600), (32769, 600), (32769, 512)])
+def test_trial_division_pass_lines(count, n_primes):
+    """Prime counts around the one-pass limit of 512, candidate counts around the
+    second pass's line of 32,768: odd rows of two limbs, every 7th a multiple of the
+    last prime used or of the next one."""
+    from paper_1305_3699_amd import trial_division
+    pr = primality.small_primes(10000)
+    vals = np.random.default_rng(count + n_primes).integers(0, 1 << 62, size=count, dtype=np.uint64) | np.uint64(1)
+    for i, p in ((0, pr[n_primes - 1]), (7, pr[n_primes])):
+        vals[i::14] = vals[i::14] // np.uint64(p) * np.uint64(p)
+    want = np.ones(count, dtype=np.uint8)
+    for p in pr[:n_primes]:
+        want[vals % np.uint64(p) == 0] = 0
+    rows = np.ascontiguousarray(vals).view(np.uint32).reshape(count, 2)
+    assert np.array_equal(_flags(trial_division(_dev(rows), n_primes=n_primes)), want)
+
+
 def _mr_case(cands, rounds, limbs, seed):
     from paper_1305_3699_amd import miller_rabin
     rng = random.Random(seed)
