@@ -363,8 +363,9 @@ bool emul_modexp_mfma(const ModPlan &mp, const MfmaTables &T, const std::vector<
                 acc[l] = (uint32_t)v;
                 cy = v >> 32;
             }
-            // the value is below (K+2) N: subtract N until it is canonical
-            for (;;) {
+            // the value is below (2 K + 1) N, (K + 1) N on other keys than wide ones: subtract N
+            // until it is canonical
+            for (int left = c.T.wide ? 2 * K : K;; left--) {
                 std::vector<uint32_t> d(K + 1);
                 uint64_t c1 = 1;
                 for (int l = 0; l <= K; l++) {
@@ -373,6 +374,10 @@ bool emul_modexp_mfma(const ModPlan &mp, const MfmaTables &T, const std::vector<
                     c1 = v >> 32;
                 }
                 if (!c1) break;
+                if (left == 0) {
+                    t_in_range = false;
+                    break;
+                }
                 acc = d;
             }
             std::copy(acc.begin(), acc.begin() + L, out + (g0 + e) * (size_t)L);

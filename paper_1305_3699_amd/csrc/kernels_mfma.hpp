@@ -47,6 +47,9 @@ struct MShp {
     static constexpr int XSLOTS = 4 * W * MT;
     static constexpr int EXIT_WORDS = (2 * XSLOTS + 1) * NM;
     static_assert(XSLOTS > K, "a limb slot for each of the exit's K + 1 limbs");
+    // the quotient of an exit product is at most 2 K M (wide form; K M otherwise), so its
+    // value is below (2 K + 1) N
+    static_assert(2 * K + 1 < 1 << 11, "the exit's quotient by N is one estimate (limbs_estimate)");
     // The exchange buffers (the entry stages its inputs there); a single wave
     // exchanges nothing
     static constexpr bool WAVE = W == 1;
@@ -627,7 +630,7 @@ __device__ __forceinline__ void mfma_exit_limbs(const gu32 *__restrict__ mb, con
         limbs_of_sums<LC>(T, v, lane);
 #pragma unroll
         for (int c = 0; c < LC; c++) v[c] = 64 * c + lane <= K ? v[c] : 0u;
-        const uint32_t q = limbs_quotient<LC>(v, t, nd);        // the value is below (K + 2) N
+        const uint32_t q = limbs_quotient<LC>(v, t, nd);        // the value is below (2 K + 1) N
 #pragma unroll
         for (int c = 0; c < LC; c++) T[c] = v[c] + (uint64_t)q * (uint32_t)~N[c];                // - q N
         if (lane == 0) T[0] += q;
