@@ -119,7 +119,6 @@ int mfma_tiles(const MLayout &shape, size_t elements);
 int mfma_job_tiles(const MLayout &shape, size_t elements, int tile_elems);
 // Fewest elements a tile is given when a small launch is spread out.
 constexpr int kMinTileElems = 4;
-bool mfma_supported(int K);
 int mfma_blocks_per_cu(const MLayout &shape);
 hipError_t launch_modexp_mfma(const MLayout &shape, const ModexpMfmaLaunch &a, hipStream_t s);
 hipError_t launch_montmul_mfma(const MLayout &shape, const MontMulMfmaLaunch &a, hipStream_t s);

@@ -35,14 +35,6 @@ hipError_t launch_montmul_mfma_t(const MontMulMfmaLaunch &a, hipStream_t s);
 #include "kernel_configs_mfma.inc"
 #undef RNSRSA_MSHAPE
 
-bool mfma_supported(int K) {
-#define RNSRSA_MSHAPE(k, w, mt, nt) \
-    if (K == k) return true;
-#include "kernel_configs_mfma.inc"
-#undef RNSRSA_MSHAPE
-    return false;
-}
-
 size_t modexp_mfma_table_words(const MLayout &s, int max_window, size_t workgroups) {
     return workgroups * ((size_t)1 << max_window) * (size_t)s.W * s.SLOTS() * 64;
 }

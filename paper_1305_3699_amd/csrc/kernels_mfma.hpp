@@ -1514,15 +1514,15 @@ hipError_t launch_montmul_mfma_t(const MontMulMfmaLaunch &a, hipStream_t s) {
     return hipGetLastError();
 }
 
-// Resident tiles per CU of the kernel for this shape (occupancy).
+// Resident workgroups per CU of the kernel for this shape (occupancy); 0 for the
+// shapes with W = 1, whose tile is chosen without it.
 template <int K, int W, int MT, int NT>
 int mfma_blocks_per_cu_t() {
     int n = 0;
-    using S = MShp<K, W, MT, NT>;
-    if constexpr (!S::LY.team())
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, modexp_mfma_kernel<K, W, MT, NT, kPlain>, S::THREADS, 0) != hipSuccess)
-        return 0;
-    return n * (S::WAVE ? S::WAVE_GROUP : 1);
+    if constexpr (W > 1)
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, modexp_mfma_kernel<K, W, MT, NT, kPlain>, 64 * W, 0) != hipSuccess)
+            return 0;
+    return n;
 }
 
 }  // namespace rnsrsa

@@ -173,7 +173,7 @@ int64_t est_weight(uint32_t g, uint32_t m) { return (int64_t)(((uint64_t)g * kEs
 // of 2^32; step (iv)'s sum is positive and, but in the first tile (whose
 // reduction takes any sum below 2^64), small enough to leave a result below
 // 2^32 without a correction.
-bool wide_fits(const ModPlan &mp, const MLayout &ly, const std::vector<uint32_t> &nu2, long double gsum) {
+bool wide_fits(const ModPlan &mp, const std::vector<uint32_t> &nu2, long double gsum) {
     const BaseSet &bs = *mp.base;
     const int K = bs.K;
     const Limbs c = bn_from_u64((uint64_t)2 * K + 1);
@@ -192,7 +192,7 @@ bool wide_fits(const ModPlan &mp, const MLayout &ly, const std::vector<uint32_t>
         const uint64_t hi = (1ull << kWideShift) + ah + (smax >> 32) + 2;   // bound of the sum over 2^32
         if (m + hi >= 1ull << 32) return false;
     }
-    return ly.MT >= 1;
+    return true;
 }
 
 // Per-lane slot table [W][MT][64] of f(channel) (channel -1 or >= K: junk).
@@ -271,7 +271,7 @@ MfmaTables make_mfma_tables(const ModPlan &mp, const MfmaShape &sh, bool with_ba
         }
         // a base whose primes lie too close to 2^32 (at k = 65 most draws) keeps the
         // scaled form with the narrow second extension
-        out.wide = wide = wide_fits(mp, ly, nu2, gsum);
+        out.wide = wide = wide_fits(mp, nu2, gsum);
     }
     if (!out.scaled) {
         std::fill(sgn.begin(), sgn.end(), 1);
