@@ -291,8 +291,21 @@ MfmaShape auto_tile(const MfmaShape &sh, size_t tiles, int dev, bool small_jobs)
 // tiles) 55 and 77 us.  At exactly one tile per SIMD some workgroups wait for a
 // second round now and then (8,192 decryptions: 1.53 to 2.0 ms split), hence the 64th
 // left out; above it they all do (16,384: 3.2 ms, 2.45 ms on single waves).
-bool split_tiles(const MfmaShape &sh, size_t tiles, int dev) {
-    return sh.split_waves() && 64 * tiles <= 63 * (size_t)device_simds(dev);
+// A single-wave workgroup serves one job, so where jobs of a few tiles leave many of
+// its four waves idle, the kernel whose rounds end first runs: a CU holds two
+// single-wave workgroups, or four of the split kernel's, whose rounds take, in 0.1 ms
+// of a 1024-bit power, 24 (16 if the last has at most one per CU) and 15 (9, 11 up to
+// two).  1,100 candidates with 5 bases, single and split: 6.6 and 3.5 ms; 600 jobs of 20
+// powers 3.7 and 2.4 ms, 300 of 70 4.0 and 2.5 ms; 200 of 100, one round, 2.3 ms single.
+bool split_tiles(const MfmaShape &sh, size_t tiles, size_t groups, int dev) {
+    const size_t simds = (size_t)device_simds(dev), cus = simds / 4;
+    if (!sh.split_waves() || !cus) return false;
+    if (64 * tiles <= 63 * simds) return true;
+    if (8 * tiles >= 7 * kWaveGroup * groups) return false;
+    const size_t r1 = groups % (2 * cus), r3 = tiles % simds;
+    const size_t single = groups / (2 * cus) * 24 + (r1 == 0 ? 0 : r1 <= cus ? 16 : 24);
+    const size_t split = tiles / simds * 15 + (r3 == 0 ? 0 : r3 <= cus ? 9 : r3 <= 2 * cus ? 11 : 15);
+    return split < single;
 }
 
 // Shapes with W = 1 spread only while the launch keeps within one workgroup per CU
@@ -380,7 +393,7 @@ int run_modexp(const rns_ctx *c0, const rns_ctx *c1, const uint32_t *E0, const u
         a.njobs = njobs;
         a.tiles = per_job * njobs;
         a.groups = sh.groups(per_job) * njobs;
-        a.split = split_tiles(sh, (size_t)a.tiles, c0->device);
+        a.split = split_tiles(sh, (size_t)a.tiles, (size_t)a.groups, c0->device);
         a.max_window = c0->window;
         a.form = njobs < 2 || c1->mform == c0->mform ? c0->mform : kPlain;
         Scratch table;

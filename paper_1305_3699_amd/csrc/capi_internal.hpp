@@ -131,8 +131,9 @@ GarnerLaunch garner_launch_of(const rsa_key *key, const uint32_t *mpq, uint32_t 
 MfmaShape auto_tile(const MfmaShape &sh, size_t tiles, int dev, bool small_jobs = false);
 // SIMDs of device dev (4 per compute unit), cached; 0 if unknown.
 int device_simds(int dev);
-// Whether a launch of `tiles` tiles of shape sh runs the split kernel.
-bool split_tiles(const MfmaShape &sh, size_t tiles, int dev);
+// Whether a launch of `tiles` tiles of shape sh, in `groups` workgroups of single
+// waves, runs the split kernel.
+bool split_tiles(const MfmaShape &sh, size_t tiles, size_t groups, int dev);
 // Elements per tile for a matrix-core launch of `tiles` full tiles of shape
 // sh on device dev: 0 (all 16*NT columns) unless the launch would leave
 // SIMDs without a wave; then the largest of 16*NT/2, /4, ... down to

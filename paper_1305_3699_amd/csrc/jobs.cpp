@@ -223,7 +223,7 @@ hipError_t launch_group(const JobGroup &g, const MJob *d_jobs, uint32_t *table, 
     a.njobs = (int)g.jobs.size();
     a.tiles = g.tiles;
     a.groups = g.groups;
-    a.split = split_tiles(g.shape, (size_t)g.tiles, g.device);
+    a.split = split_tiles(g.shape, (size_t)g.tiles, (size_t)g.groups, g.device);
     a.max_window = g.max_window;
     a.table = table;
     a.form = g.form;

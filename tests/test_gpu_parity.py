@@ -327,6 +327,23 @@ def test_spread_launches(bits, n, opts):
                           _run_modexp(_ctx(N, L, engine=ENGINE_CHANNEL), bases, e))
 
 
+@pytest.mark.parametrize("njobs,n", [(1009, 1), (600, 20), (300, 70), (200, 100), (130, 130)])
+def test_launches_of_many_small_jobs(njobs, n):
+    """More tiles than SIMDs in jobs that leave waves of a single-wave workgroup idle
+    (k = 33): the split kernel or single waves, by the rounds of each; outputs equal
+    the channel engine's."""
+    from paper_1305_3699_amd import ENGINE_CHANNEL, modexp_jobs
+    rng = random.Random(njobs)
+    N, L = rng.getrandbits(1024) | (1 << 1023) | 1, 32
+    bases = np.frombuffer(rng.randbytes(4 * njobs * n * L), dtype=np.uint32).reshape(njobs * n, L).copy()
+    bases[:, -1] &= 0x7FFFFFFF
+    e = gen.to_limbs(rng.getrandbits(40) | 1, 2)[0]
+    ctx, d, x = _ctx(N, L), _dev(bases), _dev(e)
+    outs = modexp_jobs([(ctx, d[i * n:(i + 1) * n], x) for i in range(njobs)])
+    got = np.concatenate([_host(o) for o in outs])
+    assert np.array_equal(got, _run_modexp(_ctx(N, L, engine=ENGINE_CHANNEL), bases, e))
+
+
 @pytest.mark.parametrize("limbs,k", [(1, 2), (2, 3), (3, 5), (4, 5), (7, 9), (8, 9)])
 def test_exit_of_small_bases(limbs, k):
     """Leaving the bases of up to 9 channels, one element per lane: moduli whose top
