@@ -51,8 +51,7 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=" + ARCH,
 # measured 3-19% faster per launch than the default scheduler on these (k = 33:
 # 16,384 RSA-2048 CRT decryptions 2.53 ms, 2.75 ms with the default; RSA-16384
 # plain decryption +19%); k = 49 measured 3% slower and its 32-element tile does
-# not compile with it, nor does k = 17's, and the small test bases keep the
-# default.  The split kernel keeps it too (8,192 decryptions 1.55 ms, 1.84 ms with
+# not compile with it, and k = 17 and the small bases keep the default.  The split kernel keeps it too (8,192 decryptions 1.55 ms, 1.84 ms with
 # the ILP one).
 ILP_SCHED_K = {33, 65, 66, 97, 129, 257, 513}
 ILP_SCHED = ["-mllvm", "-amdgpu-sched-strategy=iterative-ilp"]

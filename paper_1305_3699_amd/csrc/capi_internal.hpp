@@ -124,10 +124,9 @@ int crt_combine(const rsa_key *key, const uint32_t *mpq, uint32_t *m, size_t bat
 GarnerLaunch garner_launch_of(const rsa_key *key, const uint32_t *mpq, uint32_t *m, size_t batch);
 // Tile of one matrix-core launch of `tiles` workgroups of shape sh on device
 // dev: the 16-element tile of the same (K, W, MT) instead of the 32-element one
-// when the latter would leave fewer than 1.5 resident waves per SIMD.  Below
-// that the smaller tile's shorter per-wave work (and twice the workgroups)
-// wins; above it the 32-element tile's shared constant loads do (measured for
-// k = 17 .. 129).  Shapes without that alternative are returned unchanged.
+// when the latter's workgroups would not fill every CU's resident slots, for
+// a team when the 16-element tiles' rounds over the CUs end first, and for jobs of a
+// few elements each.  Shapes without that alternative are returned unchanged.
 MfmaShape auto_tile(const MfmaShape &sh, size_t tiles, int dev, bool small_jobs = false);
 // SIMDs of device dev (4 per compute unit), cached; 0 if unknown.
 int device_simds(int dev);

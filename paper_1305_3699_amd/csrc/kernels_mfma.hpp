@@ -68,17 +68,14 @@ struct MShp {
     static constexpr int TEAM_OPERANDS = 32 * MT + TEAM_TILES * KSTEPS * 256 + (8 * KSTEPS + 1) * NT * 64;
     static constexpr int TEAM_IO = TEAM_OPERANDS + (2 * MT + TEAM_WAVES) * NT * 64;
     static constexpr int TEAM_WORDS = TEAM_IO + 16 * NT * (2 * K + 1 > 2 * XSLOTS + 1 ? 2 * K + 1 : 2 * XSLOTS + 1);
-    // Single-wave shapes: waves of a workgroup, the LDS words each needs (16
-    // elements' inputs, then a product's second operand, then 16 elements'
-    // limb sums), and the words of the constants they share
+    // Single-wave shapes: waves of a workgroup, the LDS words each needs (its elements'
+    // inputs, then a product's second operand, then their limb sums), and the
+    // words of the constants they share
     static constexpr int WAVE_GROUP = kWaveGroup;
-    static constexpr int WAVE_IO_WORDS = 16 * (2 * K + 1) > (2 * XSLOTS + 1) * 16 ? 16 * (2 * K + 1) : (2 * XSLOTS + 1) * 16;
+    static constexpr int WAVE_IO_WORDS = NM * (2 * K + 1 > 2 * XSLOTS + 1 ? 2 * K + 1 : 2 * XSLOTS + 1);
     static constexpr int WAVE_WORDS = ((WAVE_IO_WORDS > SLOTS * 64 ? WAVE_IO_WORDS : SLOTS * 64) + 3) & ~3;
-    // The smallest bases: a wave's part of LDS holds all its elements' inputs and limb
-    // sums, not only 16 elements', and the exit takes one element per lane
-    static constexpr bool WAVE_WHOLE = WAVE && K <= 9;
-    static_assert(!WAVE_WHOLE || (NM <= 64 && NM * (2 * K + 1) <= WAVE_WORDS && NM * (2 * XSLOTS + 1) <= WAVE_WORDS),
-                  "inputs and limb sums of the whole tile");
+    // The smallest bases leave the RNS with one element per lane
+    static constexpr bool EXIT_LANES = WAVE && K <= 9;
     static constexpr int WAVE_TILE_WORDS = 2 * MT * KSTEPS * 64 * 4 + MT * 32;
     static constexpr int WAVE_MM_WORDS = (NT == 1 ? 1 : 2) * MT * KSTEPS * 64 * 4 + MT * 32;   // a standalone product's
     static constexpr int WORK_WORDS = EXIT_WORDS > BUF_WORDS ? EXIT_WORDS : BUF_WORDS;
@@ -910,8 +907,7 @@ __device__ __forceinline__ void mfma_entry(const MJob &J, const uint32_t *__rest
     }
 }
 
-// The entry of one wave's tile, 16 elements at a time (wl: 16 rows), or all at once
-// (WAVE_WHOLE).
+// The entry of one wave's tile (wl: its part of LDS).
 template <int K, int MT, int NT, class C>
 __device__ __forceinline__ void wave_entry(const MJob &J, int e0, uint32_t *__restrict__ wl, int lane, const C &c,
                                            MState<MT, NT> &a) {
@@ -922,27 +918,9 @@ __device__ __forceinline__ void wave_entry(const MJob &J, int e0, uint32_t *__re
         const MSlotP sp = c.slotP(mt);
         mB[mt] = sb.m, uB[mt] = sb.u, mP[mt] = sp.m, uP[mt] = sp.u;
     }
-    if constexpr (MShp<K, 1, MT, NT>::WAVE_WHOLE) {
-        mfma_stage_inputs<1, 16 * NT>(J, e0, wl, 0, lane);
-        wave_sync();
-        mfma_entry<MShp<K, 1, MT, NT>::ECOLS, 4 * MT, MT, NT>(J, wl, 0, lane, mB, uB, mP, uP, a);
-        wave_sync();
-        return;
-    }
-#pragma unroll
-    for (int nt = 0; nt < NT; nt++) {
-        MState<MT, 1> h;
-        wave_sync();
-        mfma_stage_inputs<1, 16>(J, e0 + 16 * nt, wl, 0, lane);
-        wave_sync();
-        mfma_entry<MShp<K, 1, MT, NT>::ECOLS, 4 * MT, MT, 1>(J, wl, 0, lane, mB, uB, mP, uP, h);
-#pragma unroll
-        for (int mt = 0; mt < MT; mt++) {
-            a.b[mt][nt] = h.b[mt][0];
-            a.p[mt][nt] = h.p[mt][0];
-        }
-        a.r[nt] = h.r[0];
-    }
+    mfma_stage_inputs<1, 16 * NT>(J, e0, wl, 0, lane);
+    wave_sync();
+    mfma_entry<MShp<K, 1, MT, NT>::ECOLS, 4 * MT, MT, NT>(J, wl, 0, lane, mB, uB, mP, uP, a);
 }
 
 // M mod N in the kept representation (M tiles from tile0 on) into a table entry.

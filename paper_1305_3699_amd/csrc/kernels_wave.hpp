@@ -15,11 +15,12 @@
 // so a single wave keeps both units busy, with two tiles' results in registers
 // instead of all of them.
 //
-// What bounds it: vector issue, about 330 instructions a product at k = 33, a third
-// of them quarter-rate multiply-adds, beside 54 matrix instructions of 16 cycles.
-// Three waves with three tiles each, digits
-// exchanged through LDS between two barriers, kept the vector unit 58% and the
-// matrix cores 28% busy, hardly at the same time.  RSA-2048 CRT decryptions
+// What bounds it: about 290 vector instructions a product at k = 33, multiply-adds
+// among them at the full rate, and 54 matrix instructions of 16 cycles.  Issuing both keeps
+// the vector unit 63% and the matrix cores 39% busy (16,384 decryptions), which
+// together is the whole time: with two waves per SIMD the two units still take turns.
+// Three waves with three tiles each, digits exchanged through LDS between two
+// barriers, kept them 58% and 28% busy.  RSA-2048 CRT decryptions
 // (k = 33): 16,384 in 3.17 -> 2.45 ms, 32,768 in 6.96 -> 4.93 ms; RSA-1024 (k =
 // 17) 16,384 in 1.04 -> 0.70 ms.
 #pragma once
@@ -163,7 +164,7 @@ struct WaveEngine {
     // longer than its issue, so G NT chains are interleaved.
     // Steps of one tile with the first extension's tiles in registers measured
     // best for 16 elements (16,384 decryptions: 2.53 ms; two tiles and every tile
-    // from LDS 2.66 ms), two tiles for 32, whose registers hold no tiles (2.71 ms).
+    // from LDS 2.66 ms); two tiles for 32 (k <= 9), whose registers hold none.
     static constexpr int G = NT == 1 ? 1 : 2;
     __device__ __forceinline__ void load_tiles() {
         if (A1REG)
@@ -856,7 +857,7 @@ __device__ __forceinline__ void modexp_wave_tile(const MJob &J, int e0, uint32_t
     w.load_tiles();
     wave_exponent<K, MT, F != kPlain, MT, NT>(J, e0, w, 0, lane, (gu32 *)table + (slot << max_window) * (S::SLOTS * 64) + lane, wl, true);
 
-    // leave the RNS (see mfma_exit), one group of 16 elements at a time
+    // leave the RNS (see mfma_exit)
     if constexpr (decltype(w)::WIDE) {                           // the digits xi' = r (M'_t)^-1
 #pragma unroll
         for (int mt = 0; mt < MT; mt++) {
@@ -868,7 +869,7 @@ __device__ __forceinline__ void modexp_wave_tile(const MJob &J, int e0, uint32_t
     }
     gcv4i *xt = (gcv4i *)(mb + S::LY.xt());
     uint64_t *tsum = (uint64_t *)wl;
-    uint32_t *rl = wl + 2 * (S::WAVE_WHOLE ? 16 * NT : 16) * S::XSLOTS;
+    uint32_t *rl = wl + 2 * S::NM * S::XSLOTS;
     mfma_v4i D[MT][NT];
 #pragma unroll
     for (int mt = 0; mt < MT; mt++) {
@@ -883,33 +884,21 @@ __device__ __forceinline__ void modexp_wave_tile(const MJob &J, int e0, uint32_t
                 D[mt][nt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(t[ks], w.d2[nt].w[ks], D[mt][nt], 0, 0, 0);
         }
     }
-    const int left = J.batch - e0, ne = left < te ? left : te;
-    if constexpr (S::WAVE_WHOLE) {
-        wave_sync();
-#pragma unroll
-        for (int nt = 0; nt < NT; nt++) {
-#pragma unroll
-            for (int mt = 0; mt < MT; mt++)
-                tsum[(16 * nt + (lane & 15)) * S::XSLOTS + 4 * mt + (lane >> 4)] =
-                    mfma_accumulate<S::PAIR_I32>(D[mt][nt], kExitOffset, w.kf);
-            if (lane < 16) rl[16 * nt + lane] = a.r[nt];
-        }
-        wave_sync();
-        mfma_exit_lanes<K, 1, MT, NT>(mb, mk, tsum, rl, w.Mpinv_r, lane, J, e0, ne);
-        return;
-    }
+    wave_sync();
 #pragma unroll
     for (int nt = 0; nt < NT; nt++) {
-        wave_sync();
 #pragma unroll
         for (int mt = 0; mt < MT; mt++)
-            tsum[(lane & 15) * S::XSLOTS + 4 * mt + (lane >> 4)] =
+            tsum[(16 * nt + (lane & 15)) * S::XSLOTS + 4 * mt + (lane >> 4)] =
                 mfma_accumulate<S::PAIR_I32>(D[mt][nt], kExitOffset, w.kf);
-        if (lane < 16) rl[lane] = a.r[nt];
-        wave_sync();
-        mfma_exit_limbs<K, 1, MT, NT>(mb, mk, tsum, rl, w.Mpinv_r, 0, 1, lane, J, e0 + 16 * nt,
-                                      ne - 16 * nt < 16 ? ne - 16 * nt : 16);
+        if (lane < 16) rl[16 * nt + lane] = a.r[nt];
     }
+    wave_sync();
+    const int left = J.batch - e0, ne = left < te ? left : te;
+    if constexpr (S::EXIT_LANES)
+        mfma_exit_lanes<K, 1, MT, NT>(mb, mk, tsum, rl, w.Mpinv_r, lane, J, e0, ne);
+    else
+        mfma_exit_limbs<K, 1, MT, NT>(mb, mk, tsum, rl, w.Mpinv_r, 0, 1, lane, J, e0, ne);
 }
 
 // The same over the WV waves of a workgroup (16 elements).
