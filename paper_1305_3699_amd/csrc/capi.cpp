@@ -288,9 +288,13 @@ MfmaShape auto_tile(const MfmaShape &sh, size_t tiles, int dev, bool small_jobs)
 // A launch with fewer tiles than SIMDs keeps the split kernel's workgroups all
 // resident: 8,000 RSA-2048 decryptions (1,000 tiles) take 1.39 ms split and 1.73
 // ms on single waves, a lone one 0.91 and 1.6 ms, 16,000 RSA-1024 encryptions (1,000
-// tiles) 55 and 77 us.  At exactly one tile per SIMD some workgroups wait for a
-// second round now and then (8,192 decryptions: 1.53 to 2.0 ms split), hence the 64th
-// left out; above it they all do (16,384: 3.2 ms, 2.45 ms on single waves).
+// tiles) 55 and 77 us.  Close to one tile per SIMD it depends on where the launches
+// before left the placement whether some workgroups wait for a second round: at
+// 1,024 tiles with other kernels between, 8,192 decryptions 1.40 to 2.08 ms split
+// (mean 1.85) and 1.75 on single waves, 16,384 powers 1.37 to 2.13 (mean 1.66) and
+// 1.72; at 1,008, 1.39 to 2.02 (mean 1.70); at 988 none waits (1.39).  Hence the 64th
+// left out.  Above one tile per SIMD they all do (16,384 decryptions: 3.2 ms, 2.45 ms
+// on single waves).
 // A single-wave workgroup serves one job, so where jobs of a few tiles leave many of
 // its four waves idle, the kernel whose rounds end first runs: a CU holds two
 // single-wave workgroups, or four of the split kernel's, whose rounds take, in 0.1 ms
